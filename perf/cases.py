@@ -14,7 +14,9 @@ A case names one pass through the public entry points (``System``, ``Batch``, ``
 
 Inputs are made from the seed alone.  Positions are jittered lattices of molecules in the composition the dynamics
 leads to (dumbbells, bonded sites, chains), so that they are quick to make at every size and start free of overlaps.
-Particles are reported by tag, and positions unwrapped, since the engine re-orders particles and folds them.
+Dynamics are reported by tag, with positions unwrapped, since the engine re-orders particles and folds them.  Single
+evaluations take configurations stored along the cells' Morton curve (as a saved run's are), so that the engine's order
+is theirs.
 ``exact`` evaluates the same definitions in FP64 with plain torch.
 """
 import math
@@ -199,12 +201,13 @@ def _assembly(c, rng):
     n3 = int(0.01 * ns)
     n2 = int(0.15 * ns)
     single = n - 2 * n2 - 3 * n3
-    x = _sites(rng, single + n2 + n3, L, 1.0)
+    x = _sites(rng, single + n2 + n3, L, 1.1)        # a triplet's ends lie up to 0.4 from its middle site
     rm = 0.3 * 2.0 ** 0.1
     mid, far = x[single:], _directions(rng, n2 + n3)
     bond = (rm + 0.0013 * np.clip(rng.standard_normal(n2 + n3), -2.5, 2.5))[:, None]
-    pos = np.concatenate([x[:single], mid - 0.5 * bond * far, mid + 0.5 * bond * far,
-                          mid[n2:] + (0.5 * bond[n2:] + rng.uniform(1.05 * rm, 0.45, (n3, 1))) * far[n2:]])
+    lean = np.where(np.arange(n2 + n3) < n2, 0.5, 0.0)[:, None]
+    pos = np.concatenate([x[:single], mid - (1.0 - lean) * bond * far, mid + lean * bond * far,
+                          mid[n2:] + rng.uniform(1.05 * rm, 0.4, (n3, 1)) * far[n2:]])
     types = np.ones(n, np.int32)
     types[:n - ns] = 0
     p = rng.permutation(n)
@@ -319,7 +322,7 @@ def _patchy(c, rng):
 
 _MAKE = dict(dumbbells=_dumbbells, assembly=_assembly, reactive=_reactive, unequal=_unequal, network=_network)
 #: dt and kT of the workloads
-_DYN = dict(dumbbells=(0.001, 0.03), assembly=(0.001, 0.05), network=(0.002, 1.0), batch=(0.002, 0.1), rigid=(0.001, 1.0))
+_DYN = dict(dumbbells=(0.001, 0.03), assembly=(0.001, 0.05), network=(0.001, 1.0), batch=(0.002, 0.1), rigid=(0.001, 1.0))
 
 
 def _inputs(case, seed):
@@ -330,7 +333,19 @@ def _inputs(case, seed):
         return _patchy(case, rng), rng
     if case["kind"] == "stress":
         return None, rng
-    return _MAKE[case["system"]](case, rng), rng
+    s = _MAKE[case["system"]](case, rng)
+    return (_curved(s) if case["kind"] in ("frame", "forces", "hvp") else s), rng
+
+
+def _curved(s, skin=0.3):
+    """The particles sorted along the Morton curve of cells one list radius wide (in FP32, as positions are)."""
+    L = np.float64(s.L)
+    nc = min(256, max(3, int(L / ((float(s.table.rcut.max()) + skin) * (1.0 + 1e-5)))))
+    c = np.clip(np.floor((s.pos + np.float32(0.5 * L)) * np.float32(nc / L)).astype(np.int64), 0, nc - 1)
+    key = sum(((c[:, d] >> b) & 1) << (3 * b + d) for b in range(8) for d in range(3))
+    p = np.argsort(key, kind="stable")
+    s.pos, s.vel, s.types = s.pos[p], s.vel[p], s.types[p]
+    return s
 
 
 def _rows(case, rng):
@@ -366,7 +381,7 @@ def prepare(case, seed):
             edge[B.slots(r), :3] = x.L
         tags = np.concatenate([np.arange(B.offsets[r], B.offsets[r] + len(x.pos)) for r, x in enumerate(s)])
         dt, kT = _DYN["batch"]
-        st.update(S=B, L=torch.from_numpy(edge).cuda(), tags=torch.from_numpy(tags.astype(np.int32)).cuda(),
+        st.update(S=B, L=torch.from_numpy(edge).cuda(), tags=torch.from_numpy(tags.astype(np.int64)).cuda(),
                   cfg=B.integrator(dt=dt, kT=kT, gamma=1.0))
         return st
     S = System.from_workload(s)
@@ -389,11 +404,11 @@ def prepare(case, seed):
         st.update(x=x.cuda().requires_grad_(), a=a.cuda(), theta=th.requires_grad_())
         return st
     S.build()
+    assert bool((S.rtag == torch.arange(S.N, device="cuda")).all())
     if kind == "hvp":
         V = torch.zeros((case["nvec"], case["n"], 4), dtype=torch.float32)
         V[:, :, :3] = _tangents(case, rng)
-        tag = (S.pos[:, 3].view(torch.int32) >> 4).long()
-        st["V"] = V.cuda()[:, tag].contiguous()
+        st["V"] = V.cuda()
         S.reserve_hvp_vectors(case["nvec"])
     return st
 
@@ -414,7 +429,8 @@ def _grad_inputs(s, rng):
 def _state(S, L, rtag):
     """Unwrapped positions and velocities by tag."""
     x = torch.addcmul(S.pos, S.image.to(torch.float32), L)
-    return x.index_select(0, rtag)[:, :3], S.vel.index_select(0, rtag)[:, :3]
+    at = rtag.long()
+    return x[:, :3][at], S.vel[:, :3][at]
 
 
 def run(st):
@@ -423,7 +439,7 @@ def run(st):
     if kind in ("md", "batch"):
         r = S.run(c["steps"], st["cfg"], step0=st["step"], log_period=c["log"])
         st["step"] += c["steps"]
-        rtag = S.rtag if kind == "md" else S.rtag.index_select(0, st["tags"])
+        rtag = S.rtag if kind == "md" else S.rtag[st["tags"]]
         x, v = _state(S, st["L"], rtag)
         return dict(x=x, v=v, ev=r.ev, bonds=r.bonds)
     if kind == "rigid":
@@ -438,12 +454,12 @@ def run(st):
         F, ev = S.compute_forces()
         value, grad = S.soft_bonds(grad=True)
         n = S.bond_count()
-        return dict(F=F.index_select(0, S.rtag), ev=ev, soft=value, grad=grad.index_select(0, S.rtag)[:, :3], bonds=n)
+        return dict(F=F, ev=ev, soft=value, grad=grad[:, :3], bonds=n)
     if kind == "forces":
         F, ev = S.compute_forces(gather={"triplet": False, "gather": True, "sums": "sums"}[c["path"]])
-        return dict(F=F.index_select(0, S.rtag), ev=ev)
+        return dict(F=F, ev=ev)
     if kind == "hvp":
-        return S.hvp_batch(st["V"]).index_select(1, S.rtag)[:, :, :3]
+        return S.hvp_batch(st["V"])[:, :, :3]
     if kind == "grad":
         E = swap_energy(st["M"], st["x"], st["theta"])
         F = swap_forces(st["M"], st["x"], st["theta"])
