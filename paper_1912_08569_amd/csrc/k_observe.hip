@@ -12,9 +12,9 @@
 // autocorrelation method, Sec. 2.2 after eq. p3) of a series of logged rows
 // (E, W(6), K(6)): V/kT times the average over the off-diagonal components
 // xy, xz, yz and over every time origin of sigma(t0) sigma(t0 + t), with
-// sigma_ab = -(K_ab + W_ab)/V.  One block per lag, FP64, a fixed-order tree
-// over the block's threads.
-#include "rc_internal.h"
+// sigma_ab = -(K_ab + W_ab)/V.  FP64, a lag or a tile of lags per block, a fixed order
+// of additions.
+#include "rc_gather.h"
 
 namespace rc {
 
@@ -74,8 +74,10 @@ hipError_t launch_partner_counts(const int* p0, const int* pt, const unsigned ch
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(kBlock) void k_stress_acf(const double* __restrict__ rows, int T, double inv_v,
-                                                       double v_over_kt, double* __restrict__ G) {
+// One block per lag: the better form for at most one lag per CU (100000 rows, 101 lags: 148 us against 266 us
+// with tiles of lags; equal, 8 us, at 500 to 2000 rows).
+__global__ __launch_bounds__(kBlock) void k_stress_acf_few(const double* __restrict__ rows, int T, double inv_v,
+                                                           double v_over_kt, double* __restrict__ G) {
     const int t = blockIdx.x;  // lag
     double acc = 0.0;
     for (int t0 = threadIdx.x; t0 < T - t; t0 += blockDim.x) {
@@ -97,9 +99,126 @@ __global__ __launch_bounds__(kBlock) void k_stress_acf(const double* __restrict_
     if (threadIdx.x == 0) G[t] = v_over_kt * red[0] / (3.0 * (double)(T - t));
 }
 
+// A block of 512 threads computes LG * kAcfLags consecutive lags (LG groups of
+// threads).  It walks the time origins in chunks: the stresses of the chunk's
+// origins and of the rows its lags reach are formed once in LDS, and each
+// thread multiplies OWN consecutive origins with kAcfLags lags out of a
+// register window.  Bound by reading the 104-byte rows, which each block does
+// twice (against once per lag before): an address unit takes a cycle for each
+// lane of such a stride, about 6 cycles per row and block, four times the
+// products.  The next chunk's rows are requested before this one is multiplied.
+// Whole rows read 16 bytes per lane and spread over LDS were slower (150
+// against 43 us at 20000 rows, 1001 lags).  The LDS index skips one double in
+// every OWN, so that lanes OWN apart fall on different banks.
+// us, a block per lag against this (rows, lags): (8000, 2001) 96, 21; (20000, 1001) 126, 43; (20000, 5001) 549, 55.
+constexpr int kAcfThreads = 512;
+constexpr int kAcfLags = 16;
+constexpr int kAcfRows = 2048;   // rows of each series in LDS
+
+template <int LG>
+__global__ __launch_bounds__(kAcfThreads) void k_stress_acf(const double* __restrict__ rows, int T, int max_lag,
+                                                            double inv_v, double v_over_kt, double* __restrict__ G) {
+    constexpr int kGroup = kAcfThreads / LG;           // threads per group of lags
+    constexpr int kOwn = kAcfRows / kGroup;            // origins per thread
+    constexpr int kChunk = kAcfRows - LG * kAcfLags;   // origins per chunk
+    constexpr int kFlight = kAcfRows / kAcfThreads;    // rows per thread and series
+    auto at = [](int i) { return i + i / kOwn; };
+    constexpr int kS = kAcfRows + kAcfRows / kOwn;
+    __shared__ double s_a[3][kS];
+    __shared__ double s_b[3][kS];
+    __shared__ double s_sum[kAcfThreads / kWave][kAcfLags];
+    const int l0 = blockIdx.x * (LG * kAcfLags);   // the block's first lag (<= max_lag < T)
+    const int grp = threadIdx.x / kGroup, own = (threadIdx.x % kGroup) * kOwn;
+    const int off = own + grp * kAcfLags;
+    struct Rows {
+        double v[kFlight][6];
+    };
+    // kAcfRows rows from r0 on (the last row in place of those past the end)
+    auto request = [&](int r0, Rows& x) {
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {   // xy, xz, yz: W at 4 + c, K at 10 + c
+            const double* r = rows + (size_t)min(r0 + (int)threadIdx.x + u * kAcfThreads, T - 1) * kEvWords;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x.v[u][c] = r[4 + c];
+                x.v[u][3 + c] = r[10 + c];
+            }
+        }
+    };
+    auto store = [&](const Rows& x, double(*s)[kS]) {
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                s[c][at(threadIdx.x + u * kAcfThreads)] = -(x.v[u][3 + c] + x.v[u][c]) * inv_v;
+    };
+    double acc[kAcfLags] = {};
+    Rows ra, rb;
+    request(0, ra);
+    request(l0, rb);
+    for (int t0 = 0; t0 < T - l0; t0 += kChunk) {
+        __syncthreads();
+        store(ra, s_a);
+        store(rb, s_b);
+        __syncthreads();
+        if (t0 + kChunk < T - l0) {
+            request(t0 + kChunk, ra);
+            request(t0 + kChunk + l0, rb);
+        }
+        const int i0 = t0 + own, lag = l0 + grp * kAcfLags;   // the thread's first origin and lag
+        if (own >= kChunk || i0 + lag >= T) continue;
+        if (i0 + kOwn - 1 + lag + kAcfLags - 1 < T) {   // every product of the thread exists
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                double a[kOwn], b[kOwn + kAcfLags - 1];
+#pragma unroll
+                for (int u = 0; u < kOwn; ++u) a[u] = s_a[c][at(own) + u];
+#pragma unroll
+                for (int u = 0; u < kOwn + kAcfLags - 1; ++u) b[u] = s_b[c][at(off) + at(u)];
+#pragma unroll
+                for (int u = 0; u < kOwn; ++u)
+#pragma unroll
+                    for (int l = 0; l < kAcfLags; ++l) acc[l] += a[u] * b[u + l];
+            }
+        } else {   // products past the series' end are cleared bitwise (whatever they are; no branches)
+            const int live = T - i0 - lag;   // row u + l of the thread's lags exists when below this
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int u = 0; u < kOwn; ++u) {
+                    const double a = s_a[c][at(own) + u];
+#pragma unroll
+                    for (int l = 0; l < kAcfLags; ++l) {
+                        const long long p = __double_as_longlong(a * s_b[c][at(off) + at(u + l)]);
+                        acc[l] += __longlong_as_double(p & (long long)((u + l - live) >> 31));
+                    }
+                }
+        }
+    }
+    // fixed order: the wavefront's sums, then the group's wavefronts one after the other
+    wave_sum_store<kAcfLags>(acc, s_sum[threadIdx.x / kWave]);
+    __syncthreads();
+    const int t = l0 + (int)threadIdx.x;
+    if (threadIdx.x < LG * kAcfLags && t <= max_lag) {
+        constexpr int nw = kGroup / kWave;
+        const int g = threadIdx.x / kAcfLags, l = threadIdx.x % kAcfLags;
+        double sum = 0.0;
+        for (int w = 0; w < nw; ++w) sum += s_sum[g * nw + w][l];
+        G[t] = v_over_kt * sum / (3.0 * (double)(T - t));
+    }
+}
+
 hipError_t launch_stress_acf(const double* rows, int T, double volume, double kT, int max_lag, double* G,
                              hipStream_t s) {
-    hipLaunchKernelGGL(k_stress_acf, dim3(max_lag + 1), dim3(kBlock), 0, s, rows, T, 1.0 / volume, volume / kT, G);
+    const int n = max_lag + 1;
+    const double inv_v = 1.0 / volume, v_over_kt = volume / kT;
+    if (n <= 256)
+        hipLaunchKernelGGL(k_stress_acf_few, dim3(n), dim3(kBlock), 0, s, rows, T, inv_v, v_over_kt, G);
+    else if (n <= 256 * kAcfLags)   // a block holds a CU's LDS: 16 lags each while that makes at most one per CU
+        hipLaunchKernelGGL(k_stress_acf<1>, dim3(nblk(n, kAcfLags)), dim3(kAcfThreads), 0, s, rows, T, max_lag, inv_v,
+                           v_over_kt, G);
+    else
+        hipLaunchKernelGGL(k_stress_acf<2>, dim3(nblk(n, 2 * kAcfLags)), dim3(kAcfThreads), 0, s, rows, T, max_lag,
+                           inv_v, v_over_kt, G);
     return hipGetLastError();
 }
 

@@ -1,0 +1,35 @@
+"""Kernels at the sizes where their tiling can go wrong (edges of tiles, remainders, the smallest and
+the largest of a range), against the FP64 oracle or the general path of the same quantity."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import observables_ref
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,max_lag", [(1, 0), (2, 1), (300, 255), (2047, 256), (2049, 2048), (4111, 287),
+                                       (6200, 4096), (6145, 6144)])
+def test_stress_autocorrelation_tiles(T, max_lag):
+    # tiles of 2048 origins and 16 or 32 lags; a row whose stress is not a number reaches exactly the
+    # lags that read it.  Both sides add n = 3 (T - t) products in FP64: |difference| <= 2 n u sum |products|
+    from paper_1912_08569_amd import System
+    S = System.from_workload(W.small_reactive(N=300, density=0.2, seed=1))
+    V = float(S.edges[0]) ** 3
+    rng = np.random.default_rng(T)
+    rows = rng.standard_normal((T, 13)) * 50.0
+    bad = T - 1 if T > 100 else None
+    if bad is not None:
+        rows[bad, 5] = np.nan
+    G = S.stress_autocorrelation(rows, 0.7, max_lag)
+    s = observables_ref.shear_stress(rows, V)
+    for t in sorted({0, 1, 15, 16, 31, 32, max_lag // 2, max_lag - 1, max_lag} & set(range(max_lag + 1))):
+        p = s[:T - t] * s[t:]
+        ref = V / 0.7 * p.sum() / (3 * (T - t))
+        if np.isnan(ref):
+            assert np.isnan(G[t])
+        else:
+            n = 3 * (T - t)
+            assert abs(G[t] - ref) <= 2 * (n + 8) * 2.0 ** -53 * V / 0.7 * np.abs(p).sum() / n, (t, G[t], ref)
