@@ -30,17 +30,28 @@ struct Deriv {  // value and first two r-derivatives of one term, plus geometry
     float r, rx, ry, rz;  // r and rhat
 };
 
+// The Hessian-vector kernels' term arithmetic is written with explicit fused multiply-adds and contraction
+// off, so that every number of vectors per thread gives the same bits.
+// 2n(2n+1) q^2 - n(n+1) q
+__device__ __forceinline__ float curvature(float n, float q, float q2) {
+#pragma clang fp contract(off)
+    const float a = 2.0f * n * __fmaf_rn(2.0f, n, 1.0f), b = n * (n + 1.0f);
+    return __fmaf_rn(a, q2, -(b * q));
+}
+
 // pair: phi'(r), phi''(r)
 __device__ __forceinline__ void pair_d12(const DevEntry& e, float r2, float r, float& d1, float& d2) {
+#pragma clang fp contract(off)
     const float q = qpow(e.sig2 / r2, e.n);
     const float q2 = q * q, n = (float)e.n;
     d1 = 4.0f * e.eps * n * (q - 2.0f * q2) / r;
-    d2 = 4.0f * e.eps * (2.0f * n * (2.0f * n + 1.0f) * q2 - n * (n + 1.0f) * q) / r2;
+    d2 = 4.0f * e.eps * curvature(n, q, q2) / r2;
 }
 
 // w = sqrt(Lambda) vhat and its first two r-derivatives
 __device__ __forceinline__ void w_d012(const DevEntry& e, bool inside, float r2, float r, float& w,
                                        float& w1, float& w2) {
+#pragma clang fp contract(off)
     if (inside) {
         w = e.sqrt_lam;
         w1 = 0.0f;
@@ -51,109 +62,187 @@ __device__ __forceinline__ void w_d012(const DevEntry& e, bool inside, float r2,
     const float q2 = q * q, n = (float)e.n;
     w = e.sqrt_lam * 4.0f * (q - q2);
     w1 = e.sqrt_lam * 4.0f * n * (2.0f * q2 - q) / r;
-    w2 = -e.sqrt_lam * 4.0f * (2.0f * n * (2.0f * n + 1.0f) * q2 - n * (n + 1.0f) * q) / r2;
+    w2 = -e.sqrt_lam * 4.0f * curvature(n, q, q2) / r2;
 }
 
-// S_c and dS_c = sum_b w'_cb rhat_cb . (v_b - v_c) over c's swap partners
-__device__ __forceinline__ void centre_sums(int c, const float4& pc, const float4& vc, const int* nlist,
-                                            const int* nn, int k_max, int N, const float4* pos, const float4* v,
-                                            const DevEntry* tab, int nt, const Box& box, double& S,
-                                            double& dS) {
-    const int tc = ptype(pc.w);
-    const int cnt = nn_swap(nn[c]);   // swap-kind neighbours fill the front of the column
-    S = 0.0;
-    dS = 0.0;
-    for (int t = 0; t < cnt; ++t) {
-        const int b = nlist[(size_t)t * N + c];
-        const float4 pb = pos[b];
-        const DevEntry& e = tab[tc * nt + ptype(pb.w)];
-        if (e.kind != RC_KIND_SWAP) continue;
-        double dx, dy, dz;
-        const double r2d = canon_r2(pc, pb, box, dx, dy, dz);
-        if (!(r2d < e.rcut2)) continue;
-        const float r2 = (float)r2d, r = sqrtf(r2);
-        float w, w1, w2;
-        w_d012(e, r2d <= e.rmin2, r2, r, w, w1, w2);
-        const float4 vb = v[b];
-        const float dr = ((float)dx * (vb.x - vc.x) + (float)dy * (vb.y - vc.y) + (float)dz * (vb.z - vc.z)) / r;
-        S += (double)w;
-        dS += (double)(w1 * dr);
+// a . (u - v) over the first three components
+__device__ __forceinline__ float along(float ax, float ay, float az, const float4& u, const float4& v, float& dx,
+                                       float& dy, float& dz) {
+#pragma clang fp contract(off)
+    dx = u.x - v.x;
+    dy = u.y - v.y;
+    dz = u.z - v.z;
+    return __fmaf_rn(az, dz, __fmaf_rn(ay, dy, ax * dx));
+}
+
+// Both passes: one thread per particle and group of V tangent vectors (grid
+// row y holds vectors yV .. yV + V - 1).  The list walk, the FP64 decision and
+// the derivatives of a term are the same for every vector, so a thread does
+// them once for its V vectors; a vector's own part is two loads and ~20 FP32
+// operations per term.  The next neighbour's index and position are requested
+// before the current one is used.  Bound by the latency of the gathers of v and
+// dS.  Walking marked neighbours (inside the cutoff) only, or v and dS of the
+// block's particles in LDS, gained nothing (83 and 98 us).
+// 64 vectors at 32768 particles, both passes: 160 -> 86 us.
+// Scratch (16 bytes per particle and vector hold it): S of every particle,
+// then dS of every particle per vector.
+
+// f(j, pos[j]) for the slots [0, cnt) of particle m's column, the next neighbour in flight
+template <class F>
+__device__ __forceinline__ void walk_ahead(const HvpArgs& a, int m, int ns, int cnt, const float4& pm, F&& f) {
+    auto slot = [&](int s) { return (size_t)(s < ns ? s : a.k_max - 1 - (s - ns)) * a.N + m; };
+    int j = cnt > 0 ? a.nlist[slot(0)] : m, jn = cnt > 1 ? a.nlist[slot(1)] : m;
+    float4 pj = cnt > 0 ? a.pos[j] : pm;
+    for (int s = 0; s < cnt; ++s) {
+        const int j2 = s + 2 < cnt ? a.nlist[slot(s + 2)] : m;
+        const float4 pn = a.pos[jn];
+        f(j, pj);
+        j = jn;
+        pj = pn;
+        jn = j2;
     }
 }
 
-// first pass: (S, dS) of every particle; grid row y works on vector y
+// first pass: S and dS = sum_b w'_mb rhat_mb . (v_b - v_m) over m's swap partners
+template <int V>
 __global__ __launch_bounds__(kBlock) void k_hvp_sums(HvpArgs a) {
     extern __shared__ DevEntry s_tab[];
     load_table_adj(s_tab, a.tab);
-    const int m = xcd_block(gridDim.x) * blockDim.x + threadIdx.x;
+    const int m = xcd_block(gridDim.x) * kBlock + threadIdx.x;
     if (m >= a.N) return;
-    const size_t vo = (size_t)blockIdx.y * a.N;
-    const float4* v = a.v + vo;
-    double S, dS;
-    centre_sums(m, a.pos[m], v[m], a.nlist, a.nn, a.k_max, a.N, a.pos, v, s_tab, a.tab.nt, a.box, S, dS);
-    a.sums[vo + m] = make_double2(S, dS);
+    const int y0 = blockIdx.y * V, nv = min(V, a.nvec - y0);   // vectors past the last repeat it and are not stored
+    const float4* v[V];
+    float4 vm[V];
+    double dS[V];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+        v[u] = a.v + (size_t)(y0 + min(u, nv - 1)) * a.N;
+        vm[u] = v[u][m];
+        dS[u] = 0.0;
+    }
+    const float4 pm = a.pos[m];
+    const int tm = ptype(pm.w), ns = nn_swap(a.nn[m]);   // swap-kind neighbours fill the front of the column
+    double S = 0.0;
+    walk_ahead(a, m, ns, ns, pm, [&](int b, const float4& pb) {
+#pragma clang fp contract(off)
+        const DevEntry& e = s_tab[tm * a.tab.nt + ptype(pb.w)];
+        if (e.kind != RC_KIND_SWAP) return;
+        double dx, dy, dz;
+        const double r2d = canon_r2(pm, pb, a.box, dx, dy, dz);
+        if (!(r2d < e.rcut2)) return;
+        float4 vb[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u) vb[u] = v[u][b];
+        const float r2 = (float)r2d, r = sqrtf(r2);
+        float w, w1, w2;
+        w_d012(e, r2d <= e.rmin2, r2, r, w, w1, w2);
+        S += (double)w;
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            float Dx, Dy, Dz;
+            const float dr = along((float)dx, (float)dy, (float)dz, vb[u], vm[u], Dx, Dy, Dz) / r;
+            dS[u] += (double)(w1 * dr);
+        }
+    });
+    double* sums = reinterpret_cast<double*>(a.sums);
+    if (y0 == 0) sums[m] = S;
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+        if (u < nv) sums[(size_t)(y0 + u + 1) * a.N + m] = dS[u];
 }
 
+template <int V>
 __global__ __launch_bounds__(kBlock) void k_hvp(HvpArgs a) {
     extern __shared__ DevEntry s_tab[];
     load_table_adj(s_tab, a.tab);
-    const int nt = a.tab.nt;
-    const int m = xcd_block(gridDim.x) * blockDim.x + threadIdx.x;
+    const int m = xcd_block(gridDim.x) * kBlock + threadIdx.x;
     if (m >= a.N) return;
-    const size_t vo = (size_t)blockIdx.y * a.N;
-    const float4* v = a.v + vo;
-    const double2* sums = a.sums + vo;
+    const int y0 = blockIdx.y * V, nv = min(V, a.nvec - y0);
+    const double* sums = reinterpret_cast<const double*>(a.sums);
+    const float4* v[V];
+    const double* ds[V];
+    float4 vm[V];
+    double dSm[V];
+    float hx[V], hy[V], hz[V];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+        const int y = y0 + min(u, nv - 1);
+        v[u] = a.v + (size_t)y * a.N;
+        ds[u] = sums + (size_t)(y + 1) * a.N;
+        vm[u] = v[u][m];
+        dSm[u] = ds[u][m];
+        hx[u] = hy[u] = hz[u] = 0.f;
+    }
     const float4 pm = a.pos[m];
-    const float4 vm = v[m];
     const int tm = ptype(pm.w);
     const int packed = a.nn[m];
     const int ns = nn_swap(packed), cnt = ns + nn_other(packed);
-    const double2 sm = sums[m];
-    const double Sm = sm.x, dSm = sm.y;
-    float hx = 0.f, hy = 0.f, hz = 0.f;
-    for (int s = 0; s < cnt; ++s) {
-        const int slot = s < ns ? s : a.k_max - 1 - (s - ns);
-        const int j = a.nlist[(size_t)slot * a.N + m];
-        const float4 pj = a.pos[j];
-        const DevEntry& e = s_tab[tm * nt + ptype(pj.w)];
-        if (e.kind == RC_KIND_NONE) continue;
+    const double Sm = sums[m];
+    walk_ahead(a, m, ns, cnt, pm, [&](int j, const float4& pj) {
+#pragma clang fp contract(off)
+        const DevEntry& e = s_tab[tm * a.tab.nt + ptype(pj.w)];
+        if (e.kind == RC_KIND_NONE) return;
         double dxd, dyd, dzd;
         const double r2d = canon_r2(pm, pj, a.box, dxd, dyd, dzd);
-        if (!(r2d < e.rcut2)) continue;
+        if (!(r2d < e.rcut2)) return;
+        float4 vj[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u) vj[u] = v[u][j];
         const float r2 = (float)r2d, r = sqrtf(r2), ir = 1.0f / r;
         const float rx = (float)dxd * ir, ry = (float)dyd * ir, rz = (float)dzd * ir;
-        const float4 vj = v[j];
-        const float Dx = vj.x - vm.x, Dy = vj.y - vm.y, Dz = vj.z - vm.z;
-        const float dr = rx * Dx + ry * Dy + rz * Dz;
-        float G, dG;
-        pair_d12(e, r2, r, G, dG);
-        dG *= dr;
+        float G0, dG0, w = 0.f, w1 = 0.f, w2 = 0.f, X = 0.f;
+        pair_d12(e, r2, r, G0, dG0);
+        bool three = false;
         if (e.kind == RC_KIND_SWAP) {
-            float w, w1, w2;
             w_d012(e, r2d <= e.rmin2, r2, r, w, w1, w2);
-            if (w1 != 0.0f || w2 != 0.0f) {
-                const double2 sj = sums[j];
-                const double Sj = sj.x, dSj = sj.y;
-                const float X = (float)((Sm - (double)w) + (Sj - (double)w));
-                const float dX = (float)((dSm - (double)(w1 * dr)) + (dSj - (double)(w1 * dr)));
-                G += w1 * X;
-                dG += w2 * dr * X + w1 * dX;
-            }
+            three = w1 != 0.0f || w2 != 0.0f;
         }
-        const float c = G * ir;
-        hx -= dG * rx + c * (Dx - dr * rx);
-        hy -= dG * ry + c * (Dy - dr * ry);
-        hz -= dG * rz + c * (Dz - dr * rz);
-    }
-    a.hv[vo + m] = make_float4(hx, hy, hz, 0.0f);
+        double dSj[V];
+        if (three) {
+            const double Sj = sums[j];
+#pragma unroll
+            for (int u = 0; u < V; ++u) dSj[u] = ds[u][j];
+            X = (float)((Sm - (double)w) + (Sj - (double)w));
+        }
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            float Dx, Dy, Dz;
+            const float dr = along(rx, ry, rz, vj[u], vm[u], Dx, Dy, Dz);
+            float G = G0, dG = dG0 * dr;
+            if (three) {
+                const double d = (double)(w1 * dr);
+                const float dX = (float)((dSm[u] - d) + (dSj[u] - d));
+                G = __fmaf_rn(w1, X, G);
+                dG = dG + __fmaf_rn(w1, dX, (w2 * dr) * X);
+            }
+            const float c = G * ir;
+            hx[u] = hx[u] - __fmaf_rn(c, __fmaf_rn(-dr, rx, Dx), dG * rx);
+            hy[u] = hy[u] - __fmaf_rn(c, __fmaf_rn(-dr, ry, Dy), dG * ry);
+            hz[u] = hz[u] - __fmaf_rn(c, __fmaf_rn(-dr, rz, Dz), dG * rz);
+        }
+    });
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+        if (u < nv) a.hv[(size_t)(y0 + u) * a.N + m] = make_float4(hx[u], hy[u], hz[u], 0.0f);
+}
+
+template <int V>
+static void launch_hvp_v(const HvpArgs& a, hipStream_t s) {
+    const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
+    const dim3 grid(nblk(a.N, kBlock), nblk(a.nvec, V));
+    hipLaunchKernelGGL(k_hvp_sums<V>, grid, dim3(kBlock), shm, s, a);
+    hipLaunchKernelGGL(k_hvp<V>, grid, dim3(kBlock), shm, s, a);
 }
 
 hipError_t launch_hvp(const HvpArgs& a, hipStream_t s) {
     if (a.nvec < 1 || a.nvec > 65535) return hipErrorInvalidValue;
-    const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
-    const dim3 grid(nblk(a.N, kBlock), a.nvec);
-    hipLaunchKernelGGL(k_hvp_sums, grid, dim3(kBlock), shm, s, a);
-    hipLaunchKernelGGL(k_hvp, grid, dim3(kBlock), shm, s, a);
+    // Vectors per thread, by the blocks one vector per thread would make: sharing the walk pays once they
+    // fill the chip several times (us with 1, 2, 4, 8 vectors per thread at 512 blocks: 21.9, 22.4, 25.1, 30.1;
+    // 1024: 28.9, 24.5, 25.8, 30.3; 2048: 45.5, 33.8, 30.3, 32.7; 8192: 141, 97, 86, 89)
+    const long blocks = (long)nblk(a.N, kBlock) * a.nvec;
+    if (blocks >= 2048) launch_hvp_v<4>(a, s);
+    else if (blocks >= 1024) launch_hvp_v<2>(a, s);
+    else launch_hvp_v<1>(a, s);
     return hipGetLastError();
 }
 

@@ -33,3 +33,17 @@ def test_stress_autocorrelation_tiles(T, max_lag):
         else:
             n = 3 * (T - t)
             assert abs(G[t] - ref) <= 2 * (n + 8) * 2.0 ** -53 * V / 0.7 * np.abs(p).sum() / n, (t, G[t], ref)
+
+
+@pytest.mark.parametrize("nvec", [33, 65])
+def test_hvp_vectors_per_thread(nvec):
+    # two and four vectors per thread with one vector left over, a ragged last block, several types: each
+    # product equals the single product (one vector per thread) bit for bit
+    from paper_1912_08569_amd import System
+    S = System.from_workload(W.unequal_lambda_mixture(N=8195))
+    S.build()
+    gen = torch.Generator().manual_seed(nvec)
+    V = torch.randn((nvec, S.N, 4), generator=gen).to(S.device)
+    H = S.hvp_batch(V)
+    for k in (0, 1, nvec // 2, nvec - 2, nvec - 1):
+        assert torch.equal(H[k], S.hvp(V[k])), k
