@@ -255,11 +255,11 @@ int rc_build_nlist(rc_ctx* ctx, const float* pos, float* vel /* NULL ok */, int 
  * Cut decisions use the canonical FP64 predicate (minimum image
  * d = x_j - x_i folded once by +-L, r^2 = (dx*dx + dy*dy) + dz*dz, no fused
  * multiply-add, compared with r_cut*r_cut); the terms are evaluated in FP32.
- * Default algorithm (the triplet kernel): each lane owns a centre, walks its
- * list for the pair terms, stages the active swap partners of centres with two
- * or more of them in LDS, and the wavefront enumerates all (j<k) triplets of
- * its 64 centres across its lanes; forces on j and k go out with atomics, so
- * the summation order (last bits) is not deterministic.
+ * Default algorithm (the triplet kernel): each wavefront evaluates the list
+ * entries of 64 centres, stages the active swap partners of centres with two
+ * or more of them in LDS, and enumerates all (j<k) triplets across its lanes;
+ * forces on partners go out with atomics, so the summation order (last bits)
+ * is not deterministic.
  * flags:
  *   RC_FORCE_ACCUMULATE  add into force instead of overwriting it
  *   RC_FORCE_GATHER      atomic-free gather algorithm (each particle sums

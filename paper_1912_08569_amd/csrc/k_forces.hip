@@ -20,8 +20,11 @@ static inline int nblk(long n, int b) { return (int)((n + b - 1) / b); }
 // ---------------------------------------------------------------------------
 // atomic-free gather force kernel (RC_FORCE_GATHER)
 // ---------------------------------------------------------------------------
-template <bool EV, bool BATCH, bool SF>
+// A wavefront owns OW particles: 64, or fewer where 64 would leave most of
+// the chip without a wavefront (gather_owners).
+template <bool EV, bool BATCH, bool SF, int OW>
 __global__ __launch_bounds__(kWave) void k_forces_gather(ForceArgs a) {
+    static_assert(!BATCH || OW == kWave, "a batch chunk has 64 slots");
     extern __shared__ DevEntry s_tab[];
     const int blk = xcd_block(gridDim.x);
     Box box_r;
@@ -35,14 +38,14 @@ __global__ __launch_bounds__(kWave) void k_forces_gather(ForceArgs a) {
         box_r = a.box;
         load_table(s_tab, a.tab);
     }
-    const int m = blk * kWave + threadIdx.x;
-    const bool live = m < lim;
+    const int m = blk * OW + threadIdx.x;
+    const bool live = (int)threadIdx.x < OW && m < lim;
     const float4 pm = live ? a.pos[m] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int packed = live ? a.nn[m] : 0;
     Acc acc = {};
     const OneSystem sys{s_tab, a.tab.nt, box_r};
-    wave_gather<EV, kDefaultWidth, SF>(m - (int)threadIdx.x, live, pm, packed, a.pos, a.nlist, a.nn, a.k_max, a.N,
-                                       sys, acc, a.ssum);
+    wave_gather<EV, kDefaultWidth, SF, OneSystem, false, false, 4, OW>(m - (int)threadIdx.x, live, pm, packed, a.pos,
+                                                                       a.nlist, a.nn, a.k_max, a.N, sys, acc, a.ssum);
     if (live) {
         float4 f = make_float4(acc.fx, acc.fy, acc.fz, acc.e);
         if (a.accumulate) {
@@ -64,19 +67,33 @@ __global__ __launch_bounds__(kWave) void k_forces_gather(ForceArgs a) {
 
 // ---------------------------------------------------------------------------
 // triplet kernel (default of rc_compute_forces): one wavefront per block.
-// Pair terms per lane; the active partners of centres with two or more of
-// them are staged in an LDS pool; the wave then enumerates every (j<k)
-// triplet of its 64 centres across its lanes.  Forces on partners leave with
-// global atomics, the centre's share is gathered in LDS first.
+// The list entries of its 64 centres are evaluated flat, two per lane and
+// pass as in wave_gather (a lane per centre evaluated its own list before: the
+// wavefront took its longest list's time), and every lane sums its centre's
+// terms from LDS in slot order.  The active partners of centres with two or
+// more of them are kept in an LDS pool; the wave then enumerates every (j<k)
+// triplet of its 64 centres across its lanes for the energy and the virial,
+// and adds up each partner's w of the others, which gives the force on it in
+// one product.  It leaves with global atomics, or stays in LDS for a partner
+// among the wavefront's own 64.  Those atomics bound the kernel: with the six
+// of every triplet it took 142 us at 200003 particles of three types, 90 of
+// them in the atomics; now 71 (20 without them).  The pool is filled while the
+// entries are summed when the wavefront's swap ranges fit it, else in rounds
+// by walks of the lists.
 // ---------------------------------------------------------------------------
 constexpr int kPool = 512;   // staged partners per wave and round
 
 __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_ev) {
+    constexpr int PL = 2, W = PL * kWave;   // entries per lane and pass
     extern __shared__ DevEntry s_tab[];
     __shared__ int p_j[kPool];
-    __shared__ float p_w[kPool], p_g[kPool], p_dx[kPool], p_dy[kPool], p_dz[kPool];
+    __shared__ float p_w[kPool], p_g[kPool], p_dx[kPool], p_dy[kPool], p_dz[kPool], p_s[kPool];
     __shared__ int l_pool[kWave], l_k[kWave], l_tri[kWave + 1];
     __shared__ float l_f[kWave][4];
+    __shared__ int s_off[kWave], s_ns[kWave], s_j[W];
+    __shared__ unsigned char s_own[W];
+    __shared__ float4 s_pos[kWave];
+    __shared__ float s_c[8][W];   // phi'/r, phi, d, w, w'/r, 1 for an active swap partner
     load_table(s_tab, a.tab);
     const int nt = a.tab.nt;
     const int lane = threadIdx.x;
@@ -84,62 +101,132 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     const bool live = i < a.N;
     float4 pi = live ? a.pos[i] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int ti = ptype(pi.w);
-    const int cnt = live ? a.nn[i] : 0;
+    const int packed = live ? a.nn[i] : 0;
+    const int ns = nn_swap(packed), cnt = ns + nn_other(packed);
+    const int inc = wave_inclusive_scan(cnt), my_off = inc - cnt;
+    const int T = __builtin_amdgcn_readlane(inc, kWave - 1);
+    const int pinc = wave_inclusive_scan(ns), poff = pinc - ns;
+    const bool fits = __builtin_amdgcn_readlane(pinc, kWave - 1) <= kPool;
+    s_off[lane] = my_off;
+    s_ns[lane] = ns;
+    s_pos[lane] = pi;
     float fx = 0.f, fy = 0.f, fz = 0.f, en = 0.f;
     float w6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     int nact = 0;
-    walk_list<false>(i, pi, ti, a.nlist, cnt, a.k_max, a.N, a.pos, s_tab, nt, a.box, -1,
-                         [&](int, const float4&, const DevEntry& e, const PairGeom& pg) {
-                             const float r2 = pg.r2, dx = pg.dx, dy = pg.dy, dz = pg.dz;
-                             float phi, g;
-                             pair_eval(e, r2, phi, g);
-                             fx += g * dx;
-                             fy += g * dy;
-                             fz += g * dz;
-                             en += 0.5f * phi;
-                             const float c = -0.5f * g;
-                             w6[0] += c * dx * dx; w6[1] += c * dy * dy; w6[2] += c * dz * dz;
-                             w6[3] += c * dx * dy; w6[4] += c * dx * dz; w6[5] += c * dy * dz;
-                             nact += (e.kind == RC_KIND_SWAP);
-                         });
+    __syncthreads();
+    for (int base = 0; base < T; base += W) {
+        const int lo = max(my_off, base) - base, hi = min(my_off + cnt, base + W) - base;
+        for (int q = lo; q < hi; ++q) s_own[q] = (unsigned char)lane;
+        __syncthreads();
+        int own[PL], jj[PL];
+        float4 pj[PL];
+#pragma unroll
+        for (int u = 0; u < PL; ++u) {
+            const int e = base + u * kWave + lane;
+            own[u] = -1;
+            jj[u] = 0;
+            if (e < T) {
+                own[u] = s_own[e - base];
+                const int sl = e - s_off[own[u]], nso = s_ns[own[u]];
+                const int slot = sl < nso ? sl : a.k_max - 1 - (sl - nso);
+                jj[u] = a.nlist[(size_t)slot * a.N + (i - lane) + own[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PL; ++u) {
+            pj[u] = pi;
+            if (own[u] >= 0) {
+                const unsigned lj = (unsigned)(jj[u] - (i - lane));
+                if (lj < (unsigned)kWave) pj[u] = s_pos[lj];
+                else pj[u] = a.pos[jj[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PL; ++u) {
+            float c[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (own[u] >= 0) {
+                const float4 po = s_pos[own[u]];
+                const DevEntry& e = s_tab[ptype(po.w) * nt + ptype(pj[u].w)];
+                if (e.kind != RC_KIND_NONE) {
+                    const PairGeom pg = pair_geom<true>(po, pj[u], a.box, e);
+                    if (pg.cut) {
+                        pair_eval(e, pg.r2, c[1], c[0]);
+                        c[2] = pg.dx;
+                        c[3] = pg.dy;
+                        c[4] = pg.dz;
+                        if (e.kind == RC_KIND_SWAP) {
+                            float v, v1r;
+                            vhat_eval(e, pg.inside, pg.r2, v, v1r);
+                            c[5] = e.sqrt_lam * v;
+                            c[6] = e.sqrt_lam * v1r;
+                            c[7] = 1.0f;
+                        }
+                    }
+                }
+            }
+            s_j[u * kWave + lane] = jj[u];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s_c[q][u * kWave + lane] = c[q];
+        }
+        __syncthreads();
+        for (int q = lo; q < hi; ++q) {
+            const float g = s_c[0][q], dx = s_c[2][q], dy = s_c[3][q], dz = s_c[4][q];
+            fx += g * dx;
+            fy += g * dy;
+            fz += g * dz;
+            en += 0.5f * s_c[1][q];
+            const float c = -0.5f * g;
+            w6[0] += c * dx * dx; w6[1] += c * dy * dy; w6[2] += c * dz * dz;
+            w6[3] += c * dx * dy; w6[4] += c * dx * dz; w6[5] += c * dy * dz;
+            if (s_c[7][q] != 0.0f) {
+                if (fits) {
+                    const int at = poff + nact;   // at most ns active partners
+                    p_j[at] = s_j[q];
+                    p_w[at] = s_c[5][q];
+                    p_g[at] = s_c[6][q];
+                    p_dx[at] = dx;
+                    p_dy[at] = dy;
+                    p_dz[at] = dz;
+                }
+                ++nact;
+            }
+        }
+        __syncthreads();
+    }
     // ---- wave-wide triplet stage -------------------------------------------
     const int k = (nact >= 2) ? nact : 0;
-    int incl = k;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int t = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += t;
-    }
+    const int incl = wave_inclusive_scan(k);
     const int off = incl - k;
-    const int total = __shfl(incl, kWave - 1, kWave);
+    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
     l_f[lane][0] = l_f[lane][1] = l_f[lane][2] = l_f[lane][3] = 0.f;
     int round_start = 0;
     bool done = (k == 0);
     while (round_start < total) {
-        const bool mine = !done && off >= round_start && off + k <= round_start + kPool;
-        // the admitted lanes form a run; the next round starts at the first lane left out
-        int next = total;
-        {
+        bool mine = !done;
+        int next = total, pool = poff;
+        if (!fits) {
+            // the admitted lanes form a run; the next round starts at the first lane left out
+            mine = !done && off >= round_start && off + k <= round_start + kPool;
             int cand = (!done && !mine) ? off : total;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) cand = min(cand, __shfl_xor(cand, o, kWave));
             next = cand;
-        }
-        if (mine) {
-            int q = off - round_start;
-            walk_list<true>(i, pi, ti, a.nlist, cnt, a.k_max, a.N, a.pos, s_tab, nt, a.box, -1,
-                                 [&](int j, const float4&, const DevEntry& e, const PairGeom& pg) {
-                                     const float dx = pg.dx, dy = pg.dy, dz = pg.dz;
-                                     float u, u1r;
-                                     vhat_eval(e, pg.inside, pg.r2, u, u1r);
-                                     p_j[q] = j;
-                                     p_w[q] = e.sqrt_lam * u;
-                                     p_g[q] = e.sqrt_lam * u1r;
-                                     p_dx[q] = dx;
-                                     p_dy[q] = dy;
-                                     p_dz[q] = dz;
-                                     ++q;
-                                 });
+            pool = off - round_start;
+            if (mine) {
+                int q = pool;
+                walk_list<true, 4>(i, pi, ti, a.nlist, packed, a.k_max, a.N, a.pos, s_tab, nt, a.box, -1,
+                                   [&](int j, const float4&, const DevEntry& e, const PairGeom& pg) {
+                                       float u, u1r;
+                                       vhat_eval(e, pg.inside, pg.r2, u, u1r);
+                                       p_j[q] = j;
+                                       p_w[q] = e.sqrt_lam * u;
+                                       p_g[q] = e.sqrt_lam * u1r;
+                                       p_dx[q] = pg.dx;
+                                       p_dy[q] = pg.dy;
+                                       p_dz[q] = pg.dz;
+                                       ++q;
+                                   });
+            }
         }
         const int tcount = mine ? k * (k - 1) / 2 : 0;
         int tinc = tcount;
@@ -150,7 +237,9 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
         }
         l_tri[lane] = tinc - tcount;
         if (lane == kWave - 1) l_tri[kWave] = tinc;
-        l_pool[lane] = off - round_start;
+        l_pool[lane] = pool;
+        if (mine)
+            for (int q = pool; q < pool + k; ++q) p_s[q] = 0.0f;
         l_k[lane] = mine ? k : 0;
         __syncthreads();
         const int T = l_tri[kWave];
@@ -170,15 +259,8 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
             const int qa = l_pool[c] + aa, qb = l_pool[c] + aa + 1 + loc;
             const float wa = p_w[qa], wb = p_w[qb];
             const float ca = -p_g[qa] * wb, cb = -p_g[qb] * wa;  // force on a = ca d_a
-            const float fax = ca * p_dx[qa], fay = ca * p_dy[qa], faz = ca * p_dz[qa];
-            const float fbx = cb * p_dx[qb], fby = cb * p_dy[qb], fbz = cb * p_dz[qb];
-            float* Fa = reinterpret_cast<float*>(a.force + p_j[qa]);
-            float* Fb = reinterpret_cast<float*>(a.force + p_j[qb]);
-            atomicAdd(Fa + 0, fax); atomicAdd(Fa + 1, fay); atomicAdd(Fa + 2, faz);
-            atomicAdd(Fb + 0, fbx); atomicAdd(Fb + 1, fby); atomicAdd(Fb + 2, fbz);
-            atomicAdd(&l_f[c][0], -(fax + fbx));
-            atomicAdd(&l_f[c][1], -(fay + fby));
-            atomicAdd(&l_f[c][2], -(faz + fbz));
+            atomicAdd(&p_s[qa], wb);
+            atomicAdd(&p_s[qb], wa);
             atomicAdd(&l_f[c][3], wa * wb);
             w6[0] += ca * p_dx[qa] * p_dx[qa] + cb * p_dx[qb] * p_dx[qb];
             w6[1] += ca * p_dy[qa] * p_dy[qa] + cb * p_dy[qb] * p_dy[qb];
@@ -188,7 +270,23 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
             w6[5] += ca * p_dy[qa] * p_dz[qa] + cb * p_dy[qb] * p_dz[qb];
         }
         __syncthreads();
-        if (mine) done = true;
+        if (mine) {   // the forces on the centre's partners, and minus their sum on the centre
+            for (int q = pool; q < pool + k; ++q) {
+                const float c = -p_g[q] * p_s[q];
+                if (c == 0.0f) continue;   // a bonded partner (w' = 0): most of them
+                const float gx = c * p_dx[q], gy = c * p_dy[q], gz = c * p_dz[q];
+                const unsigned lj = (unsigned)(p_j[q] - (i - lane));
+                float* F = lj < (unsigned)kWave ? l_f[lj] : reinterpret_cast<float*>(a.force + p_j[q]);
+                atomicAdd(F + 0, gx);
+                atomicAdd(F + 1, gy);
+                atomicAdd(F + 2, gz);
+                fx -= gx;
+                fy -= gy;
+                fz -= gz;
+            }
+            done = true;
+        }
+        __syncthreads();
         round_start = next;
     }
     __syncthreads();
@@ -274,28 +372,56 @@ static hipError_t launch_sums(const ForceArgs& a, bool batch, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <bool BATCH>
-static hipError_t launch_gather_any(const ForceArgs& a, hipStream_t s) {
+template <bool BATCH, int OW>
+static void launch_gather_ow(const ForceArgs& a, hipStream_t s) {
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
-    const dim3 g(nblk(a.N, kWave)), b(kWave);
+    const dim3 g(nblk(a.N, OW)), b(kWave);
     if (a.ssum) {
-        hipError_t e = launch_sums(a, BATCH, s);
-        if (e != hipSuccess) return e;
         if (a.ev_part)
-            hipLaunchKernelGGL((k_forces_gather<true, BATCH, true>), g, b, shm, s, a);
+            hipLaunchKernelGGL((k_forces_gather<true, BATCH, true, OW>), g, b, shm, s, a);
         else
-            hipLaunchKernelGGL((k_forces_gather<false, BATCH, true>), g, b, shm, s, a);
+            hipLaunchKernelGGL((k_forces_gather<false, BATCH, true, OW>), g, b, shm, s, a);
     } else {
         if (a.ev_part)
-            hipLaunchKernelGGL((k_forces_gather<true, BATCH, false>), g, b, shm, s, a);
+            hipLaunchKernelGGL((k_forces_gather<true, BATCH, false, OW>), g, b, shm, s, a);
         else
-            hipLaunchKernelGGL((k_forces_gather<false, BATCH, false>), g, b, shm, s, a);
+            hipLaunchKernelGGL((k_forces_gather<false, BATCH, false, OW>), g, b, shm, s, a);
+    }
+}
+
+// The fewest particles per wavefront, 8 to 64, that make at most 4096 wavefronts (four per SIMD).  A
+// wavefront's time is its rows of 64 entries one after the other, each as long as its longest partner walk, so
+// a chip with idle SIMDs wants more wavefronts with fewer rows; past four per SIMD the energy/virial rows and
+// the partly filled rows of entries cost more (us without ev at 8, 16, 32, 64 particles per wavefront, density
+// 0.25: 16000 particles 15.6, 20.9, 25.8, 39.1; 65536: 28.5, 24.1, 27.5, 41.9; 131072: 47.8, 40.1, 32.1, 43.8).
+int gather_owners(int N) {
+    int ow = 8;
+    while (ow < kWave && (long)N > 4096L * ow) ow *= 2;
+    return ow;
+}
+
+hipError_t launch_forces_gather(const ForceArgs& a, hipStream_t s) {
+    if (a.ssum) {
+        hipError_t e = launch_sums(a, false, s);
+        if (e != hipSuccess) return e;
+    }
+    switch (gather_owners(a.N)) {
+        case 8: launch_gather_ow<false, 8>(a, s); break;
+        case 16: launch_gather_ow<false, 16>(a, s); break;
+        case 32: launch_gather_ow<false, 32>(a, s); break;
+        default: launch_gather_ow<false, kWave>(a, s);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_forces_gather(const ForceArgs& a, hipStream_t s) { return launch_gather_any<false>(a, s); }
-hipError_t launch_forces_gather_batch(const ForceArgs& a, hipStream_t s) { return launch_gather_any<true>(a, s); }
+hipError_t launch_forces_gather_batch(const ForceArgs& a, hipStream_t s) {
+    if (a.ssum) {
+        hipError_t e = launch_sums(a, true, s);
+        if (e != hipSuccess) return e;
+    }
+    launch_gather_ow<true, kWave>(a, s);
+    return hipGetLastError();
+}
 
 // ---------------------------------------------------------------------------
 // fused MD step: gather forces at x_in, finish the previous step's final half
@@ -459,7 +585,7 @@ __global__ __launch_bounds__(kBlock) void k_bonds(const float4* __restrict__ pos
     unsigned c = 0;
     if (i < N) {
         const float4 pi = pos[i];
-        walk_list<true>(i, pi, ptype(pi.w), nlist, nn[i], k_max, N, pos, s_tab, tab.nt, box, -1,
+        walk_list<true, 4>(i, pi, ptype(pi.w), nlist, nn[i], k_max, N, pos, s_tab, tab.nt, box, -1,
                         [&](int j, const float4&, const DevEntry&, const PairGeom& pg) {
                             if (j > i && pg.bond) ++c;
                         });
@@ -487,7 +613,7 @@ __global__ __launch_bounds__(kBlock) void k_bond_partners(const float4* __restri
     if (i >= N) return;
     const float4 pi = pos[i];
     int p = -1;
-    walk_list<true>(i, pi, ptype(pi.w), nlist, nn[i], k_max, N, pos, s_tab, tab.nt, box, -1,
+    walk_list<true, 4>(i, pi, ptype(pi.w), nlist, nn[i], k_max, N, pos, s_tab, tab.nt, box, -1,
                     [&](int, const float4& pj, const DevEntry&, const PairGeom& pg) {
                         if (pg.bond) p = (p == -1) ? ptag(pj.w) : -2;
                     });
@@ -575,7 +701,7 @@ __global__ __launch_bounds__(kWave) void k_bonds_batch(const float4* __restrict_
     unsigned c = 0;
     if (i < d.off + d.n) {
         const float4 pi = pos[i];
-        walk_list<true>(i, pi, ptype(pi.w), nlist, nn[i], k_max, N, pos, s_tab, tab.nt, d.box, -1,
+        walk_list<true, 4>(i, pi, ptype(pi.w), nlist, nn[i], k_max, N, pos, s_tab, tab.nt, d.box, -1,
                         [&](int j, const float4&, const DevEntry&, const PairGeom& pg) {
                             if (j > i && pg.bond) ++c;
                         });

@@ -68,6 +68,11 @@ int reduce_rows(rc_ctx* c, int nb, int first, int count, double* out, hipStream_
 
 Table dev_table(const rc_ctx* c) { return Table{c->d_tab, c->nt}; }
 
+// energy/virial rows of the force kernels: one per block, which is one wavefront
+int force_rows(int N, unsigned flags) {
+    return nblocks(N, (flags & (RC_FORCE_GATHER | RC_FORCE_SUMS)) ? gather_owners(N) : kWave);
+}
+
 // rc_compute_forces on given scratch: part (per-block FP64 rows, kEvWords
 // doubles per wavefront block) when ev is wanted, ssum (N floats) for the
 // two-pass form.  Launches only; allocates nothing.
@@ -82,7 +87,7 @@ int forces_into(rc_ctx* c, const float* pos, const int* nlist, const int* nn, in
     if ((r = check_list(c, nlist, nn, k_max))) return r;
     const bool sums = flags & RC_FORCE_SUMS;
     const bool gather = (flags & RC_FORCE_GATHER) || sums;
-    const int nb = nblocks(N, kWave);
+    const int nb = force_rows(N, flags);
     ForceArgs a{};
     a.pos = reinterpret_cast<const float4*>(pos);
     a.nlist = nlist;
@@ -397,7 +402,7 @@ int rc_compute_forces(rc_ctx* c, const float* pos, const int* nlist, const int* 
                       float* force, double* ev, unsigned flags, int* status, void* stream) {
     int r = check_common(c, N, pos);
     if (r) return r;
-    const int nb = nblocks(N, kWave);   // both force kernels run one wavefront per block
+    const int nb = force_rows(N, flags);
     if ((flags & RC_FORCE_SUMS) && (r = ensure_ssum(c, (size_t)N))) return r;
     if (ev && (r = ensure_part(c, sizeof(double) * kEvWords * (size_t)nb))) return r;
     return forces_into(c, pos, nlist, nn, k_max, N, box, force, ev, flags, status, c->d_part, c->d_ssum,

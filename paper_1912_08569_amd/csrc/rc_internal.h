@@ -98,13 +98,19 @@ struct PairGeom {
     bool bond;         // r^2 <  r_min^2
 };
 
+// The term arithmetic below is written with explicit fused multiply-adds and
+// contraction off, so that a kernel's bits do not depend on how its code is
+// arranged.  XFIRST: the order of the square's sum, dx^2 first (the walks of a
+// list) or dy^2 first (the flat list entries and the switching sums).
+template <bool XFIRST>
 __device__ __forceinline__ PairGeom pair_geom(const float4& pi, const float4& pj, const Box& b, const DevEntry& e) {
+#pragma clang fp contract(off)
     PairGeom g;
     g.dx = pj.x - pi.x;
     g.dy = pj.y - pi.y;
     g.dz = pj.z - pi.z;
     const bool wrap = fabsf(g.dx) > b.hf[0] || fabsf(g.dy) > b.hf[1] || fabsf(g.dz) > b.hf[2];
-    g.r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
+    g.r2 = __fmaf_rn(g.dz, g.dz, XFIRST ? __fmaf_rn(g.dy, g.dy, g.dx * g.dx) : __fmaf_rn(g.dx, g.dx, g.dy * g.dy));
     g.cut = g.r2 < e.rcut2_lo;
     g.inside = g.r2 < e.rmin2_lo;
     g.bond = g.inside;
@@ -157,10 +163,11 @@ __device__ __forceinline__ float qpow(float s2, int n) {
 // Pair term (eq. 2b for SWAP; WCA = n 6 plus the +eps shift): energy phi and
 // g = phi'(r)/r, so that the force on i from the pair is g * (x_j - x_i).
 __device__ __forceinline__ void pair_eval(const DevEntry& e, float r2, float& phi, float& g) {
+#pragma clang fp contract(off)
     const float ir2 = inv_r2(r2);
     float q = qpow(e.sig2 * ir2, e.n);
     float q2 = q * q;
-    phi = 4.0f * e.eps * (q2 - q) + (e.kind == RC_KIND_WCA ? e.eps : 0.0f);
+    phi = __fmaf_rn(4.0f * e.eps, __fmaf_rn(q, q, -q), e.kind == RC_KIND_WCA ? e.eps : 0.0f);
     g = 4.0f * e.eps * (float)e.n * (q - 2.0f * q2) * ir2;
 }
 
@@ -168,6 +175,7 @@ __device__ __forceinline__ void pair_eval(const DevEntry& e, float r2, float& ph
 // 'inside' is the canonical decision r^2 <= r_min^2.
 __device__ __forceinline__ void vhat_eval(const DevEntry& e, bool inside, float r2, float& u,
                                           float& u1r) {
+#pragma clang fp contract(off)
     if (inside) {
         u = 1.0f;
         u1r = 0.0f;
@@ -181,13 +189,14 @@ __device__ __forceinline__ void vhat_eval(const DevEntry& e, bool inside, float 
 }
 
 // pair_eval and vhat_eval of one entry sharing 1/r^2 and (sigma/r)^n (the
-// same values as the two calls)
+// same values as the two calls, phi's last bit apart: it squares q once more)
 __device__ __forceinline__ void pair_vhat_eval(const DevEntry& e, bool swap, bool inside, float r2, float& phi,
                                                float& g, float& u, float& u1r) {
+#pragma clang fp contract(off)
     const float ir2 = inv_r2(r2);
     const float q = qpow(e.sig2 * ir2, e.n);
     const float q2 = q * q;
-    phi = 4.0f * e.eps * (q2 - q) + (e.kind == RC_KIND_WCA ? e.eps : 0.0f);
+    phi = __fmaf_rn(4.0f * e.eps, q2 - q, e.kind == RC_KIND_WCA ? e.eps : 0.0f);
     g = 4.0f * e.eps * (float)e.n * (q - 2.0f * q2) * ir2;
     u = 0.0f;
     u1r = 0.0f;
@@ -483,6 +492,8 @@ struct ForceArgs {
     float* ssum;           // [N] switching sums: non-NULL selects the two-pass form
 };
 hipError_t launch_forces_triplet(const ForceArgs& a, hipStream_t s);
+// particles per wavefront (and per row of ev_part) of the gather kernel for N particles
+int gather_owners(int N);
 hipError_t launch_forces_gather(const ForceArgs& a, hipStream_t s);
 hipError_t launch_forces_gather_batch(const ForceArgs& a, hipStream_t s);
 // first pass of the two-pass form: the kernel that fills ssum (for graphs)

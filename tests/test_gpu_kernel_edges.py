@@ -47,3 +47,24 @@ def test_hvp_vectors_per_thread(nvec):
     H = S.hvp_batch(V)
     for k in (0, 1, nvec // 2, nvec - 2, nvec - 1):
         assert torch.equal(H[k], S.hvp(V[k])), k
+
+
+@pytest.mark.parametrize("N,density,gather", [
+    (90, 0.05, False), (90, 0.05, True), (90, 0.05, "sums"), (2003, 0.6, False), (4097, 0.25, False),
+    (32768, 0.25, True), (32769, 0.25, True), (65537, 0.25, True), (65537, 0.25, "sums")])
+def test_forces_per_wavefront(N, density, gather):
+    # gather: 8, 16 and 32 particles per wavefront and their limits; triplet kernel: partner pools that
+    # hold the wavefront's swap ranges and (density 0.6) that do not; ragged last wavefronts
+    from oracle import swap_ref
+    from paper_1912_08569_amd import System
+    from parity_util import assert_energy, assert_forces, assert_pe, assert_virial
+    s = W.small_reactive(N=N, density=density, seed=N, min_dist=0.85)
+    S = System.from_workload(s)
+    F, ev = S.compute_forces(gather=gather)
+    x, _, _, ty = S.state_by_tag()
+    ref = swap_ref.evaluate(x, ty, s.L, s.table)
+    F = S.by_tag(F)
+    assert_forces(F, ref)
+    assert_pe(F[:, 3], ref)
+    assert_energy(float(ev[0]), ref)
+    assert_virial(ev[1:7].cpu().numpy(), ref)
