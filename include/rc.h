@@ -160,7 +160,8 @@ int rc_get_rlist(const rc_ctx* ctx, int a, int b, double* r_list);
 /* Gather width of the fused step kernel: the flattened (particle, list slot)
  * entries each lane of a wavefront evaluates per pass (1, 2 or 4; default 2).
  * A tuning knob only: every width sums each particle's terms in the same
- * order, so results are bit-identical.  RC_ERR_ARG for other values.        */
+ * order, so results are bit-identical.  (Systems too small to fill the GPU
+ * take one entry per lane whatever the width.)  RC_ERR_ARG for other values.        */
 int rc_set_gather_width(rc_ctx* ctx, int width);
 /* How the fused step (and rc_compute_forces with RC_FORCE_SUMS) evaluates
  * the three-body forces of eq. (3bp):
@@ -485,9 +486,10 @@ typedef struct rc_md_options {
                            lengths so that rollbacks stay rare; 0: always
                            max_chunk steps (rollbacks repair stale chunks)    */
     int one_block;      /* 1: with use_graph, a system of at most 1024 particles
-                           (walk or sums form) runs each graph_steps-step replay
-                           as one launch of one workgroup that keeps the
-                           positions in LDS (same results, bit for bit); 0:
+                           (walk or sums form) with lists short enough for that
+                           to be faster runs each graph_steps-step replay as one
+                           launch of one workgroup that keeps the positions in
+                           LDS (same results, bit for bit); 0:
                            hipGraphs only.  Ignored by rc_batch_run.          */
     int resume;         /* 1: the state owes its last step's final half kick
                            (it is what an earlier call left when it returned an

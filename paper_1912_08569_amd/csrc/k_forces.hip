@@ -359,8 +359,52 @@ __global__ __launch_bounds__(kWave) void k_swap_sums(ForceArgs a) {
     a.ssum[m] = swap_sum(m, pm, packed, a.pos, a.nlist, a.N, s_tab, a.tab.nt, box_r);
 }
 
-void sums_kernel_info(bool batch, const void** fn) {
-    *fn = batch ? reinterpret_cast<const void*>(&k_swap_sums<true>) : reinterpret_cast<const void*>(&k_swap_sums<false>);
+// The same sums from the packed list (the steps' first pass), OW particles per
+// wavefront as in k_step_few.  A lane per particle took the wavefront's longest
+// swap range in fours (8.6 us per launch at 5000 particles of density 0.25; now
+// 4.8, about a launch's own time).
+template <bool BATCH, int OW>
+__global__ __launch_bounds__(kWave) void k_swap_sums_packed(ForceArgs a) {
+    static_assert(!BATCH || OW == kWave, "a batch chunk has 64 slots");
+    constexpr int PL = 2, G = kWave / OW;
+    extern __shared__ DevEntry s_tab[];
+    __shared__ float4 s_pos[OW];
+    __shared__ float s_w[2][PL * kWave];
+    const int lane = threadIdx.x, nt = a.tab.nt;
+    const int ngr = (a.N + OW - 1) / OW;   // the grid
+    const int per = ngr / 8, bx = blockIdx.x;
+    const int gr = bx < per * 8 ? (bx & 7) * per + (bx >> 3) : bx;
+    const int blk = gr / G, h = gr % G, base_m = gr * OW;
+    const int m = base_m + lane;
+    const int mc = min(base_m + min(lane, OW - 1), a.N - 1), m64 = blk * kWave + lane;
+    const float4 pm0 = a.pos[mc];
+    const int nn64 = a.nn[min(m64, a.N - 1)];
+    Box box_r;
+    int lim = a.N;
+    if constexpr (BATCH) {
+        const RepDesc& d = a.rep[a.chunk_rep[blk]];
+        box_r = d.box;
+        lim = d.off + d.n;
+        load_table(s_tab, Table{a.tab.e + d.tab, nt});
+    } else {
+        box_r = a.box;
+        load_table(s_tab, a.tab);
+    }
+    const int cnt64 = m64 < lim ? nn_swap(nn64) + nn_other(nn64) : 0;
+    const int inc64 = wave_inclusive_scan(cnt64);
+    const int before = h > 0 ? __builtin_amdgcn_readlane(inc64, h * OW - 1) : 0;
+    const int T = __builtin_amdgcn_readlane(inc64, h * OW + OW - 1) - before;
+    const int from = h * OW + min(lane, OW - 1);
+    const bool live = lane < OW && m < lim;
+    const int my_off = __shfl(inc64 - cnt64, from, kWave) - before;
+    const int ns_any = nn_swap(__shfl(nn64, from, kWave));
+    const int ns = live ? ns_any : 0;
+    if (lane < OW) s_pos[lane] = pm0;
+    __syncthreads();
+    const float S = packed_sums<PL, OW, false>(base_m, s_pos, my_off, ns, T, h * OW,
+                                               (size_t)blk * kWave * a.k_max + before, a.pos, a.pl_j, a.pl_o, s_tab, nt,
+                                               box_r, s_w);
+    if (live) a.ssum[m] = S;
 }
 
 static hipError_t launch_sums(const ForceArgs& a, bool batch, hipStream_t s) {
@@ -491,6 +535,70 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(7))) void
     if (a.reset_status && blockIdx.x == 0 && threadIdx.x == 0) chunk_reset(a.reset_status, a.reset_base, a.reset_to);
 }
 
+// The plain step with few particles per wavefront, for systems whose 64-particle
+// wavefronts would hold many entries and not fill the chip: a wavefront's time
+// is its rows of 64 entries one after the other.  Same arithmetic and order as
+// k_step (bit for bit); the thermostat normals are drawn and the spring
+// partners read while the list reads are under way.
+// us per step as a run sees it (one launch for every 64 particles -> this):
+// network of 67200 beads 33.7 -> 24.2, of 5000 beads 27.9 -> 15.4; 30000
+// reactive particles (density 0.25) 21.4 -> 17.2; 20011 dumbbells 11.0 -> 10.6.
+template <bool SF, int OW>
+__global__ __launch_bounds__(kWave) void k_step_few(StepArgs a) {
+    extern __shared__ DevEntry s_tab[];
+    const int nt = a.tab.nt, lane = threadIdx.x;
+    const int ngr = (a.N + OW - 1) / OW;   // the grid
+    const int per = ngr / 8, bx = blockIdx.x;
+    const int gr = bx < per * 8 ? (bx & 7) * per + (bx >> 3) : bx;
+    constexpr int G = kWave / OW;
+    const int blk = gr / G, h = gr % G;    // the 64-particle block of the packed list and the group in it
+    const int m = gr * OW + lane;
+    const bool live = lane < OW && m < a.N;
+    const int mc = min(gr * OW + min(lane, OW - 1), a.N - 1);
+    const int m64 = blk * kWave + lane;
+    const float4 pm0 = a.pos_in[mc];
+    const float4 vm0 = a.vel[mc];
+    const int nn64 = a.nn[min(m64, a.N - 1)];
+    const uint64_t step = a.step + (a.step_base ? *a.step_base : 0ull);
+    load_table(s_tab, a.tab);
+    const float4 pm = live ? pm0 : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 vm = live ? vm0 : make_float4(0.f, 0.f, 0.f, 0.f);
+    // this group's entries within the block's
+    const int cnt64 = m64 < a.N ? nn_swap(nn64) + nn_other(nn64) : 0;
+    const int inc64 = wave_inclusive_scan(cnt64);
+    const int before = h > 0 ? __builtin_amdgcn_readlane(inc64, h * OW - 1) : 0;
+    const int packed_any = __shfl(nn64, h * OW + min(lane, OW - 1), kWave);
+    const int packed = live ? packed_any : 0;
+    Acc acc = {};
+    const OneSystem sys{s_tab, nt, a.box};
+    int2 bond = make_int2(-1, -1);
+    if (a.bonds && live) bond = a.bonds[ptag(pm.w)];
+    float nz[3] = {0.f, 0.f, 0.f};
+    int bi[2] = {-1, -1};
+    float4 bp[2] = {pm, pm};
+    wave_gather<false, 1, SF, OneSystem, false, true, 4, OW>(
+        m - lane, live, pm, packed, a.pos_in, a.nlist, a.nn, a.k_max, a.N, sys, acc, a.ssum, a.pl_j, a.pl_o,
+        (size_t)blk * kWave * a.k_max + before, h * OW, [&](int at) {
+            if (at == 0) {
+                if (a.bonds) {
+                    if (bond.x >= 0) bi[0] = a.rtag[bond.x];
+                    if (bond.y >= 0) bi[1] = a.rtag[bond.y];
+                }
+                if (a.langevin) {
+                    thermostat_normals(a.seed, (uint32_t)ptag(pm.w), step, nz[0], nz[1], nz[2]);
+                    asm volatile("" : "+v"(nz[0]), "+v"(nz[1]), "+v"(nz[2]));   // drawn here, not where they are used
+                }
+            } else if (a.bonds) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    if (bi[q] >= 0) bp[q] = a.pos_in[bi[q]];
+            }
+        });
+    if (a.bonds && live) fene_pair(bi, bp, pm, a.box, a.fene_k, a.fene_r02, acc);
+    step_finish<false, true, true>(a, a.pos_out, m, blk, live, pm, vm, acc, a.box, 0, a.seed, step, nz);
+    if (a.reset_status && blockIdx.x == 0 && threadIdx.x == 0) chunk_reset(a.reset_status, a.reset_base, a.reset_to);
+}
+
 // Step kernels by (ev, batch, width, form); log steps use the default width.
 template <bool BATCH, bool SF>
 static const void* step_fn_form(bool ev, int width) {
@@ -520,54 +628,95 @@ static ForceArgs sums_args(const StepArgs& a) {
     f.rep = a.rep;
     f.chunk_rep = a.chunk_rep;
     f.ssum = a.ssum;
+    f.pl_j = a.pl_j;
+    f.pl_o = a.pl_o;
     return f;
 }
 
-template <bool BATCH>
-static hipError_t launch_step_any(const StepArgs& a, bool ev, hipStream_t s) {
-    if (a.form == RC_FORM_SUMS) {
-        hipError_t e = launch_sums(sums_args(a), BATCH, s);
-        if (e != hipSuccess) return e;
+template <bool SF>
+static const void* few_fn(int ow) {
+    switch (ow) {
+        case 8: return reinterpret_cast<const void*>(&k_step_few<SF, 8>);
+        case 16: return reinterpret_cast<const void*>(&k_step_few<SF, 16>);
+        default: return reinterpret_cast<const void*>(&k_step_few<SF, 32>);
     }
-    const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
-    StepArgs arg = a;
-    void* args[] = {&arg};
-    return hipLaunchKernel(step_fn<BATCH>(ev, a.width, a.form), dim3(nblk(a.N, kStepBlock)), dim3(kStepBlock), args,
-                           shm, s);
 }
 
-hipError_t launch_step(const StepArgs& a, bool ev, hipStream_t s) { return launch_step_any<false>(a, ev, s); }
+// Particles per wavefront of a plain step.  list_est is the number of list
+// entries a particle would have at the largest list radius.  k_step_few at the
+// most particles that hold about one row of 64 entries (8 to 32), while that
+// makes few wavefronts: past 2560 (2.5 per SIMD) the partly filled rows and
+// integrator lanes cost sparse lists more than they save (131072 dumbbells: 13.2
+// us per step with 32 particles per wavefront, 12.7 with 64; 65536: 11.6, 12.0),
+// lists of six passes or more per 64 particles gain up to twice as many
+// (67200 beads of a network, 4200 wavefronts: 24.2, 33.7).
+static int step_particles(int N, float list_est) {
+    const long most = 64.0f * list_est >= 384.0f ? 5120 : 2560;
+    int ow = 32;
+    while (ow > 8 && (float)ow * list_est > 72.0f) ow /= 2;
+    while (ow < kStepBlock && (long)N > most * ow) ow *= 2;
+    return ow;
+}
+
+static const void* sums_fn(bool batch, int ow) {
+    if (batch) return reinterpret_cast<const void*>(&k_swap_sums_packed<true, kWave>);
+    switch (ow) {
+        case 8: return reinterpret_cast<const void*>(&k_swap_sums_packed<false, 8>);
+        case 16: return reinterpret_cast<const void*>(&k_swap_sums_packed<false, 16>);
+        case 32: return reinterpret_cast<const void*>(&k_swap_sums_packed<false, 32>);
+        default: return reinterpret_cast<const void*>(&k_swap_sums_packed<false, kWave>);
+    }
+}
+
+StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_est) {
+    StepKernel k;
+    const int few = batch ? kStepBlock : step_particles(N, list_est);
+    if (!ev) k.particles = few;
+    if (k.particles < kStepBlock)
+        k.fn = form == RC_FORM_SUMS ? few_fn<true>(few) : few_fn<false>(few);
+    else
+        k.fn = batch ? step_fn<true>(ev, width, form) : step_fn<false>(ev, width, form);
+    if (form == RC_FORM_SUMS) {
+        k.sums_fn = sums_fn(batch, few);
+        k.sums_particles = few;
+    }
+    return k;
+}
+
+static hipError_t launch_step_any(const StepArgs& a, bool batch, bool ev, hipStream_t s) {
+    const StepKernel k = step_kernel(batch, ev, a.width, a.form, a.N, a.list_est);
+    const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
+    if (k.sums_fn) {
+        ForceArgs f = sums_args(a);
+        void* fargs[] = {&f};
+        hipError_t e = hipLaunchKernel(k.sums_fn, dim3(nblk(a.N, k.sums_particles)), dim3(kWave), fargs, shm, s);
+        if (e != hipSuccess) return e;
+    }
+    StepArgs arg = a;
+    void* args[] = {&arg};
+    return hipLaunchKernel(k.fn, dim3(nblk(a.N, k.particles)), dim3(kStepBlock), args, shm, s);
+}
+
+hipError_t launch_step(const StepArgs& a, bool ev, hipStream_t s) { return launch_step_any(a, false, ev, s); }
+hipError_t launch_step_batch(const StepArgs& a, bool ev, hipStream_t s) { return launch_step_any(a, true, ev, s); }
 
 // A plain (no ev) step launch whose kernels each run between an event pair
 // (hipExtLaunchKernel records them around the kernel alone).
-template <bool BATCH>
-static hipError_t launch_step_timed_any(const StepArgs& a, hipStream_t s, hipEvent_t* sums, hipEvent_t* step) {
+hipError_t launch_step_timed(const StepArgs& a, bool batch, hipStream_t s, hipEvent_t* sums, hipEvent_t* step) {
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
-    if (a.form == RC_FORM_SUMS) {
+    const StepKernel k = step_kernel(batch, false, a.width, a.form, a.N, a.list_est);
+    if (k.sums_fn) {
         ForceArgs f = sums_args(a);
         void* fargs[] = {&f};
-        const void* fn = BATCH ? reinterpret_cast<const void*>(&k_swap_sums<true>)
-                               : reinterpret_cast<const void*>(&k_swap_sums<false>);
-        hipError_t e = sums ? hipExtLaunchKernel(fn, dim3(nblk(a.N, kWave)), dim3(kWave), fargs, shm, s, sums[0],
-                                                 sums[1], 0)
-                            : hipLaunchKernel(fn, dim3(nblk(a.N, kWave)), dim3(kWave), fargs, shm, s);
+        hipError_t e = sums ? hipExtLaunchKernel(k.sums_fn, dim3(nblk(a.N, k.sums_particles)), dim3(kWave), fargs, shm,
+                                                 s, sums[0], sums[1], 0)
+                            : hipLaunchKernel(k.sums_fn, dim3(nblk(a.N, k.sums_particles)), dim3(kWave), fargs, shm, s);
         if (e != hipSuccess) return e;
     }
     StepArgs arg = a;
     void* args[] = {&arg};
-    return hipExtLaunchKernel(step_fn<BATCH>(false, a.width, a.form), dim3(nblk(a.N, kStepBlock)), dim3(kStepBlock),
-                              args, shm, s, step[0], step[1], 0);
+    return hipExtLaunchKernel(k.fn, dim3(nblk(a.N, k.particles)), dim3(kStepBlock), args, shm, s, step[0], step[1], 0);
 }
-
-hipError_t launch_step_timed(const StepArgs& a, bool batch, hipStream_t s, hipEvent_t* sums, hipEvent_t* step) {
-    return batch ? launch_step_timed_any<true>(a, s, sums, step) : launch_step_timed_any<false>(a, s, sums, step);
-}
-
-void step_kernel_info(bool ev, int width, int form, const void** fn) { *fn = step_fn<false>(ev, width, form); }
-
-hipError_t launch_step_batch(const StepArgs& a, bool ev, hipStream_t s) { return launch_step_any<true>(a, ev, s); }
-
-void step_batch_kernel_info(int width, int form, const void** fn) { *fn = step_fn<true>(false, width, form); }
 
 ForceArgs step_sums_args(const StepArgs& a) { return sums_args(a); }
 

@@ -68,6 +68,12 @@ int reduce_rows(rc_ctx* c, int nb, int first, int count, double* out, hipStream_
 
 Table dev_table(const rc_ctx* c) { return Table{c->d_tab, c->nt}; }
 
+// list entries per particle of a uniform system at the largest list radius
+float list_est(const rc_ctx* c, int N, const Box& b) {
+    const double r = c->rlist_max;
+    return (float)((double)N / (b.L[0] * b.L[1] * b.L[2]) * 4.18879 * r * r * r);
+}
+
 // energy/virial rows of the force kernels: one per block, which is one wavefront
 int force_rows(int N, unsigned flags) {
     return nblocks(N, (flags & (RC_FORCE_GATHER | RC_FORCE_SUMS)) ? gather_owners(N) : kWave);
@@ -496,6 +502,7 @@ static int fill_step_args(rc_ctx* c, StepArgs& a, const float* pos_in, float* po
     a.soft = (float)(0.5 * c->r_buff * soft_frac);
     a.seed = cfg->seed;
     a.status = status;
+    a.list_est = list_est(c, N, b);
     a.width = c->gather_width;
     a.form = c->step_form;
     a.ssum = nullptr;
@@ -568,11 +575,8 @@ int rc_time_fused_steps(rc_ctx* c, float* pos_a, float* pos_b, float* vel, const
     hipStream_t s = S(stream);
     // every kernel launch carries its own start/stop events, which time its
     // execution alone (not the dispatch gaps between launches)
-    const void* fn;
-    step_kernel_info(false, a.width, a.form, &fn);
-    const void* sums_fn = nullptr;
-    if (a.form == RC_FORM_SUMS) sums_kernel_info(false, &sums_fn);
-    const int nk = sums_fn ? 2 : 1;
+    const StepKernel kn = step_kernel(false, false, a.width, a.form, N, a.list_est);
+    const int nk = kn.sums_fn ? 2 : 1;
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
     std::vector<hipEvent_t> ev((size_t)2 * nk * reps, nullptr);
     hipError_t err = hipSuccess;
@@ -583,15 +587,15 @@ int rc_time_fused_steps(rc_ctx* c, float* pos_a, float* pos_b, float* vel, const
         a.pos_out = P[(k + 1) & 1];
         a.step = step0 + (uint64_t)k;
         hipEvent_t* e = &ev[(size_t)2 * nk * k];
-        if (sums_fn) {
+        if (kn.sums_fn) {
             ForceArgs f = step_sums_args(a);
             void* args[] = {&f};
-            err = hipExtLaunchKernel(sums_fn, dim3(nblocks(N, kWave)), dim3(kWave), args, shm, s, e[0], e[1], 0);
+            err = hipExtLaunchKernel(kn.sums_fn, dim3(nblocks(N, kn.sums_particles)), dim3(kWave), args, shm, s, e[0], e[1], 0);
             e += 2;
         }
         if (err == hipSuccess) {
             void* args[] = {&a};
-            err = hipExtLaunchKernel(fn, dim3(nblocks(N, kStepBlock)), dim3(kStepBlock), args, shm, s, e[0], e[1], 0);
+            err = hipExtLaunchKernel(kn.fn, dim3(nblocks(N, kn.particles)), dim3(kStepBlock), args, shm, s, e[0], e[1], 0);
         }
     }
     if (err == hipSuccess) err = launch_fold_status(c->d_blk, nblocks(N, kStepBlock), nullptr, N, status, s);
@@ -835,18 +839,8 @@ struct PlainOps final : DriveOps {
                                       buf->bonds_log + row));
         return RC_OK;
     }
-    const void* graph_fn() override {
-        const void* fn;
-        step_kernel_info(false, c->gather_width, c->step_form, &fn);
-        return fn;
-    }
-    const void* graph_sums_fn() override {
-        if (c->step_form != RC_FORM_SUMS) return nullptr;
-        const void* fn;
-        sums_kernel_info(false, &fn);
-        return fn;
-    }
-    bool block_ok() override { return step_block_fits(N, c->nt, c->step_form); }
+    StepKernel plain_step() override { return step_kernel(false, false, c->gather_width, c->step_form, N, list_est(c, N, b)); }
+    bool block_ok() override { return step_block_fits(N, c->nt, c->step_form, list_est(c, N, b)); }
     // the cell sort permutes pos, vel and image through the workspace's
     // temporaries and copies them back, so those hold the rebuilt state
     bool rebuild_snapshot(const float4** p, const float4** v, const int4** im) override {

@@ -586,17 +586,7 @@ struct BatchOps final : DriveOps {
                                                 buf->ev_log + (size_t)row * b->R * kEvWords, kEvWords, s));
         return RC_OK;
     }
-    const void* graph_fn() override {
-        const void* fn;
-        step_batch_kernel_info(b->c.gather_width, b->c.step_form, &fn);
-        return fn;
-    }
-    const void* graph_sums_fn() override {
-        if (b->c.step_form != RC_FORM_SUMS) return nullptr;
-        const void* fn;
-        sums_kernel_info(true, &fn);
-        return fn;
-    }
+    StepKernel plain_step() override { return step_kernel(true, false, b->c.gather_width, b->c.step_form, b->n_slots, 0.0f); }
     // the batch cell sort also permutes (pos, vel, image) of every slot through
     // the workspace's temporaries and copies them back
     bool rebuild_snapshot(const float4** p, const float4** v, const int4** im) override {

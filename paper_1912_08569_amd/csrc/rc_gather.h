@@ -145,11 +145,20 @@ __device__ __forceinline__ void gather_sync() {
 // PK: the entries come from the packed copy of the list (pl_j, pl_o: neighbour
 // and owner lane of every flattened entry, pack_wave_lists) instead of the
 // owner map in LDS and a search of the list columns; same entries, same order.
-template <bool EV, int kPerLane, bool SF, class Ctx, bool WS = false, bool PK = false, int AHEAD = 1, int OW = kWave>
+// OW < 64: the first OW lanes own particles; with PK, pl_first is their first
+// entry in the packed list and lane0 the packed owner lane of their first.
+// mid(0), mid(1): called once each, while the first pass waits for its
+// neighbours' indices and for their positions.
+struct NoMid {
+    __device__ __forceinline__ void operator()(int) const {}
+};
+template <bool EV, int kPerLane, bool SF, class Ctx, bool WS = false, bool PK = false, int AHEAD = 1, int OW = kWave,
+          class Mid = NoMid>
 __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4& pm, int packed,
                                             const float4* pos, const int* nlist, const int* nn, int k_max,
                                             int N, const Ctx& ctx, Acc& acc, const float* ssum = nullptr,
-                                            const int* pl_j = nullptr, const unsigned char* pl_o = nullptr) {
+                                            const int* pl_j = nullptr, const unsigned char* pl_o = nullptr,
+                                            size_t pl_first = 0, int lane0 = 0, Mid&& mid = Mid{}) {
     const int nt = ctx.nt;
     constexpr int NC = Stage<EV, SF>::n;
     constexpr int CE = Stage<EV, SF>::e;
@@ -182,8 +191,10 @@ __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4&
     if (SF) s_S[lane] = live ? ssum[base_m + lane] : 0.0f;
     gather_sync<WS>();
     const int T = PK ? __builtin_amdgcn_readlane(inc, kWave - 1) : s_off[kWave];
-    const size_t pk_base = (size_t)base_m * k_max;  // the wavefront's region of the packed list
+    // the wavefront's entries of the packed list
+    const size_t pk_base = OW < kWave || WS ? pl_first : (size_t)base_m * k_max;
     double S = 0.0;
+    bool first = true;
     int nact = 0;
     for (int base = 0; base < T; base += W) {
         if (!PK) {
@@ -206,7 +217,7 @@ __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4&
             sw[u] = false;
             if (e < T) {
                 if (PK) {
-                    own[u] = pl_o[pk_base + e];
+                    own[u] = pl_o[pk_base + e] - (OW < kWave ? lane0 : 0);
                     jj[u] = pl_j[pk_base + e];
                     sw[u] = true;  // S_j is read for every entry and used for swap-kind ones only
                 } else {
@@ -219,11 +230,12 @@ __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4&
                 }
             }
         }
+        if (first) mid(0);
 #pragma unroll
         for (int u = 0; u < kPerLane; ++u) {
             pj[u] = pm;
             if (own[u] >= 0) {
-                // neighbours among the wave's own 64 particles come from its LDS copy
+                // neighbours among the wave's own particles come from its LDS copy
                 const unsigned lj = (unsigned)(jj[u] - base_m);
                 if (lj < (unsigned)OW)
                     pj[u] = s_pos[lj];
@@ -235,6 +247,8 @@ __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4&
                 sj[u] = sw[u] ? (lj < (unsigned)OW ? s_S[lj] : ssum[jj[u]]) : 0.0f;
             }
         }
+        if (first) mid(1);
+        first = false;
 #pragma unroll
         for (int u = 0; u < kPerLane; ++u) {
             float c[NC];
@@ -308,6 +322,10 @@ __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4&
         }
         gather_sync<WS>();
     }
+    if (first) {   // no entries at all
+        mid(0);
+        mid(1);
+    }
     if (!SF && live && nact >= 2) {
         const int m = base_m + lane;
         float prefix = 0.0f;
@@ -358,33 +376,104 @@ __device__ __forceinline__ float swap_sum(int m, const float4& pm, int packed, c
     return s;
 }
 
+// swap_sum of the OW particles of a wavefront, bit for bit, from its T entries
+// of the packed list (from pl_first on, owner lane lane0 the first's): the
+// entries evaluated flat, 64 PL per pass, and every owner's swap entries (ns of
+// them, from entry my_off on) added from LDS in slot order.  own_pos: the
+// owners' positions; s_w: the wavefront's slice.  Every lane takes part.
+template <int PL, int OW, bool WS>
+__device__ __forceinline__ float packed_sums(int base_m, const float4* own_pos, int my_off, int ns, int T, int lane0,
+                                             size_t pl_first, const float4* pos, const int* pl_j,
+                                             const unsigned char* pl_o, const DevEntry* tab, int nt, const Box& box,
+                                             float (*s_w)[PL * kWave]) {
+    constexpr int W = PL * kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    float S = 0.0f;
+    for (int base = 0; base < T; base += W) {
+        int own[PL], jj[PL];
+        float4 pj[PL];
+#pragma unroll
+        for (int u = 0; u < PL; ++u) {
+            const int e = base + u * kWave + lane;
+            own[u] = -1;
+            jj[u] = 0;
+            if (e < T) {
+                own[u] = pl_o[pl_first + e] - lane0;
+                jj[u] = pl_j[pl_first + e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PL; ++u) {
+            pj[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (own[u] >= 0) {
+                const unsigned lj = (unsigned)(jj[u] - base_m);
+                if (lj < (unsigned)OW) pj[u] = own_pos[lj];
+                else pj[u] = pos[jj[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PL; ++u) {
+            float sl = 0.0f, v = 0.0f;   // sqrt(lambda eps) and vhat of an entry inside its cutoff
+            if (own[u] >= 0) {
+                const float4 po = own_pos[own[u]];
+                const DevEntry& e = tab[ptype(po.w) * nt + ptype(pj[u].w)];
+                if (e.kind == RC_KIND_SWAP) {
+                    const PairGeom g = pair_geom<false>(po, pj[u], box, e);
+                    if (g.cut) {
+                        sl = e.sqrt_lam;
+                        v = vhat_value(e, g.inside, g.r2);
+                    }
+                }
+            }
+            s_w[0][u * kWave + lane] = sl;
+            s_w[1][u * kWave + lane] = v;
+        }
+        gather_sync<WS>();
+        const int lo = max(my_off, base) - base, hi = min(my_off + ns, base + W) - base;
+        for (int q = lo; q < hi; ++q) S = __fmaf_rn(s_w[0][q], s_w[1][q], S);
+        gather_sync<WS>();
+    }
+    return S;
+}
+
 // FENE springs of particle m (tag-indexed partner table, -1 = none; rtag
 // maps a tag to its current index): F_m += K d / (1 - r^2/R0^2) per bond,
 // d = x_j - x_m (minimum image); half the bond energy -(K R0^2/2) ln(1 -
 // r^2/R0^2) and half its virial -K d d /(1 - r^2/R0^2) go to m.  A bond
 // stretched to R0 or beyond yields a non-finite force.
 template <bool EV>
+__device__ __forceinline__ void fene_one(const float4& pm, const float4& pj, const Box& box, float K, float R02,
+                                         Acc& acc) {
+    double dxd, dyd, dzd;
+    const double r2d = canon_r2(pm, pj, box, dxd, dyd, dzd);
+    const float dx = (float)dxd, dy = (float)dyd, dz = (float)dzd;
+    const float s = 1.0f - (float)r2d / R02;
+    const float g = s > 0.0f ? K / s : __int_as_float(0x7fc00000);
+    acc.fx = __fmaf_rn(g, dx, acc.fx);
+    acc.fy = __fmaf_rn(g, dy, acc.fy);
+    acc.fz = __fmaf_rn(g, dz, acc.fz);
+    if (EV) {
+        acc.e += -0.25f * K * R02 * logf(s);
+        acc_virial(acc, -0.5f * g, dx, dy, dz);
+    }
+}
+
+template <bool EV>
 __device__ __forceinline__ void fene_add(int tag, const float4& pm, const int2* bonds, const int* rtag,
                                          const float4* pos, const Box& box, float K, float R02, Acc& acc) {
     const int2 b = bonds[tag];
     const int part[2] = {b.x, b.y};
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        if (part[q] < 0) continue;
-        const float4 pj = pos[rtag[part[q]]];
-        double dxd, dyd, dzd;
-        const double r2d = canon_r2(pm, pj, box, dxd, dyd, dzd);
-        const float dx = (float)dxd, dy = (float)dyd, dz = (float)dzd;
-        const float s = 1.0f - (float)r2d / R02;
-        const float g = s > 0.0f ? K / s : __int_as_float(0x7fc00000);
-        acc.fx += g * dx;
-        acc.fy += g * dy;
-        acc.fz += g * dz;
-        if (EV) {
-            acc.e += -0.25f * K * R02 * logf(s);
-            acc_virial(acc, -0.5f * g, dx, dy, dz);
-        }
-    }
+    for (int q = 0; q < 2; ++q)
+        if (part[q] >= 0) fene_one<EV>(pm, pos[rtag[part[q]]], box, K, R02, acc);
+}
+
+// the springs to partners already read: indices (-1 = none) and positions
+__device__ __forceinline__ void fene_pair(const int (&part)[2], const float4 (&pj)[2], const float4& pm,
+                                          const Box& box, float K, float R02, Acc& acc) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (part[q] >= 0) fene_one<false>(pm, pj[q], box, K, R02, acc);
 }
 
 // A double moved across lanes by a DPP pattern with a source for every lane.

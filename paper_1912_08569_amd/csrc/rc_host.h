@@ -222,10 +222,8 @@ struct DriveOps {
     virtual hipError_t launch(const StepArgs& a, bool ev) = 0;
     // reduce the partial rows of the last ev launch into log row `row`
     virtual int reduce_ev(int row) = 0;
-    // kernel that the step graphs replay, and the first-pass kernel of the
-    // sums form (NULL for the walk form)
-    virtual const void* graph_fn() = 0;
-    virtual const void* graph_sums_fn() = 0;
+    // the kernels of a plain step (launched and replayed)
+    virtual StepKernel plain_step() = 0;
     // whether graph replays may run as one-workgroup launches of G steps, and
     // such a launch (a: launch arguments of the replay's first step)
     virtual bool block_ok() { return false; }

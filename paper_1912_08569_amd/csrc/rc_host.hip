@@ -444,11 +444,11 @@ static int add_node(rc_ctx* c, hipGraph_t g, hipGraphNode_t& prev, const void* f
     return RC_OK;
 }
 
-static int build_graphs(rc_ctx* c, const void* fn, const void* sums_fn, const StepArgs& tmpl, int G, hipStream_t s) {
+static int build_graphs(rc_ctx* c, const StepKernel& kn, const StepArgs& tmpl, int G, hipStream_t s) {
     drop_graphs(c);
     const void* add_fn;
     add_step_kernel_info(&add_fn);
-    const int nb = nblocks(tmpl.N, kStepBlock);
+    const int nb = nblocks(tmpl.N, kn.particles);
     const size_t shm = sizeof(DevEntry) * c->nt * c->nt;
     int r;
     for (int p = 0; p < 2; ++p) {
@@ -467,13 +467,13 @@ static int build_graphs(rc_ctx* c, const void* fn, const void* sums_fn, const St
             a.step = (uint64_t)k;
             a.step_base = c->d_step_base;
             a.ev_part = nullptr;
-            if (sums_fn) {
+            if (kn.sums_fn) {
                 ForceArgs f = step_sums_args(a);
                 void* args[] = {&f};
-                if ((r = add_node(c, g, prev, sums_fn, args, nblocks(tmpl.N, kWave), kWave, shm))) return r;
+                if ((r = add_node(c, g, prev, kn.sums_fn, args, nblocks(tmpl.N, kn.sums_particles), kWave, shm))) return r;
             }
             void* args[] = {&a};
-            if ((r = add_node(c, g, prev, fn, args, nb, kStepBlock, shm))) return r;
+            if ((r = add_node(c, g, prev, kn.fn, args, nb, kStepBlock, shm))) return r;
         }
         {
             unsigned long long* p_base = c->d_step_base;
@@ -486,7 +486,7 @@ static int build_graphs(rc_ctx* c, const void* fn, const void* sums_fn, const St
         HIP_TRY(c, hipGraphUpload(c->gc.exec[p], s));
     }
     c->gc.key = tmpl;
-    c->gc.fn = fn;
+    c->gc.fn = kn.fn;
     c->gc.steps = G;
     c->gc.valid = true;
     return RC_OK;
@@ -674,7 +674,7 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
         }
         if (timing && !ev && (mode == RC_STEP_START || mode == RC_STEP_CONT)) {
             // the plain step launches (log steps and the finishing kick are other work)
-            const bool two = ops.graph_sums_fn() != nullptr;
+            const bool two = ops.plain_step().sums_fn != nullptr;
             size_t qk = 0, qs = 0;
             int rr = tk_take(&qk, 0);
             if (!rr && two) rr = tk_take(&qs, 1);
@@ -711,9 +711,9 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
         StepArgs key = tmpl;
         key.pos_in = reinterpret_cast<const float4*>(buf->pos);
         key.pos_out = reinterpret_cast<float4*>(buf->pos_alt);
-        const void* fn = ops.graph_fn();
-        if (!c->gc.valid || c->gc.steps != G || c->gc.fn != fn || !same_args(c->gc.key, key)) {
-            if ((r = build_graphs(c, fn, ops.graph_sums_fn(), key, G, s))) return finish(r);
+        const StepKernel kn = ops.plain_step();
+        if (!c->gc.valid || c->gc.steps != G || c->gc.fn != kn.fn || !same_args(c->gc.key, key)) {
+            if ((r = build_graphs(c, kn, key, G, s))) return finish(r);
         }
     }
     uint64_t dev_base = ~0ull;   // value *d_step_base will hold once queued work ran

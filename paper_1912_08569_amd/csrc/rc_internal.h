@@ -445,6 +445,7 @@ struct StepArgs {
     const RepDesc* rep;        // [R]
     const int* chunk_rep;      // [N / 64] replica of each 64-slot chunk
     const uint64_t* seeds;     // [R] thermostat keys
+    float list_est;            // single systems: list entries per particle at the largest list radius (launcher)
     int width;                 // gather width of the non-logging steps: 1, 2 or 4 (read by the launcher)
     int form;                  // RC_FORM_WALK or RC_FORM_SUMS (read by the launcher)
     float* ssum;               // [N] per-particle switching sums (RC_FORM_SUMS)
@@ -467,13 +468,18 @@ hipError_t launch_step_timed(const StepArgs& a, bool batch, hipStream_t s, hipEv
 // (the buffer a.pos_in names), *step_base is read as the first step's index
 // and advanced by G.  step_block_fits says whether a system fits the kernel.
 constexpr int kBlockMaxN = 1024;
-bool step_block_fits(int N, int nt, int form);
+bool step_block_fits(int N, int nt, int form, float list_est);
 hipError_t launch_step_block(const StepArgs& a, float4* pos_final, unsigned long long* step_base, int G,
                              hipStream_t s);
-// the head-form step kernel (same launch shape and arguments as k_step)
-void step_kernel_info(bool ev, int width, int form, const void** fn);
 hipError_t launch_step_batch(const StepArgs& a, bool ev, hipStream_t s);
-void step_batch_kernel_info(int width, int form, const void** fn);
+// the kernels of one step of N particles: fn on blocks of one wavefront for `particles` each (its only
+// argument a StepArgs), after sums_fn (a ForceArgs, sums_particles per block) when that is not NULL
+struct StepKernel {
+    const void* fn = nullptr;
+    const void* sums_fn = nullptr;
+    int particles = kStepBlock, sums_particles = kStepBlock;
+};
+StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_est);
 
 struct ForceArgs {
     const float4* pos;
@@ -490,15 +496,15 @@ struct ForceArgs {
     const RepDesc* rep;    // batches only
     const int* chunk_rep;
     float* ssum;           // [N] switching sums: non-NULL selects the two-pass form
+    const int* pl_j;       // the packed list (a step's first pass only)
+    const unsigned char* pl_o;
 };
 hipError_t launch_forces_triplet(const ForceArgs& a, hipStream_t s);
 // particles per wavefront (and per row of ev_part) of the gather kernel for N particles
 int gather_owners(int N);
 hipError_t launch_forces_gather(const ForceArgs& a, hipStream_t s);
 hipError_t launch_forces_gather_batch(const ForceArgs& a, hipStream_t s);
-// first pass of the two-pass form: the kernel that fills ssum (for graphs)
-// and its arguments for a step (positions pos_in)
-void sums_kernel_info(bool batch, const void** fn);
+// arguments of the first pass of the two-pass form for a step (positions pos_in)
 ForceArgs step_sums_args(const StepArgs& a);
 
 struct IntegrateArgs {

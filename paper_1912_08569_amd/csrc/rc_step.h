@@ -10,11 +10,15 @@
 
 namespace rc {
 
-template <bool EV>
+// NZ: the thermostat normals were drawn by the caller (nz).  SHARED: other
+// wavefronts of the same 64-particle block write its status slot too.  v_out: a
+// copy of the new velocity and path length.
+template <bool EV, bool NZ = false, bool SHARED = false>
 __device__ __forceinline__ void step_finish(const StepArgs& a, float4* pos_out, int m, int blk, bool live,
                                             const float4& pm,
                                             const float4& vm, const Acc& acc, const Box& box, int tag0,
-                                            uint64_t seed, uint64_t step) {
+                                            uint64_t seed, uint64_t step, const float* nz = nullptr,
+                                            float4* v_out = nullptr) {
     float kin[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float path = 0.0f, path_in = 0.0f;
     bool bad = false, lost = false;
@@ -44,7 +48,13 @@ __device__ __forceinline__ void step_finish(const StepArgs& a, float4* pos_out, 
             float sx = hdt * vx, sy = hdt * vy, sz = hdt * vz;  // A (first half of the drift)
             if (a.langevin) {                                  // O
                 float z0, z1, z2;
-                thermostat_normals(seed, (uint32_t)(ptag(pm.w) - tag0), step, z0, z1, z2);
+                if constexpr (NZ) {
+                    z0 = nz[0];
+                    z1 = nz[1];
+                    z2 = nz[2];
+                } else {
+                    thermostat_normals(seed, (uint32_t)(ptag(pm.w) - tag0), step, z0, z1, z2);
+                }
                 const float c2 = a.c2[tm];
                 vx = a.c1 * vx + c2 * z0;
                 vy = a.c1 * vy + c2 * z1;
@@ -65,6 +75,7 @@ __device__ __forceinline__ void step_finish(const StepArgs& a, float4* pos_out, 
                     isfinite(vz));
             pos_out[m] = make_float4(x, y, z, pm.w);
             a.vel[m] = make_float4(vx, vy, vz, path);
+            if (v_out) *v_out = make_float4(vx, vy, vz, path);
             if (a.image && (ix | iy | iz)) {
                 int4 im = a.image[m];
                 im.x += ix;
@@ -87,9 +98,15 @@ __device__ __forceinline__ void step_finish(const StepArgs& a, float4* pos_out, 
         if (fl) {
             int* slot = a.blk + 3 * blk;
             const int st = (int)(step & 0x7fffffff);
-            slot[0] |= fl;
-            if (fl & RC_FLAG_REBUILD) slot[1] = min(slot[1], st);
-            if (fl & RC_FLAG_STALE) slot[2] = min(slot[2], st);
+            if constexpr (SHARED) {
+                atomicOr(&slot[0], fl);
+                if (fl & RC_FLAG_REBUILD) atomicMin(&slot[1], st);
+                if (fl & RC_FLAG_STALE) atomicMin(&slot[2], st);
+            } else {
+                slot[0] |= fl;
+                if (fl & RC_FLAG_REBUILD) slot[1] = min(slot[1], st);
+                if (fl & RC_FLAG_STALE) slot[2] = min(slot[2], st);
+            }
         }
     }
     if (EV) {

@@ -68,3 +68,36 @@ def test_forces_per_wavefront(N, density, gather):
     assert_pe(F[:, 3], ref)
     assert_energy(float(ev[0]), ref)
     assert_virial(ev[1:7].cpu().numpy(), ref)
+
+
+def _step_system(name):
+    kind, n = name.split("-")
+    n = int(n)
+    if kind == "dumbbells":
+        return W.dumbbell_mixture(N=n, seed=n)
+    if kind == "assembly":
+        return W.assembly_mixture(N=n, seed=n)
+    if kind == "reactive":
+        return W.small_reactive(N=n, density=0.25, seed=n, min_dist=0.95)
+    return W.vitrimer_network(n_chains=n, n_dimers=3, seed=n)
+
+
+@pytest.mark.parametrize("form", ["walk", "sums"])
+@pytest.mark.parametrize("name", ["dumbbells-70", "dumbbells-511", "dumbbells-512", "dumbbells-513", "dumbbells-1024",
+                                  "dumbbells-1025", "assembly-333", "assembly-20001", "reactive-100", "reactive-700",
+                                  "reactive-20481", "reactive-41000", "network-9", "network-300"])
+def test_few_particles_per_wavefront_equal_64(name, form):
+    # plain steps of small systems (8, 16 or 32 particles per wavefront, the one-workgroup replays, springs)
+    # against the same steps taken as log steps, which always run 64 particles per wavefront: bit for bit,
+    # in the plain and the graph replayed form
+    from paper_1912_08569_amd import System
+    s = _step_system(name)
+    dt = 2e-4 if name.startswith("network") else 0.001
+    out = []
+    for period, graph in ((1, False), (0, False), (0, True)):
+        S = System.from_workload(s, step_form=form)
+        cfg = S.integrator(dt=dt, kT=0.05, gamma=1.0, seed=11)
+        S.run(50, cfg, log_period=period, use_graph=graph, max_chunk=18, adapt=False)
+        out.append((S.pos.clone(), S.vel.clone(), S.image.clone()))
+    for other in out[1:]:
+        assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(out[0], other))
