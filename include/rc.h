@@ -354,6 +354,23 @@ int rc_rigid_step(rc_ctx* ctx, float* pos, float* vel, const float* force, int* 
                   const rc_integrator* cfg /* host */, uint64_t step, int half, int* status /* NULL ok */,
                   void* stream);
 
+/* Steps of rigid bodies: for k = 0 .. n_steps - 1 the first half of step step0
+ * + k, the forces (rc_compute_forces with RC_FORCE_GATHER on the given list,
+ * plus the springs of rc_set_bonds if any) and the second half, as rc_rigid_step
+ * does them, from the forces in `force`.  The run ends early, before the forces
+ * of the first step k in which some particle's path length (vel.w) is not at
+ * most `soft` after its first half: *done (host) receives that k, n_steps when
+ * every step was done.  The caller then builds the list and calls again with
+ * step0 + k, n_steps - k and pending != 0 (the first half of step0 is done
+ * already; its forces are evaluated first).
+ * RC_ERR_NONFINITE: a path length is not finite (*done is the step, its first
+ * half done).  Returns when the steps are done.  n_steps >= 1.                  */
+int rc_rigid_run(rc_ctx* ctx, float* pos, float* vel, float* force, int* image /* NULL ok */, const int* rtag,
+                 const int* nlist, const int* nn, int k_max, int B, const int* centre, const int* first,
+                 const int* member, const float* offset, const float* inertia, float* theta, float* omega, int N,
+                 rc_box box, const rc_integrator* cfg /* host */, uint64_t step0, int n_steps, int pending,
+                 double soft, int* status /* NULL ok */, int* done /* host */, void* stream);
+
 /* ---- fused step (the metric path: a3 + a5 in one kernel) ---------------------
  * One kernel per MD step.  Reads pos_in, writes pos_out (pos_in != pos_out,
  * double buffered).  Each particle m gathers every force term that moves it:

@@ -22,7 +22,7 @@ __all__ = [
     "rc_compute_forces_noalloc", "rc_thermostat_normals", "rc_workspace_bytes", "rc_set_workspace",
     "rc_ctx_device_bytes", "rc_batch_workspace_bytes", "rc_batch_set_workspace",
     "rc_integrate_step", "rc_step_fused", "rc_bond_count", "rc_md_run", "rc_force_hvp", "rc_force_hvp_batch", "rc_partner_counts", "rc_stress_autocorrelation",
-    "rc_param_grad", "rc_clear_status", "rc_read_status", "rc_time_fused_steps",
+    "rc_rigid_step", "rc_rigid_run", "rc_param_grad", "rc_clear_status", "rc_read_status", "rc_time_fused_steps",
     "rc_param_vjp", "rc_soft_bonds", "rc_bond_partners", "rc_set_bonds", "rc_fene_forces", "BatchContext", "rc_batch_cells_workspace_bytes", "rc_batch_build_cells", "rc_batch_build_nlist",
     "rc_batch_compute_forces", "rc_batch_bond_count", "rc_batch_step_fused", "rc_batch_run",
     "rc_batch_time_fused_steps", "rc_batch_relayout_lists",
@@ -207,6 +207,22 @@ def rc_rigid_step(ctx: Context, pos, vel, force, image, rtag, bodies, theta, ome
                                  _ptr(bodies["member"]), _ptr(bodies["offset"]), _ptr(bodies["inertia"]),
                                  _ptr(theta), _ptr(omega), N, bx, ctypes.byref(cfg), int(step), int(half),
                                  _ptr(status), _stream(stream)), ctx.handle)
+
+
+def rc_rigid_run(ctx: Context, pos, vel, force, image, rtag, nlist, nn, bodies, theta, omega, bx, cfg, step0, n_steps,
+                 pending, soft, status=None, stream=None):
+    """(code, steps done): RC_OK, or RC_ERR_NONFINITE for a non-finite path length (other errors raise)."""
+    N = pos.shape[0]
+    done = ctypes.c_int()
+    code = L.load().rc_rigid_run(ctx.handle, _ptr(pos), _ptr(vel), _ptr(force), _ptr(image), _ptr(rtag), _ptr(nlist),
+                                 _ptr(nn), _kmax(nlist, N), int(bodies["centre"].shape[0]), _ptr(bodies["centre"]),
+                                 _ptr(bodies["first"]), _ptr(bodies["member"]), _ptr(bodies["offset"]),
+                                 _ptr(bodies["inertia"]), _ptr(theta), _ptr(omega), N, bx, ctypes.byref(cfg),
+                                 int(step0), int(n_steps), int(pending), float(soft), _ptr(status),
+                                 ctypes.byref(done), _stream(stream))
+    if code != L.RC_ERR_NONFINITE:
+        check(code, ctx.handle)
+    return code, done.value
 
 
 def rc_compute_forces(ctx: Context, pos, nlist, nn, bx, force, ev=None, flags=0, status=None, stream=None):

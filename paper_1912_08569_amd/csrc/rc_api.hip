@@ -141,7 +141,7 @@ int rc_create(rc_ctx** out, int ntypes, const rc_pair_coeff* table, double r_buf
         hipMalloc(&c->d_tab, sizeof(DevEntry) * ntypes * ntypes) != hipSuccess ||
         hipMemcpy(c->d_tab, c->host_tab.data(), sizeof(DevEntry) * ntypes * ntypes,
                   hipMemcpyHostToDevice) != hipSuccess ||
-        hipMalloc(&c->d_step_base, sizeof(unsigned long long)) != hipSuccess ||
+        hipMalloc(&c->d_step_base, 2 * sizeof(unsigned long long)) != hipSuccess ||
         hipMalloc(&c->d_slices, sizeof(double) * kRowSlices) != hipSuccess ||
         noalloc_scratch_here(c->device, &c->noalloc_scratch) != hipSuccess ||
         // the private stream the driver's rebuild graphs are recorded on: created here, as creating a

@@ -84,7 +84,7 @@ struct rc_ctx {
     rc::DevEntry* d_tab = nullptr;
     double* d_part = nullptr;           // block partial rows (13 doubles each) or param partials
     size_t part_bytes = 0;
-    unsigned long long* d_step_base = nullptr;
+    unsigned long long* d_step_base = nullptr;   // the replays' step counter, then a rigid run's stop word
     double* d_slices = nullptr;         // kRowSlices doubles: the two-launch row reduction
     int* d_blk = nullptr;               // per-block status slots of the step kernel
     int blk_cap = 0;                    // slots allocated (blocks)
@@ -105,7 +105,7 @@ struct rc_ctx {
     const int* bonds_rtag = nullptr;    // tag -> index map the springs read (caller-owned)
     int bonds_n = 0;
     double fene_k = 0.0, fene_r0 = 0.0;
-    int* h_status = nullptr;            // pinned host copy of a status word (driver waits)
+    int* h_status = nullptr;            // pinned: a status word's host copy (driver waits), then kHostWords more
     hipEvent_t ev_sync = nullptr;       // the driver's wait event (no timing)
     GraphCache gc;
     RebuildGraph rg[2];                 // the driver's rebuilds, one per position buffer
@@ -168,6 +168,11 @@ int ensure_plist(rc_ctx* c, int N, int k_max);
 // the packed copy of (nlist, nn, k_max, N): made on the stream unless it is the current one
 int packed_list_for(rc_ctx* c, const int* nlist, const int* nn, int k_max, int N, hipStream_t s);
 void free_ctx_buffers(rc_ctx* c);       // every device buffer the context owns
+// the context's pinned host words (kHostWords that kernels write follow the status copy) and wait event
+constexpr int kHostWords = 8;
+int ensure_host_words(rc_ctx* c);
+// wait for everything queued on the stream so far
+int wait_spin(rc_ctx* c, hipStream_t s);
 // copy a device status word to the host and wait for it by spinning on an event
 int read_status_spin(rc_ctx* c, const int* d_status, int* hst, hipStream_t s);
 int ensure_blk(rc_ctx* c, int nb, hipStream_t s);

@@ -141,7 +141,7 @@ int set_workspace(rc_ctx* c, void* ws, size_t bytes, int N, int k_max, int nvec)
 }
 
 size_t ctx_device_bytes(const rc_ctx* c) {
-    size_t b = sizeof(DevEntry) * (size_t)c->nt * (size_t)c->nt + sizeof(unsigned long long) + c->part_bytes +
+    size_t b = sizeof(DevEntry) * (size_t)c->nt * (size_t)c->nt + 2 * sizeof(unsigned long long) + c->part_bytes +
                sizeof(int) * 3 * (size_t)c->blk_cap + (c->d_slices ? sizeof(double) * kRowSlices : 0);
     if (!c->ws_user) b += 5 * c->pl_cap + sizeof(float) * c->ssum_cap + 2 * sizeof(double) * c->hsum_cap;
     return b;
@@ -162,19 +162,30 @@ int ensure_ssum(rc_ctx* c, size_t n) {
     return RC_OK;
 }
 
-int read_status_spin(rc_ctx* c, const int* d_status, int* hst, hipStream_t s) {
-    if (!c->h_status) HIP_TRY(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_status), sizeof(int) * RC_STATUS_WORDS));
+int ensure_host_words(rc_ctx* c) {
+    if (!c->h_status)
+        HIP_TRY(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_status), sizeof(int) * (RC_STATUS_WORDS + kHostWords)));
     if (!c->ev_sync) HIP_TRY(c, hipEventCreateWithFlags(&c->ev_sync, hipEventDisableTiming));
-    HIP_TRY(c, hipMemcpyAsync(c->h_status, d_status, sizeof(int) * RC_STATUS_WORDS, hipMemcpyDeviceToHost, s));
-    for (const rc_ctx::StatusExtra& x : c->status_extra)
-        HIP_TRY(c, hipMemcpyAsync(x.host, x.dev, x.bytes, hipMemcpyDeviceToHost, s));
+    return RC_OK;
+}
+
+int wait_spin(rc_ctx* c, hipStream_t s) {
     HIP_TRY(c, hipEventRecord(c->ev_sync, s));
-    // a blocking synchronisation costs tens of microseconds of wake-up per call; the driver calls
-    // this once per chunk, so it spins on the event instead
+    // a blocking synchronisation costs tens of microseconds of wake-up per call, so this spins on the event
     hipError_t e;
     while ((e = hipEventQuery(c->ev_sync)) == hipErrorNotReady) {
     }
-    if (e != hipSuccess) return hip_fail(c, e, "waiting for the status word");
+    if (e != hipSuccess) return hip_fail(c, e, "waiting for the stream");
+    return RC_OK;
+}
+
+int read_status_spin(rc_ctx* c, const int* d_status, int* hst, hipStream_t s) {
+    int r = ensure_host_words(c);
+    if (r) return r;
+    HIP_TRY(c, hipMemcpyAsync(c->h_status, d_status, sizeof(int) * RC_STATUS_WORDS, hipMemcpyDeviceToHost, s));
+    for (const rc_ctx::StatusExtra& x : c->status_extra)
+        HIP_TRY(c, hipMemcpyAsync(x.host, x.dev, x.bytes, hipMemcpyDeviceToHost, s));
+    if ((r = wait_spin(c, s))) return r;
     std::memcpy(hst, c->h_status, sizeof(int) * RC_STATUS_WORDS);
     return RC_OK;
 }

@@ -2,14 +2,13 @@
 
 A body is a disk (its centre particle) with massless member particles at fixed
 body-frame offsets; both are particles of the System.  Each step launches the
-stand-alone force kernel on every particle and the body kernel of
-``rc_rigid_step`` for the two BAOAB halves; the list is rebuilt when a path
-length passes the soft skin threshold.  Every step runs in the library's HIP
-kernels; this module only holds the body arrays and sequences the calls.
+stand-alone force kernel on every particle and the body kernel for the two BAOAB
+halves (``rc_rigid_run``); the list is rebuilt when a path length passes the soft
+skin threshold.  Every step runs in the library's HIP kernels; this module only
+holds the body arrays and builds the lists in between.
 """
 from __future__ import annotations
 
-import math
 import time
 
 import numpy as np
@@ -33,11 +32,6 @@ class RigidBodies:
         self.theta = torch.as_tensor(np.asarray(theta, np.float32), device=dev).clone()
         self.omega = torch.as_tensor(np.asarray(omega, np.float32), device=dev).clone()
 
-    def _half(self, cfg, step, half):
-        S = self.S
-        api.rc_rigid_step(S.ctx, S.pos, S.vel, S.force, S.image, S.rtag, self.b, self.theta, self.omega, S.box,
-                          cfg, step, half, S.status)
-
     def run(self, n_steps: int, cfg, step0: int = 0, soft_frac: float = 0.8) -> dict:
         """n_steps body steps (cfg: an integrator of dim 2); returns rebuild count and wall time."""
         S = self.S
@@ -48,15 +42,17 @@ class RigidBodies:
         rebuilds = 0
         torch.cuda.synchronize()
         t0 = time.perf_counter()
-        for k in range(n_steps):
-            self._half(cfg, step0 + k, rcl.RC_HALF_FIRST)
-            mp = float(S.vel[:, 3].max())
-            if not math.isfinite(mp):
+        k, pending = 0, False
+        while k < n_steps:
+            code, done = api.rc_rigid_run(S.ctx, S.pos, S.vel, S.force, S.image, S.rtag, S.nlist, S.nn, self.b,
+                                          self.theta, self.omega, S.box, cfg, step0 + k, n_steps - k, pending, soft,
+                                          S.status)
+            k += done
+            if code != rcl.RC_OK:
                 raise RuntimeError(f"rigid bodies: non-finite state at step {step0 + k}")
-            if mp > soft:
+            if k < n_steps:      # step k has its first half and waits for a list
                 S.build()
                 rebuilds += 1
-            S.compute_forces(gather=True, ev=False)
-            self._half(cfg, step0 + k, rcl.RC_HALF_SECOND)
+                pending = True
         torch.cuda.synchronize()
         return {"rebuilds": rebuilds, "seconds": time.perf_counter() - t0}

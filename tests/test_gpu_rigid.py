@@ -106,3 +106,72 @@ def test_rigid_argument_errors():
     S, R = _bodies(s)
     with pytest.raises(RcError):   # rigid planar bodies need dim 2
         R.run(1, S.integrator(dt=0.001, kT=1.0, gamma=1.0, seed=5, dim=3))
+
+
+def _wheels(B, seed):
+    """B bodies on a jittered lattice with 0 to 6 rim members each (more and fewer than four lanes hold)."""
+    rng = np.random.default_rng(seed)
+    arms = (np.arange(B) * 5 + 3) % 7
+    first = np.concatenate([[0], np.cumsum(arms)]).astype(np.int32)
+    own = np.repeat(np.arange(B), arms)
+    side = max(4, int(np.ceil(np.sqrt(B))))
+    L = (float(np.float32(1.6 * side)), float(np.float32(1.6 * side)), 8.0)
+    cen = np.zeros((B, 3))
+    at = np.arange(B)
+    cen[:, 0] = (at % side + 0.5) * 1.6 - 0.5 * L[0] + rng.uniform(-0.1, 0.1, B)
+    cen[:, 1] = (at // side + 0.5) * 1.6 - 0.5 * L[1] + rng.uniform(-0.1, 0.1, B)
+    ang = 2.0 * np.pi * (np.arange(len(own)) - first[own]) / np.maximum(arms[own], 1)
+    offset = (0.5 * np.stack([np.cos(ang), np.sin(ang)], axis=1)).astype(np.float32)
+    bodies = dict(centre=np.arange(B, dtype=np.int32), first=first, offset=offset,
+                  member=np.arange(B, B + len(own), dtype=np.int32), inertia=rng.uniform(0.1, 0.2, B).astype(np.float32))
+    theta = rng.uniform(-3.0, 3.0, B).astype(np.float32)
+    omega = (2.0 * rng.standard_normal(B)).astype(np.float32)
+    pos = rigid_ref.place(np.concatenate([cen, np.zeros((len(own), 3))]), bodies, theta, np.array(L))
+    types = np.concatenate([np.zeros(B, np.int32), np.full(len(own), 2, np.int32)])
+    vel = np.zeros(pos.shape, np.float32)
+    vel[:B, :2] = 2.0 * rng.standard_normal((B, 2))
+    return bodies, theta, omega, pos.astype(np.float32), types, vel, L
+
+
+@pytest.mark.parametrize("B", [1, 15, 17, 130])
+def test_rigid_run_equals_single_half_steps(B):
+    # the queued run (fused halves, device-side stop at a list build) against rc_rigid_step and
+    # rc_compute_forces called one by one, bit for bit, over several rebuilds; the first step to the oracle
+    from paper_1912_08569_amd import RigidBodies, System
+    from paper_1912_08569_amd import _lib as rcl
+    from paper_1912_08569_amd import api
+    bodies, theta, omega, pos, types, vel, L = _wheels(B, 1017)
+    print(f"case: B={B} N={len(pos)}", flush=True)
+    table, steps, frac = W.patchy_table(), 60, 0.8
+
+    def fresh():
+        S = System(pos, types, L, table, vel=vel)
+        S.build()
+        return S, RigidBodies(S, bodies, theta, omega), S.integrator(dt=0.002, kT=1.0, gamma=1.0, seed=3, dim=2)
+
+    S, R, cfg = fresh()
+    x0, v0, _, ty = S.state_by_tag()
+    R.run(1, cfg, step0=5)
+    x1 = S.state_by_tag()[0]
+    ref = rigid_ref.step(x0, v0, theta, omega, ty, bodies, S.edges, table, S.mass, 0.002, 1.0, 1.0, 3, 5)
+    dx = np.abs(swap_ref.min_image(ref["pos"], x1.astype(np.float64), np.array(S.edges)))
+    assert dx.max() < 1e-5, dx.max()
+
+    S, R, cfg = fresh()
+    got = R.run(steps, cfg, step0=5, soft_frac=frac)
+    T, Q, cfg = fresh()
+    T.compute_forces(gather=True, ev=False)
+    builds = 0
+    for k in range(steps):
+        for half in (rcl.RC_HALF_FIRST, rcl.RC_HALF_SECOND):
+            api.rc_rigid_step(T.ctx, T.pos, T.vel, T.force, T.image, T.rtag, Q.b, Q.theta, Q.omega, T.box, cfg,
+                              5 + k, half, T.status)
+            if half == rcl.RC_HALF_FIRST:
+                if float(T.vel[:, 3].max()) > 0.5 * T.r_buff * frac:
+                    T.build()
+                    builds += 1
+                T.compute_forces(gather=True, ev=False)
+    assert got["rebuilds"] == builds >= 1
+    for a, b in ((S.pos, T.pos), (S.vel, T.vel), (S.image, T.image), (R.theta, Q.theta), (R.omega, Q.omega),
+                 (S.force, T.force)):
+        assert bool((a == b).all())
