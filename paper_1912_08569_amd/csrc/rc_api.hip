@@ -705,7 +705,7 @@ int rc_param_grad(rc_ctx* c, const float* pos, const int* nlist, const int* nn, 
     if (!nlist || !nn || !grad) return fail(c, RC_ERR_ARG, "nlist / nn / grad are NULL");
     Box b;
     if ((r = make_box(c, box, b))) return r;
-    const int nb = nblocks(N, kBlock);
+    const int nb = nblocks(N, param_block(N));
     const int nv = c->nt * c->nt * 3;
     if ((r = ensure_part(c, sizeof(double) * (size_t)nv * nb))) return r;
     if ((r = check_list(c, nlist, nn, k_max))) return r;
@@ -732,7 +732,7 @@ int rc_param_vjp(rc_ctx* c, const float* pos, const int* nlist, const int* nn, i
     if (reinterpret_cast<uintptr_t>(adj) & 15) return fail(c, RC_ERR_ARG, "adj not 16-byte aligned");
     Box b;
     if ((r = make_box(c, box, b))) return r;
-    const int nb = nblocks(N, kBlock);
+    const int nb = nblocks(N, param_block(N));
     const int nv = c->nt * c->nt * 3;
     if ((r = ensure_part(c, sizeof(double) * (size_t)nv * nb))) return r;
     if ((r = check_list(c, nlist, nn, k_max))) return r;

@@ -629,6 +629,8 @@ hipError_t launch_partner_counts(const int* p0, const int* pt, const unsigned ch
 hipError_t launch_stress_acf(const double* rows, int T, double volume, double kT, int max_lag, double* G,
                              hipStream_t s);
 
+// threads per block (and row of partial sums) of the parameter-derivative kernels for N particles
+int param_block(int N);
 struct ParamArgs {
     const float4* pos;
     const int* nlist;
