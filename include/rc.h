@@ -575,6 +575,21 @@ int rc_set_bonds(rc_ctx* ctx, const int* bonds /* [N*2] | NULL */, const int* rt
 int rc_fene_forces(rc_ctx* ctx, const float* pos, int N, rc_box box, float* force /* [N*4] */,
                    double* ev /* [7] | NULL */, void* stream);
 
+/* ---- tag-ordered views (device arrays of N particles) -------------------------
+ * rc_load_by_tag: pos (float4, w = (tag << 4) | type, engine order) receives
+ *   xyz [N*3] (by tag) folded into the box.
+ * rc_load_moved: waits for the last rc_load_by_tag alone (not for work queued
+ *   after it); *moved (host) is 1 when some particle was then farther than reach
+ *   (minimum image) from ref [N*3] (by tag) and every distance was a number.
+ * rc_to_tags: out[3t ..] = arr[rtag[t]] (float4 array in engine order, w dropped),
+ *   negated if negate != 0.
+ * rc_from_tags: out[i] = (v[3t ..], 0) for the tag t of pos[i].                  */
+int rc_load_by_tag(rc_ctx* ctx, float* pos, const float* xyz, const float* ref, int N, rc_box box, double reach,
+                   void* stream);
+int rc_load_moved(rc_ctx* ctx, int* moved);
+int rc_to_tags(rc_ctx* ctx, const float* arr, const int* rtag, int N, int negate, float* out, void* stream);
+int rc_from_tags(rc_ctx* ctx, const float* v, const float* pos, int N, float* out, void* stream);
+
 /* ---- differentiation (hot-path step a7) --------------------------------------
  * rc_force_hvp: hv = H v with H = d^2 E / dx dx (FP32, per-particle float4,
  *   w ignored/zero): second derivatives of the pair terms (phi'', phi'/r) and

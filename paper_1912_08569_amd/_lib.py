@@ -137,6 +137,10 @@ _SIGS = {
                        ctypes.POINTER(Integrator), _U64, _I, _VP, _VP], _I),
     "rc_rigid_run": ([_VP, _VP, _VP, _VP, _VP, _VP, _VP, _VP, _I, _I, _VP, _VP, _VP, _VP, _VP, _VP, _VP, _I, Box,
                       ctypes.POINTER(Integrator), _U64, _I, _I, _D, _VP, ctypes.POINTER(_I), _VP], _I),
+    "rc_load_by_tag": ([_VP, _VP, _VP, _VP, _I, Box, _D, _VP], _I),
+    "rc_load_moved": ([_VP, ctypes.POINTER(_I)], _I),
+    "rc_to_tags": ([_VP, _VP, _VP, _I, _I, _VP, _VP], _I),
+    "rc_from_tags": ([_VP, _VP, _VP, _I, _VP, _VP], _I),
     "rc_stress_autocorrelation": ([_VP, _VP, _I, ctypes.c_double, ctypes.c_double, _I, _VP, _VP], _I),
     "rc_param_grad": ([_VP, _VP, _VP, _VP, _I, _I, Box, _VP, _VP], _I),
     "rc_param_vjp": ([_VP, _VP, _VP, _VP, _I, _I, Box, _VP, _VP, _VP], _I),

@@ -22,7 +22,7 @@ __all__ = [
     "rc_compute_forces_noalloc", "rc_thermostat_normals", "rc_workspace_bytes", "rc_set_workspace",
     "rc_ctx_device_bytes", "rc_batch_workspace_bytes", "rc_batch_set_workspace",
     "rc_integrate_step", "rc_step_fused", "rc_bond_count", "rc_md_run", "rc_force_hvp", "rc_force_hvp_batch", "rc_partner_counts", "rc_stress_autocorrelation",
-    "rc_rigid_step", "rc_rigid_run", "rc_param_grad", "rc_clear_status", "rc_read_status", "rc_time_fused_steps",
+    "rc_rigid_step", "rc_rigid_run", "rc_load_by_tag", "rc_load_moved", "rc_to_tags", "rc_from_tags", "rc_param_grad", "rc_clear_status", "rc_read_status", "rc_time_fused_steps",
     "rc_param_vjp", "rc_soft_bonds", "rc_bond_partners", "rc_set_bonds", "rc_fene_forces", "BatchContext", "rc_batch_cells_workspace_bytes", "rc_batch_build_cells", "rc_batch_build_nlist",
     "rc_batch_compute_forces", "rc_batch_bond_count", "rc_batch_step_fused", "rc_batch_run",
     "rc_batch_time_fused_steps", "rc_batch_relayout_lists",
@@ -223,6 +223,41 @@ def rc_rigid_run(ctx: Context, pos, vel, force, image, rtag, nlist, nn, bodies, 
     if code != L.RC_ERR_NONFINITE:
         check(code, ctx.handle)
     return code, done.value
+
+
+def rc_load_by_tag(ctx: Context, pos, xyz, ref, bx, reach, stream=None):
+    """xyz (N, 3) float32 by tag folded into pos (rc_load_moved tells of particles farther than reach from ref)."""
+    N = pos.shape[0]
+    if xyz.shape != (N, 3) or ref.shape != (N, 3) or xyz.dtype != torch.float32 or ref.dtype != torch.float32:
+        raise ValueError("xyz and ref must be (N, 3) float32")
+    check(L.load().rc_load_by_tag(ctx.handle, _ptr(pos), _ptr(xyz), _ptr(ref), N, bx, float(reach), _stream(stream)),
+          ctx.handle)
+
+
+def rc_load_moved(ctx: Context) -> bool:
+    """Whether some particle of the last rc_load_by_tag was farther than its reach from ref (waits for that load)."""
+    moved = ctypes.c_int()
+    check(L.load().rc_load_moved(ctx.handle, ctypes.byref(moved)), ctx.handle)
+    return bool(moved.value)
+
+
+def rc_to_tags(ctx: Context, arr, rtag, negate=False, stream=None) -> torch.Tensor:
+    """(N, 3) by tag from arr (N, 4) float32 in engine order."""
+    N = rtag.shape[0]
+    if arr.shape != (N, 4) or arr.dtype != torch.float32:
+        raise ValueError("arr must be (N, 4) float32")
+    out = torch.empty((N, 3), dtype=torch.float32, device=arr.device)
+    check(L.load().rc_to_tags(ctx.handle, _ptr(arr), _ptr(rtag), N, int(negate), _ptr(out), _stream(stream)), ctx.handle)
+    return out
+
+
+def rc_from_tags(ctx: Context, v, pos, stream=None) -> torch.Tensor:
+    """(N, 4) in engine order (w = 0) from v (N, 3) float32 by tag."""
+    if v.shape != (pos.shape[0], 3) or v.dtype != torch.float32:
+        raise ValueError("v must be (N, 3) float32")
+    out = torch.empty_like(pos)
+    check(L.load().rc_from_tags(ctx.handle, _ptr(v), _ptr(pos), pos.shape[0], _ptr(out), _stream(stream)), ctx.handle)
+    return out
 
 
 def rc_compute_forces(ctx: Context, pos, nlist, nn, bx, force, ev=None, flags=0, status=None, stream=None):

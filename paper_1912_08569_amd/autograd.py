@@ -30,18 +30,16 @@ class SwapModel:
 
     def __init__(self, system):
         self.S = system
-        self.L = torch.tensor(system.edges, dtype=torch.float32, device=system.device)
         self.half_skin = 0.5 * system.ctx.r_buff
         self.base = system.table.copy()
         self._theta = None
         system.build()
-        self._perm = (system.pos[:, 3].view(torch.int32) >> rcl.RC_TYPE_BITS).long()
-        self._ref = self._to_tag(system.pos).to(torch.float32)
+        self._ref = self._to_tag(system.pos)    # positions of the last build, by tag
         self.rebuilds = 0
 
     def positions(self) -> torch.Tensor:
         """Current positions of the system in tag order (N, 3)."""
-        return self._to_tag(self.S.pos).clone()
+        return self._to_tag(self.S.pos)
 
     # ---- parameters ---------------------------------------------------------------------------
     def theta(self) -> torch.Tensor:
@@ -73,45 +71,46 @@ class SwapModel:
         return torch.from_numpy(out)
 
     # ---- positions ----------------------------------------------------------------------------------
-    def _wrap(self, xyz):
-        L = self.L
-        w = xyz - L * torch.floor((xyz + 0.5 * L) / L)
-        return torch.where(w >= 0.5 * L, w - L, w)
+    def _by_tag(self, t: torch.Tensor) -> torch.Tensor:
+        """t as a contiguous (N, 3) float32 tensor."""
+        if t.dim() != 2 or t.shape[0] != self.S.N:
+            raise RuntimeError(f"expected ({self.S.N}, 3) values by tag, not {tuple(t.shape)}")
+        return t.detach().to(torch.float32).expand(self.S.N, 3).contiguous()
 
-    def _load_x(self, xyz: torch.Tensor):
-        x = self._wrap(xyz.detach().to(torch.float32))
+    def _on_list(self, xyz: torch.Tensor, evaluate):
+        """evaluate() on the positions xyz with a list valid for them.
+
+        It is queued behind the load at once, so that the host's wait for the moved flag is over by the
+        time it is done; positions that had moved too far get a list and are evaluated again."""
         S = self.S
-        d = x - self._ref
-        d = d - self.L * torch.round(d / self.L)
-        need = bool((d * d).sum(dim=1).max() > self.half_skin ** 2)
         S.invalidate()   # positions written here, outside the driver
-        S.pos[:, :3] = x[self._perm]
-        if need:
+        api.rc_load_by_tag(S.ctx, S.pos, self._by_tag(xyz), self._ref, S.box, self.half_skin)
+        out = evaluate()
+        if api.rc_load_moved(S.ctx):
             S.build()
-            self._perm = (S.pos[:, 3].view(torch.int32) >> rcl.RC_TYPE_BITS).long()
-            self._ref = x.clone()
+            self._ref = self._to_tag(S.pos)
             self.rebuilds += 1
-        return self._perm
-
-    def _to_tag(self, arr):
-        out = torch.empty((self.S.N, 3), dtype=arr.dtype, device=arr.device)
-        out[self._perm] = arr[:, :3]
+            out = evaluate()
         return out
 
+    def _to_tag(self, arr, negate=False):
+        return api.rc_to_tags(self.S.ctx, arr, self.S.rtag, negate)
+
     def _to_engine(self, a_tag):
-        a = torch.zeros((self.S.N, 4), dtype=torch.float32, device=self.S.device)
-        a[:, :3] = a_tag.detach().to(torch.float32)[self._perm]
-        return a
+        return api.rc_from_tags(self.S.ctx, self._by_tag(a_tag), self.S.pos)
 
     # ---- evaluations (tag order) ---------------------------------------------------------------
     def load(self, xyz, theta):
         self._load_theta(theta)
-        self._load_x(xyz)
+        self._on_list(xyz, lambda: None)
 
-    def forces_energy(self, xyz, theta):
-        self.load(xyz, theta)
-        F, ev = self.S.compute_forces(gather=True)
-        return self._to_tag(F), ev[0].clone()
+    def forces_energy(self, xyz, theta, negate=False):
+        """(forces, energy), or (minus the forces, energy)."""
+        def evaluate():
+            F, ev = self.S.compute_forces(gather=True)
+            return self._to_tag(F, negate), ev[0].clone()
+        self._load_theta(theta)
+        return self._on_list(xyz, evaluate)
 
     def hvp(self, v_tag):
         return self._to_tag(self.S.hvp(self._to_engine(v_tag)))
@@ -122,29 +121,46 @@ class SwapModel:
     def param_vjp(self, a_tag):
         return self._upper(self.S.param_vjp(self._to_engine(a_tag)))
 
+    def energy_theta_grad(self, xyz, theta, gE):
+        """gE dE/dtheta."""
+        self._load_theta(theta)
+        g = self._on_list(xyz, lambda: self.S.param_grad_tensor() * gE.detach())
+        return self._upper(g.cpu().numpy())
+
+    def forces_grads(self, xyz, theta, gF, want_x, want_theta):
+        """gF . dF/dx and gF . dF/dtheta (None where not wanted)."""
+        def evaluate():
+            a = self._to_engine(gF)
+            gx = self._to_tag(self.S.hvp(a), negate=True) if want_x else None
+            return gx, self.S.param_vjp_tensor(a) if want_theta else None
+        self._load_theta(theta)
+        gx, gt = self._on_list(xyz, evaluate)
+        return gx, self._upper(gt.cpu().numpy()) if want_theta else None
+
     def soft_bonds(self, xyz):
-        self._load_x(xyz)
-        val, g = self.S.soft_bonds(grad=True)
-        return val[0].clone(), self._to_tag(g)
+        def evaluate():
+            val, g = self.S.soft_bonds(grad=True)
+            return val[0], self._to_tag(g)
+        val, g = self._on_list(xyz, evaluate)
+        return val.clone(), g
 
 
 class _Energy(torch.autograd.Function):
     @staticmethod
     def forward(ctx, xyz, theta, model):
-        F, E = model.forces_energy(xyz, theta)
+        G, E = model.forces_energy(xyz, theta, negate=True)     # the gradient is minus the forces
         ctx.model = model
-        ctx.save_for_backward(xyz, theta, F)
+        ctx.save_for_backward(xyz, theta, G)
         return E
 
     @staticmethod
     def backward(ctx, gE):
-        xyz, theta, F = ctx.saved_tensors
+        xyz, theta, G = ctx.saved_tensors
         gx = gt = None
         if ctx.needs_input_grad[0]:
-            gx = -F * gE.to(F.dtype)
+            gx = G * gE.to(G.dtype)
         if ctx.needs_input_grad[1]:
-            ctx.model.load(xyz, theta)
-            gt = ctx.model.param_grad() * gE.detach().cpu()
+            gt = ctx.model.energy_theta_grad(xyz, theta, gE)
         return gx, gt, None
 
 
@@ -159,10 +175,7 @@ class _Forces(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gF):
         xyz, theta = ctx.saved_tensors
-        model = ctx.model
-        model.load(xyz, theta)
-        gx = -model.hvp(gF) if ctx.needs_input_grad[0] else None
-        gt = model.param_vjp(gF) if ctx.needs_input_grad[1] else None
+        gx, gt = ctx.model.forces_grads(xyz, theta, gF, ctx.needs_input_grad[0], ctx.needs_input_grad[1])
         return gx, gt, None
 
 

@@ -322,8 +322,8 @@ extern "C" int rc_rigid_run(rc_ctx* c, float* pos, float* vel, float* force, int
     if (r) return r;
     if ((r = check_list(c, nlist, nn, k_max))) return r;
     if (reinterpret_cast<uintptr_t>(pos) & 15) return fail(c, RC_ERR_ARG, "positions not 16-byte aligned");
-    if ((r = ensure_host_words(c))) return r;
-    // every earlier run's launches have ended (each run waits for its own), so the words are free
+    if ((r = ensure_host_words(c)) || (r = wait_event(c))) return r;
+    // every launch that writes the words has ended (a run waits for its own, a load's event was waited for)
     volatile int* host = c->h_status + RC_STATUS_WORDS;
     host[0] = n_steps;
     host[1] = -1;

@@ -173,6 +173,7 @@ constexpr int kHostWords = 8;
 int ensure_host_words(rc_ctx* c);
 // wait for everything queued on the stream so far
 int wait_spin(rc_ctx* c, hipStream_t s);
+int wait_event(rc_ctx* c);   // for what was queued when the wait event was last recorded
 // copy a device status word to the host and wait for it by spinning on an event
 int read_status_spin(rc_ctx* c, const int* d_status, int* hst, hipStream_t s);
 int ensure_blk(rc_ctx* c, int nb, hipStream_t s);

@@ -171,6 +171,10 @@ int ensure_host_words(rc_ctx* c) {
 
 int wait_spin(rc_ctx* c, hipStream_t s) {
     HIP_TRY(c, hipEventRecord(c->ev_sync, s));
+    return wait_event(c);
+}
+
+int wait_event(rc_ctx* c) {
     // a blocking synchronisation costs tens of microseconds of wake-up per call, so this spins on the event
     hipError_t e;
     while ((e = hipEventQuery(c->ev_sync)) == hipErrorNotReady) {

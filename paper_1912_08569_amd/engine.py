@@ -206,28 +206,37 @@ class System:
         api.rc_force_hvp_batch(self.ctx, self.pos, self.nlist, self.nn, self.box, V, out)
         return out
 
-    def param_grad(self) -> np.ndarray:
+    def param_grad_tensor(self) -> torch.Tensor:
+        """dE/d(eps, sigma, lambda) of every entry, (nt, nt, 3) float64 on the device."""
         if not self.built:
             self.build()
         nt = self.ctx.ntypes
-        g = torch.zeros(nt * nt * 3, dtype=torch.float64, device=self.device)
+        g = torch.empty((nt, nt, 3), dtype=torch.float64, device=self.device)
         api.rc_param_grad(self.ctx, self.pos, self.nlist, self.nn, self.box, g)
-        return g.cpu().numpy().reshape(nt, nt, 3)
+        return g
+
+    def param_grad(self) -> np.ndarray:
+        return self.param_grad_tensor().cpu().numpy()
+
+    def param_vjp_tensor(self, adj: torch.Tensor) -> torch.Tensor:
+        """sum_m adj_m . dF_m/dtheta for theta = (eps, sigma, lambda) of every entry, adj (N,4) in engine order;
+        (nt, nt, 3) float64 on the device."""
+        if not self.built:
+            self.build()
+        nt = self.ctx.ntypes
+        g = torch.empty((nt, nt, 3), dtype=torch.float64, device=self.device)
+        api.rc_param_vjp(self.ctx, self.pos, self.nlist, self.nn, self.box, adj.contiguous(), g)
+        return g
 
     def param_vjp(self, adj: torch.Tensor) -> np.ndarray:
-        """sum_m adj_m . dF_m/dtheta for theta = (eps, sigma, lambda) of every entry, adj (N,4) in engine order."""
-        if not self.built:
-            self.build()
-        nt = self.ctx.ntypes
-        g = torch.zeros(nt * nt * 3, dtype=torch.float64, device=self.device)
-        api.rc_param_vjp(self.ctx, self.pos, self.nlist, self.nn, self.box, adj.contiguous(), g)
-        return g.cpu().numpy().reshape(nt, nt, 3)
+        """param_vjp_tensor on the host."""
+        return self.param_vjp_tensor(adj).cpu().numpy()
 
     def soft_bonds(self, grad: bool = False):
         """Soft bond count (float64 device scalar) and, if grad, its gradient (N,4) in engine order."""
         if not self.built:
             self.build()
-        val = torch.zeros(1, dtype=torch.float64, device=self.device)
+        val = torch.empty(1, dtype=torch.float64, device=self.device)
         g = torch.empty_like(self.pos) if grad else None
         api.rc_soft_bonds(self.ctx, self.pos, self.nlist, self.nn, self.box, val, g)
         return val, g

@@ -215,3 +215,87 @@ def test_trajectory_gradient_matches_oracle_finite_differences():
     fd = (oracle_observable(0.8 + h) - oracle_observable(0.8 - h)) / (2 * h)
     assert abs(fd) > 0.0
     assert float(g) == pytest.approx(fd, rel=0.03), (float(g), fd)
+
+
+@pytest.mark.parametrize("N", [63, 257, 3000])
+def test_tag_views_equal_tensor_operations(N):
+    # rc_load_by_tag, rc_to_tags and rc_from_tags against the same operations in torch, bit for bit, with
+    # positions up to several boxes away, on the edges, and (the flag) moved, not moved and not a number
+    from paper_1912_08569_amd import System, api
+    rng = np.random.default_rng(N)
+    L = [6.0, 7.5, 9.25]
+    pos = (rng.uniform(-0.5, 0.5, (N, 3)) * L).astype(np.float32)
+    S = System(pos, np.zeros(N, np.int32), L, W.swap_table_single(lam=1.0), k_max=256)
+    print(f"case: N={N}", flush=True)
+    S.build()
+    tag = (S.pos[:, 3].view(torch.int32) >> 4).long()
+    ref = api.rc_to_tags(S.ctx, S.pos, S.rtag)
+    assert torch.equal(ref[tag], S.pos[:, :3])
+    assert torch.equal(api.rc_to_tags(S.ctx, S.pos, S.rtag, negate=True), -ref)
+    v = torch.from_numpy(rng.standard_normal((N, 3)).astype(np.float32)).cuda()
+    back = api.rc_from_tags(S.ctx, v, S.pos)
+    assert torch.equal(back[:, :3], v[tag]) and bool((back[:, 3] == 0).all())
+    Lt = torch.tensor(L, dtype=torch.float32, device="cuda")
+    x = ref + torch.from_numpy(rng.integers(-3, 4, (N, 3)).astype(np.float32)).cuda() * Lt
+    x[0] = 0.5 * Lt
+    x[1] = -0.5 * Lt
+    w = x - Lt * torch.floor((x + 0.5 * Lt) / Lt)
+    w = torch.where(w >= 0.5 * Lt, w - Lt, w)
+    word = S.pos[:, 3].clone()
+
+    def moved(y, reach):
+        api.rc_load_by_tag(S.ctx, S.pos, y, ref, S.box, reach)
+        return api.rc_load_moved(S.ctx)
+
+    assert moved(x, 100.0) is False
+    assert torch.equal(S.pos[:, :3], w[tag]) and torch.equal(S.pos[:, 3].view(torch.int32), word.view(torch.int32))
+    y = ref.clone()
+    y[N // 2, 1] += 0.2
+    assert moved(y, 0.15) is True
+    assert moved(y, 0.25) is False
+    y[3, 2] = float("nan")
+    assert moved(y, 0.15) is False
+
+
+@pytest.mark.parametrize("nt,N", [(1, 65), (2, 400), (3, 400), (5, 700), (1, 65537)])
+def test_parameter_derivatives_over_type_counts(nt, N):
+    # one walk per four types: one type (wavefront sums), up to four, more than four, and blocks of 256;
+    # an entry with lambda 0 among them.  Bars as in the tests of the two-type mixture.
+    from paper_1912_08569_amd import System
+    rng = np.random.default_rng(100 * nt + N)
+    tab = W.PairTable.empty(nt)
+    for a in range(nt):
+        for b in range(a, nt):
+            if (a + 2 * b) % 5 == 4:
+                tab.set(a, b, W.KIND_WCA, 1.0, 0.9, 6)
+            else:
+                tab.set(a, b, W.KIND_SWAP, 1.0 + 0.2 * a + 0.1 * b, 0.9 + 0.02 * (a + b), 8 + (a + b) % 3, 1.4,
+                        0.0 if (a, b) == (1, 1) else 0.5 + 0.3 * a)
+    Lf = float(np.float32((N / 0.3) ** (1.0 / 3.0)))
+    side = int(np.ceil(N ** (1.0 / 3.0)))
+    h = Lf / side
+    at = rng.permutation(side ** 3)[:N]
+    pos = ((np.stack([at % side, at // side % side, at // side ** 2], axis=1) + 0.5) * h - 0.5 * Lf
+           + rng.uniform(-0.5, 0.5, (N, 3)) * max(h - 0.95, 0.1)).astype(np.float32)
+    types = rng.integers(0, nt, N).astype(np.int32)
+    print(f"case: nt={nt} N={N}", flush=True)
+    S = System(pos, types, Lf, tab, k_max=64)
+    S.build()
+    xyz, _, _, ty = S.state_by_tag()
+    a = rng.standard_normal((N, 3)).astype(np.float32)
+    a4 = np.zeros((N, 4), np.float32)
+    a4[:, :3] = a
+    g, v = S.param_grad(), S.param_vjp(S.to_engine_order(a4))
+    iu = np.triu_indices(nt)
+    ref = adjoint_ref.param_grad(xyz.astype(np.float64), ty, Lf, tab)
+    for w in range(3):
+        assert np.abs(g[..., w][iu] - ref[..., w][iu]).max() <= 1e-5 * np.abs(ref).max()
+        assert np.array_equal(g[..., w], g[..., w].T)
+    if N <= 1000:
+        ref = adjoint_ref.force_param_vjp(xyz.astype(np.float64), ty, Lf, tab, a.astype(np.float64))
+        sc = vjp_scale(swap_ref.evaluate(xyz.astype(np.float64), ty, Lf, tab)["A_F"], a4, tab)
+        for w in range(3):
+            d = np.abs(v[..., w][iu] - ref[..., w][iu])
+            act = sc[..., w][iu] > 0
+            assert np.all(d[act] <= 1e-5 * sc[..., w][iu][act])
+            assert np.all(d[~act & (tab.kind[iu] != W.KIND_SWAP)] == 0.0)
