@@ -249,6 +249,14 @@ int rc_build_nlist(rc_ctx* ctx, const float* pos, float* vel /* NULL ok */, int 
                    const void* ws, size_t ws_bytes, int k_max, int* nlist /* [k_max*N] */,
                    int* nn /* [N] */, int* status /* [RC_STATUS_WORDS] | NULL */, void* stream);
 
+/* rc_build_list: rc_build_cells, rc_clear_status (if status is not NULL) and
+ * rc_build_nlist in one call, with fewer launches (the list kernel copies the
+ * sorted state back).  Same results; nothing is changed when an argument is
+ * refused.                                                                    */
+int rc_build_list(rc_ctx* ctx, float* pos, float* vel /* NULL ok */, int* image /* NULL ok */, int* rtag /* NULL ok */,
+                  int N, rc_box box, void* ws, size_t ws_bytes, int k_max, int* nlist, int* nn,
+                  int* status /* NULL ok */, void* stream);
+
 /* ---- forces, energy, virial (hot-path step a3) -------------------------------
  * F = -grad(E2 + E3) of the pair terms (eq. 2b / WCA) and the three-body term
  * (eq. 3bp with eq. pot), one term per centre i and unordered partner pair

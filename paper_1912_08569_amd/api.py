@@ -18,7 +18,7 @@ from ._lib import RcError, check
 
 __all__ = [
     "Context", "RcError", "box", "integrator", "pack_positions", "unpack_positions",
-    "rc_cells_workspace_bytes", "rc_build_cells", "rc_build_nlist", "rc_compute_forces",
+    "rc_cells_workspace_bytes", "rc_build_cells", "rc_build_nlist", "rc_build_list", "rc_compute_forces",
     "rc_compute_forces_noalloc", "rc_thermostat_normals", "rc_workspace_bytes", "rc_set_workspace",
     "rc_ctx_device_bytes", "rc_batch_workspace_bytes", "rc_batch_set_workspace",
     "rc_integrate_step", "rc_step_fused", "rc_bond_count", "rc_md_run", "rc_force_hvp", "rc_force_hvp_batch", "rc_partner_counts", "rc_stress_autocorrelation",
@@ -192,6 +192,13 @@ def rc_build_nlist(ctx: Context, pos, vel, bx, ws, k_max, nlist, nn, status=None
     check(L.load().rc_build_nlist(ctx.handle, _ptr(pos), _ptr(vel), N, bx, _ptr(ws),
                                   ws.numel() * ws.element_size(), int(k_max), _ptr(nlist), _ptr(nn),
                                   _ptr(status), _stream(stream)), ctx.handle)
+
+
+def rc_build_list(ctx: Context, pos, vel, image, rtag, bx, ws, k_max, nlist, nn, status=None, stream=None):
+    """rc_build_cells, rc_clear_status and rc_build_nlist in one call."""
+    check(L.load().rc_build_list(ctx.handle, _ptr(pos), _ptr(vel), _ptr(image), _ptr(rtag), pos.shape[0], bx, _ptr(ws),
+                                 ws.numel() * ws.element_size(), int(k_max), _ptr(nlist), _ptr(nn), _ptr(status),
+                                 _stream(stream)), ctx.handle)
 
 
 def _kmax(nlist, N):

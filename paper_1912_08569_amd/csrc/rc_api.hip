@@ -329,8 +329,9 @@ int rc_cells_workspace_bytes(const rc_ctx* cc, int N, rc_box box, size_t* bytes)
     return RC_OK;
 }
 
-int rc_build_cells(rc_ctx* c, float* pos, float* vel, int* image, int* rtag, int N, rc_box box, void* ws,
-                   size_t ws_bytes, void* stream) {
+// The cell sort, and with list_follows what build_nlist of the same call relies on.
+static int build_cells(rc_ctx* c, float* pos, float* vel, int* image, int* rtag, int N, rc_box box, void* ws,
+                       size_t ws_bytes, bool list_follows, int* status, int status_mode, void* stream) {
     if (c) c->md.valid = false;   // the state or the list changes outside the driver
     int r = check_common(c, N, pos);
     if (r) return r;
@@ -357,13 +358,23 @@ int rc_build_cells(rc_ctx* c, float* pos, float* vel, int* image, int* rtag, int
     a.tpos = reinterpret_cast<float4*>(w + l.tpos);
     a.tvel = reinterpret_cast<float4*>(w + l.tvel);
     a.timage = reinterpret_cast<int4*>(w + l.timage);
+    a.list_follows = list_follows;
+    a.status = status;
+    a.status_mode = status_mode;
     HIP_TRY(c, launch_cells(a, S(stream)));
     return RC_OK;
 }
 
-// fresh: the status words are written whole (the driver's rebuilds), else folded into
+int rc_build_cells(rc_ctx* c, float* pos, float* vel, int* image, int* rtag, int N, rc_box box, void* ws,
+                   size_t ws_bytes, void* stream) {
+    return build_cells(c, pos, vel, image, rtag, N, box, ws, ws_bytes, false, nullptr, kStatusFold, stream);
+}
+
+// back: the state is written there from the workspace's temporaries, which build_cells with list_follows left
+// and which the list is built from (pos and vel are then not read)
 static int build_nlist(rc_ctx* c, const float* pos, float* vel, int N, rc_box box, const void* ws, size_t ws_bytes,
-                       int k_max, int* nlist, int* nn, int* status, bool fresh, void* stream) {
+                       int k_max, int* nlist, int* nn, int* status, int status_mode, const StateBack& back,
+                       void* stream) {
     if (c) c->md.valid = false;   // the state or the list changes outside the driver
     int r = check_common(c, N, pos);
     if (r) return r;
@@ -374,20 +385,24 @@ static int build_nlist(rc_ctx* c, const float* pos, float* vel, int N, rc_box bo
     if ((r = make_box(c, box, b)) || (r = make_grid(c, c->rlist_max, b, g))) return r;
     const CellsLayout l = cells_layout(N, g.nkeys);
     if (!ws || ws_bytes < l.total) return fail(c, RC_ERR_WORKSPACE, "cells workspace needs %zu bytes", l.total);
+    const char* w = static_cast<const char*>(ws);
     NlistArgs a{};
-    a.pos = reinterpret_cast<const float4*>(pos);
+    a.pos = reinterpret_cast<const float4*>(back.pos ? w + l.tpos : reinterpret_cast<const char*>(pos));
     a.vel = reinterpret_cast<float4*>(vel);
     a.N = N;
     a.box = b;
     a.g = g;
-    a.cell_start = reinterpret_cast<const int*>(static_cast<const char*>(ws) + l.start);
+    a.cell_start = reinterpret_cast<const int*>(w + l.start);
     a.tab = dev_table(c);
     a.k_max = k_max;
     a.nlist = nlist;
     a.nn = nn;
     a.status = status;
-    a.fresh_status = fresh ? 1 : 0;
-    a.block_max = reinterpret_cast<int*>(static_cast<char*>(const_cast<void*>(ws)) + l.bmax);
+    a.status_mode = status_mode;
+    a.per_block = reinterpret_cast<int2*>(const_cast<char*>(w) + l.bmax);
+    a.back = back;
+    a.back.tvel = reinterpret_cast<const float4*>(w + l.tvel);
+    a.back.timage = reinterpret_cast<const int4*>(w + l.timage);
     if ((r = ensure_plist(c, N, k_max))) return r;
     a.pl_j = c->d_pl_j;  // the packed copy the fused step reads, made in the same launch
     a.pl_o = c->d_pl_o;
@@ -401,7 +416,28 @@ static int build_nlist(rc_ctx* c, const float* pos, float* vel, int N, rc_box bo
 
 int rc_build_nlist(rc_ctx* c, const float* pos, float* vel, int N, rc_box box, const void* ws, size_t ws_bytes,
                    int k_max, int* nlist, int* nn, int* status, void* stream) {
-    return build_nlist(c, pos, vel, N, box, ws, ws_bytes, k_max, nlist, nn, status, false, stream);
+    return build_nlist(c, pos, vel, N, box, ws, ws_bytes, k_max, nlist, nn, status, kStatusFold, StateBack{}, stream);
+}
+
+// cell sort and list in one call
+static int build_all(rc_ctx* c, float* pos, float* vel, int* image, int* rtag, int N, rc_box box, void* ws,
+                     size_t ws_bytes, int k_max, int* nlist, int* nn, int* status, int status_mode, void* stream) {
+    // what the list build refuses is refused before the sort leaves the state in the temporaries
+    if (!c) return RC_ERR_ARG;
+    int r = check_common(c, N, pos);
+    if (r) return r;
+    if ((r = check_list(c, nlist, nn, k_max)) || (r = ensure_plist(c, N, k_max))) return r;
+    if ((r = build_cells(c, pos, vel, image, rtag, N, box, ws, ws_bytes, true, status, status_mode, stream))) return r;
+    StateBack back{};
+    back.pos = reinterpret_cast<float4*>(pos);
+    back.vel = reinterpret_cast<float4*>(vel);
+    back.image = reinterpret_cast<int4*>(image);
+    return build_nlist(c, pos, vel, N, box, ws, ws_bytes, k_max, nlist, nn, status, status_mode, back, stream);
+}
+
+int rc_build_list(rc_ctx* c, float* pos, float* vel, int* image, int* rtag, int N, rc_box box, void* ws,
+                  size_t ws_bytes, int k_max, int* nlist, int* nn, int* status, void* stream) {
+    return build_all(c, pos, vel, image, rtag, N, box, ws, ws_bytes, k_max, nlist, nn, status, kStatusClear, stream);
 }
 
 int rc_compute_forces(rc_ctx* c, const float* pos, const int* nlist, const int* nn, int k_max, int N, rc_box box,
@@ -767,11 +803,9 @@ struct PlainOps final : DriveOps {
     // The cell sort and the list build of one rebuild, on stream st (direct, or being recorded)
     static int rebuild_launches(void* self, hipStream_t st) {
         PlainOps* o = static_cast<PlainOps*>(self);
-        int rr = rc_build_cells(o->c, o->rb_pos, o->buf->vel, o->buf->image, o->buf->rtag, o->N, o->box,
-                                o->buf->cells_ws, o->buf->cells_ws_bytes, st);
-        if (rr) return rr;
-        return build_nlist(o->c, o->rb_pos, o->buf->vel, o->N, o->box, o->buf->cells_ws, o->buf->cells_ws_bytes,
-                           o->buf->k_max, o->buf->nlist, o->buf->nn, o->buf->status, true, st);
+        return build_all(o->c, o->rb_pos, o->buf->vel, o->buf->image, o->buf->rtag, o->N, o->box, o->buf->cells_ws,
+                         o->buf->cells_ws_bytes, o->buf->k_max, o->buf->nlist, o->buf->nn, o->buf->status, kStatusFresh,
+                         st);
     }
     // Every rebuild of a run takes the same launches with the same arguments (for its position buffer),
     // so from the second one on they are replayed as one graph: the host no longer issues a dozen
@@ -841,8 +875,8 @@ struct PlainOps final : DriveOps {
     }
     StepKernel plain_step() override { return step_kernel(false, false, c->gather_width, c->step_form, N, list_est(c, N, b)); }
     bool block_ok() override { return step_block_fits(N, c->nt, c->step_form, list_est(c, N, b)); }
-    // the cell sort permutes pos, vel and image through the workspace's
-    // temporaries and copies them back, so those hold the rebuilt state
+    // the cell sort permutes pos, vel and image into the workspace's temporaries,
+    // from where they are copied back, so those hold the rebuilt state
     bool rebuild_snapshot(const float4** p, const float4** v, const int4** im) override {
         Grid g;
         if (make_grid(c, c->rlist_max, b, g)) return false;

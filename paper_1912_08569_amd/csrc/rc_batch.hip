@@ -23,7 +23,6 @@ struct rc_batch {
     bool seeds_set = false;
     RepDesc* d_desc = nullptr;
     int* d_chunk_rep = nullptr;
-    uint32_t* d_key_end = nullptr;
     uint64_t* d_seeds = nullptr;
     // per-replica rebuilds: the fold of every chunk writes, per replica, whether a block crossed the
     // rebuild threshold and the largest path length (d_rep: [2][R] ints), which every status read
@@ -51,7 +50,6 @@ void free_batch(rc_batch* b) {
         if (b->h_build[q]) (void)hipHostFree(b->h_build[q]);
     if (b->d_desc) (void)hipFree(b->d_desc);
     if (b->d_chunk_rep) (void)hipFree(b->d_chunk_rep);
-    if (b->d_key_end) (void)hipFree(b->d_key_end);
     if (b->d_seeds) (void)hipFree(b->d_seeds);
     delete b;
 }
@@ -177,10 +175,8 @@ int rc_batch_create(rc_batch** out, int R, int ntypes, const rc_pair_coeff* tabl
     b->nkeys = (uint32_t)keys;
     c->rlist_max = rmax_all;
     std::vector<int> chunk_rep(slots / kWave);
-    std::vector<uint32_t> key_end(R);
     for (int r = 0; r < R; ++r) {
         for (int q = b->offsets[r] / kWave; q < b->offsets[r + 1] / kWave; ++q) chunk_rep[q] = r;
-        key_end[r] = b->desc[r].key_base + b->desc[r].grid.nkeys;
     }
     b->seeds.assign(R, 0);
     bool ok = hipGetDevice(&c->device) == hipSuccess &&
@@ -193,8 +189,6 @@ int rc_batch_create(rc_batch** out, int R, int ntypes, const rc_pair_coeff* tabl
               hipMalloc(&b->d_chunk_rep, sizeof(int) * chunk_rep.size()) == hipSuccess &&
               hipMemcpy(b->d_chunk_rep, chunk_rep.data(), sizeof(int) * chunk_rep.size(), hipMemcpyHostToDevice) ==
                   hipSuccess &&
-              hipMalloc(&b->d_key_end, sizeof(uint32_t) * R) == hipSuccess &&
-              hipMemcpy(b->d_key_end, key_end.data(), sizeof(uint32_t) * R, hipMemcpyHostToDevice) == hipSuccess &&
               hipMalloc(&b->d_seeds, sizeof(uint64_t) * R) == hipSuccess &&
               hipMemcpy(b->d_seeds, b->seeds.data(), sizeof(uint64_t) * R, hipMemcpyHostToDevice) == hipSuccess &&
               hipMalloc(&b->d_rep, sizeof(int) * 2 * (size_t)R) == hipSuccess &&
@@ -271,7 +265,7 @@ int rc_batch_cells_workspace_bytes(const rc_batch* b, size_t* bytes) {
 }
 
 static int batch_build_cells(rc_batch* b, float* pos, float* vel, int* image, int* rtag, void* ws, size_t ws_bytes,
-                             const int* build, void* stream) {
+                             const int* build, bool list_follows, int* status, int status_mode, void* stream) {
     int r = check_pos(b, pos);
     if (r) return r;
     const CellsLayout l = cells_layout(b->n_slots, b->nkeys);
@@ -285,8 +279,6 @@ static int batch_build_cells(rc_batch* b, float* pos, float* vel, int* image, in
     a.N = b->n_slots;
     a.rep = b->d_desc;
     a.chunk_rep = b->d_chunk_rep;
-    a.key_end = b->d_key_end;
-    a.R = b->R;
     a.nkeys = b->nkeys;
     a.counts = reinterpret_cast<int*>(w + l.counts);
     a.cell_start = reinterpret_cast<int*>(w + l.start);
@@ -298,6 +290,9 @@ static int batch_build_cells(rc_batch* b, float* pos, float* vel, int* image, in
     a.tvel = reinterpret_cast<float4*>(w + l.tvel);
     a.timage = reinterpret_cast<int4*>(w + l.timage);
     a.build = build;
+    a.list_follows = list_follows;
+    a.status = status;
+    a.status_mode = status_mode;
     HIP_TRY(&b->c, launch_cells_batch(a, S(stream)));
     return RC_OK;
 }
@@ -306,12 +301,13 @@ int rc_batch_build_cells(rc_batch* b, float* pos, float* vel, int* image, int* r
                          void* stream) {
     if (b) b->c.md.valid = false;   // the state or the list changes outside the driver
     if (!b) return RC_ERR_ARG;
-    return batch_build_cells(b, pos, vel, image, rtag, ws, ws_bytes, nullptr, stream);
+    return batch_build_cells(b, pos, vel, image, rtag, ws, ws_bytes, nullptr, false, nullptr, kStatusFold, stream);
 }
 
-// fresh: the status words are written whole (the driver's rebuilds), else folded into
+// back: the state is written there from the workspace's temporaries (as for one system)
 static int batch_build_nlist(rc_batch* b, const float* pos, float* vel, const void* ws, size_t ws_bytes, int k_max,
-                             int* nlist, int* nn, int* status, bool fresh, const int* build, void* stream) {
+                             int* nlist, int* nn, int* status, int status_mode, const int* build, const StateBack& back,
+                             void* stream) {
     if (!b) return RC_ERR_ARG;
     int r = check_pos(b, pos);
     if (r) return r;
@@ -319,20 +315,24 @@ static int batch_build_nlist(rc_batch* b, const float* pos, float* vel, const vo
     const CellsLayout l = cells_layout(b->n_slots, b->nkeys);
     if (!ws || ws_bytes < l.total) return fail(&b->c, RC_ERR_WORKSPACE, "cells workspace needs %zu bytes", l.total);
     NlistArgsB a{};
-    a.pos = reinterpret_cast<const float4*>(pos);
+    const char* w = static_cast<const char*>(ws);
+    a.pos = reinterpret_cast<const float4*>(back.pos ? w + l.tpos : reinterpret_cast<const char*>(pos));
     a.vel = reinterpret_cast<float4*>(vel);
     a.N = b->n_slots;
     a.rep = b->d_desc;
     a.chunk_rep = b->d_chunk_rep;
     a.tab = all_tables(b);
-    a.cell_start = reinterpret_cast<const int*>(static_cast<const char*>(ws) + l.start);
+    a.cell_start = reinterpret_cast<const int*>(w + l.start);
     a.k_max = k_max;
     a.nlist = nlist;
     a.nn = nn;
     a.status = status;
-    a.fresh_status = fresh ? 1 : 0;
+    a.status_mode = status_mode;
     a.build = build;
-    a.block_max = reinterpret_cast<int*>(static_cast<char*>(const_cast<void*>(ws)) + l.bmax);
+    a.per_block = reinterpret_cast<int2*>(const_cast<char*>(w) + l.bmax);
+    a.back = back;
+    a.back.tvel = reinterpret_cast<const float4*>(w + l.tvel);
+    a.back.timage = reinterpret_cast<const int4*>(w + l.timage);
     rc_ctx* c = &b->c;
     if ((r = ensure_plist(c, b->n_slots, k_max))) return r;
     a.pl_j = c->d_pl_j;  // the packed copy the fused step reads, made in the same launch
@@ -348,7 +348,8 @@ static int batch_build_nlist(rc_batch* b, const float* pos, float* vel, const vo
 int rc_batch_build_nlist(rc_batch* b, const float* pos, float* vel, const void* ws, size_t ws_bytes, int k_max,
                          int* nlist, int* nn, int* status, void* stream) {
     if (b) b->c.md.valid = false;   // the state or the list changes outside the driver
-    return batch_build_nlist(b, pos, vel, ws, ws_bytes, k_max, nlist, nn, status, false, nullptr, stream);
+    return batch_build_nlist(b, pos, vel, ws, ws_bytes, k_max, nlist, nn, status, kStatusFold, nullptr, StateBack{},
+                             stream);
 }
 
 int rc_batch_set_rebuild_margin(rc_batch* b, double margin) {
@@ -542,11 +543,17 @@ struct BatchOps final : DriveOps {
         *kept_path = kp;
         *rebuilt = nre;
         HIP_TRY(&b->c, hipMemcpyAsync(b->d_build, set, sizeof(int) * (size_t)R, hipMemcpyHostToDevice, s));
-        int rr = batch_build_cells(b, pos, buf->vel, buf->image, buf->rtag, buf->cells_ws, buf->cells_ws_bytes,
-                                   b->d_build, s);
+        int rr = ensure_plist(&b->c, b->n_slots, buf->k_max);   // refused before the state is in the temporaries
         if (rr) return rr;
-        return batch_build_nlist(b, pos, buf->vel, buf->cells_ws, buf->cells_ws_bytes, buf->k_max, buf->nlist,
-                                 buf->nn, buf->status, true, b->d_build, s);
+        rr = batch_build_cells(b, pos, buf->vel, buf->image, buf->rtag, buf->cells_ws, buf->cells_ws_bytes, b->d_build,
+                               true, buf->status, kStatusFresh, s);
+        if (rr) return rr;
+        StateBack back{};
+        back.pos = reinterpret_cast<float4*>(pos);
+        back.vel = reinterpret_cast<float4*>(buf->vel);
+        back.image = reinterpret_cast<int4*>(buf->image);
+        return batch_build_nlist(b, pos, buf->vel, buf->cells_ws, buf->cells_ws_bytes, buf->k_max, buf->nlist, buf->nn,
+                                 buf->status, kStatusFresh, b->d_build, back, s);
     }
     hipError_t fold(int* blk, int nb, const float4* vel, int N, int* status, hipStream_t st) override {
         if (vel) {

@@ -71,7 +71,7 @@ CellsLayout cells_layout(int N, uint32_t nkeys) {
     l.rank = o; o = al(o + 4 * (size_t)N);
     l.order = o; o = al(o + 4 * (size_t)N);
     l.bsums = o; o = al(o + 4 * (nk / kScanTile + 2));
-    l.bmax = o; o = al(o + 8 * ((size_t)N / kBlock + 2));   // per block: largest list, then swap-range sums
+    l.bmax = o; o = al(o + 8 * ((size_t)N / kWave + 2));   // per block: largest list and swap-range sum
     l.tpos = o; o = al(o + 16 * (size_t)N);
     l.tvel = o; o = al(o + 16 * (size_t)N);
     l.timage = o; o = al(o + 16 * (size_t)N);

@@ -327,10 +327,19 @@ __device__ __forceinline__ void pack_wave_lists(int i, bool live, int packed, co
     const int cnt = live ? ns + min(nn_other(packed), k_max - ns) : 0;
     const int off = wave_inclusive_scan(cnt) - cnt;
     const size_t base = (size_t)(i - lane) * k_max + off;
-    for (int s = 0; s < cnt; ++s) {
-        const int slot = s < ns ? s : k_max - 1 - (s - ns);
-        pl_j[base + s] = nlist[(size_t)slot * N + i];
-        pl_o[base + s] = (unsigned char)lane;
+    for (int b = 0; b < cnt; b += 4) {   // four reads under way
+        int j[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = b + u;
+            j[u] = s < cnt ? nlist[(size_t)(s < ns ? s : k_max - 1 - (s - ns)) * N + i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (b + u < cnt) {
+                pl_j[base + b + u] = j[u];
+                pl_o[base + b + u] = (unsigned char)lane;
+            }
     }
 }
 
@@ -529,6 +538,18 @@ hipError_t launch_integrate(const IntegrateArgs& a, hipStream_t s);
 hipError_t launch_thermostat_normals(uint64_t seed, uint64_t step0, int steps, int N, float noise_z, float4* out,
                                      hipStream_t s);
 
+// What a list build does with the status words before it sets its own (KMAX, overflow flag, NSWAP): folds into
+// them, clears them all and the chunk markers as a chunk reset would (the driver's rebuilds), or clears them all.
+enum StatusMode { kStatusFold = 0, kStatusFresh = 1, kStatusClear = 2 };
+// where a list build writes back the state it reads from the cell sort's temporaries (pos NULL: nowhere)
+struct StateBack {
+    float4* pos;
+    float4* vel;            // NULL ok, as image
+    int4* image;
+    const float4* tvel;
+    const int4* timage;
+};
+
 struct CellsArgs {
     float4* pos;
     float4* vel;
@@ -547,6 +568,11 @@ struct CellsArgs {
     float4* tpos;
     float4* tvel;
     int4* timage;
+    // the list build of the same call follows: the sorted state is left in the temporaries (it writes it
+    // back), and status (NULL ok) is begun in status_mode
+    bool list_follows;
+    int* status;
+    int status_mode;
 };
 hipError_t launch_cells(const CellsArgs& a, hipStream_t s);
 
@@ -562,10 +588,11 @@ struct NlistArgs {
     int* nlist;
     int* nn;
     int* status;
-    int* block_max;    // [ceil(N / kBlock)] scratch (largest list length per block)
     int* pl_j;         // packed copy of the list (NULL: none), see pack_wave_lists
     unsigned char* pl_o;
-    int fresh_status;  // 1: write every status word (see k_nlist_status); 0: fold into them
+    int status_mode;
+    int2* per_block;   // [ceil(N / 64)] scratch: largest list and swap entries of each block
+    StateBack back;    // with back.pos, pos is the cell sort's copy and the status words are begun
 };
 hipError_t launch_nlist(const NlistArgs& a, hipStream_t s);
 // the packed copy of a list built elsewhere
@@ -663,8 +690,6 @@ struct CellsArgsB {
     int N;                  // slots
     const RepDesc* rep;
     const int* chunk_rep;
-    const uint32_t* key_end;  // [R] key_base + nkeys of each replica (ascending)
-    int R;
     uint32_t nkeys;         // whole batch
     int* counts;
     int* cell_start;
@@ -676,6 +701,9 @@ struct CellsArgsB {
     float4* tvel;
     int4* timage;
     const int* build;       // [R] nonzero: the replica is re-ordered (NULL: every replica)
+    bool list_follows;      // as in CellsArgs
+    int* status;
+    int status_mode;
 };
 hipError_t launch_cells_batch(const CellsArgsB& a, hipStream_t s);
 
@@ -691,10 +719,11 @@ struct NlistArgsB {
     int* nlist;
     int* nn;
     int* status;
-    int* block_max;
     int* pl_j;              // packed copy of the list (NULL: none), see pack_wave_lists
     unsigned char* pl_o;
-    int fresh_status;       // as in NlistArgs
+    int status_mode;        // as in NlistArgs, as the next two
+    int2* per_block;
+    StateBack back;
     const int* build;       // [R] nonzero: the replica's list is rebuilt (NULL: every replica)
 };
 hipError_t launch_nlist_batch(const NlistArgsB& a, hipStream_t s);

@@ -118,10 +118,8 @@ class System:
     def build(self):
         """Bin, re-order and build the neighbour list (grows k_max on overflow)."""
         for _ in range(4):
-            api.rc_build_cells(self.ctx, self.pos, self.vel, self.image, self.rtag, self.box, self.ws)
-            api.rc_clear_status(self.status)
-            api.rc_build_nlist(self.ctx, self.pos, self.vel, self.box, self.ws, self.k_max, self.nlist,
-                               self.nn, self.status)
+            api.rc_build_list(self.ctx, self.pos, self.vel, self.image, self.rtag, self.box, self.ws, self.k_max,
+                              self.nlist, self.nn, self.status)
             code, st = api.rc_read_status(self.status)
             if code == rcl.RC_ERR_NLIST_OVERFLOW:
                 self._grow(st[rcl.RC_ST_KMAX])

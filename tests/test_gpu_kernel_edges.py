@@ -101,3 +101,63 @@ def test_few_particles_per_wavefront_equal_64(name, form):
         out.append((S.pos.clone(), S.vel.clone(), S.image.clone()))
     for other in out[1:]:
         assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(out[0], other))
+
+
+@pytest.mark.parametrize("N,cells", [(1, 3), (63, 3), (64, 4), (65, 3), (700, 5), (72000, 17), (72001, 16), (72003, 17)])
+def test_list_holds_every_pair_once(N, cells):
+    # the list of both kernels (few particles per wavefront up to 72000) against a k-d tree: odd and even
+    # numbers of cells (an even last cell's right neighbour wraps), three cells an edge, partly filled blocks,
+    # empty and crowded cells; the state and rtag it leaves, and a second build of the same state
+    from scipy.spatial import cKDTree
+    from paper_1912_08569_amd import System
+    rng = np.random.default_rng(N)
+    t = W.PairTable.empty(2)
+    t.set(0, 0, W.KIND_SWAP, 1.0, 1.0, 10, 1.5, 1.0)
+    t.set(0, 1, W.KIND_WCA, 1.0, 0.9, 6)
+    L = [float(np.float32(1.8 * 1.01 * c)) for c in (cells, cells + 1, cells)]
+    pos = (rng.uniform(-0.5, 0.5, (N, 3)) * L).astype(np.float32)
+    pos[: N // 10] = (0.3 * pos[: N // 10]).astype(np.float32)
+    types = (rng.random(N) < 0.3).astype(np.int32)
+    print(f"case: N={N} cells={cells}", flush=True)
+    S = System(pos, types, L, t, vel=rng.standard_normal((N, 3)).astype(np.float32), k_max=500)
+    v0 = S.vel[:, :3].cpu().numpy().copy()
+    S.build()
+    x, _, tags = S.pos[:, :3].cpu().numpy(), None, (S.pos[:, 3].view(torch.int32) >> 4).cpu().numpy()
+    assert np.array_equal(x, pos[tags]) and np.array_equal(S.vel[:, :3].cpu().numpy(), v0[tags])
+    assert np.array_equal(S.rtag.cpu().numpy()[tags], np.arange(N)) and bool((S.vel[:, 3] == 0).all())
+    nn = S.nn.cpu().numpy()
+    ns, no = nn & 0xFFFF, nn >> 16
+    nl = S.nlist.cpu().numpy().reshape(-1, N)
+    ty = types[tags]
+    edge = np.array(L)
+    tree = cKDTree(np.mod(x.astype(np.float64) + 0.5 * edge, edge), boxsize=edge)
+    r_wca = 0.9 * 2.0 ** (1.0 / 6.0) + 0.3
+    P = tree.query_pairs(1.8, output_type="ndarray")
+    d = x[P[:, 1]].astype(np.float64) - x[P[:, 0]]
+    d -= edge * np.round(d / edge)
+    r = np.sqrt((d * d).sum(axis=1))
+    kind = ty[P[:, 0]] + ty[P[:, 1]]               # 0 swap, 1 WCA, 2 none
+    lim = np.where(kind == 0, 1.8, np.where(kind == 1, r_wca, 0.0))
+    sure = P[(r < lim) & (kind < 2)]
+    key = lambda a, b: a.astype(np.int64) * N + b  # noqa: E731
+    want = np.concatenate([key(sure[:, 0], sure[:, 1]), key(sure[:, 1], sure[:, 0])])
+    k = np.arange(nl.shape[0])[:, None]
+    swap, other = k < ns[None], k >= nl.shape[0] - no[None]
+    got = []
+    for mask, is_swap in ((swap, True), (other, False)):
+        s, i = np.nonzero(mask)
+        j = nl[s, i]
+        assert np.array_equal((ty[i] == 0) & (ty[j] == 0), np.full(len(i), is_swap))
+        got.append(key(i, j))
+    got = np.concatenate(got)
+    assert len(np.unique(got)) == len(got)
+    assert np.isin(want, got).all()
+    extra = got[~np.isin(got, want)]               # the radius carries a 1e-5 margin
+    i, j = extra // N, extra % N
+    d = x[j].astype(np.float64) - x[i]
+    d -= edge * np.round(d / edge)
+    lim = np.where(ty[i] + ty[j] == 0, 1.8, r_wca) * (1.0 + 2e-5)
+    assert np.all((ty[i] + ty[j] < 2) & (np.sqrt((d * d).sum(axis=1)) <= lim))
+    first = (S.pos.clone(), S.nn.clone(), S.nlist.clone())
+    S.build()
+    assert all(torch.equal(a, b) for a, b in zip(first, (S.pos, S.nn, S.nlist)))
