@@ -599,6 +599,182 @@ __global__ __launch_bounds__(kWave) void k_step_few(StepArgs a) {
     if (a.reset_status && blockIdx.x == 0 && threadIdx.x == 0) chunk_reset(a.reset_status, a.reset_base, a.reset_to);
 }
 
+// k_step_few of the two-pass form in one launch: a wavefront adds up the sums S
+// of its own particles from its entries, keeps a row of entries in registers,
+// and takes the sum of a partner outside the wavefront from a walk of the
+// partner's swap range (the same terms in the same order, so the same bits as
+// the launch that computed every S).  Only entries between r_min and r_cut need
+// their partner's sum, half of the bonded ones of stiff dumbbells: the walk costs
+// less than the first launch's own time while lists are short (fused_sums).
+// Bound by one wavefront's instructions and reads.  Records of the entries with
+// fixed places and the partners' own partners, which take three dependent reads
+// out, gained 0.3 us; 32 particles per wavefront lost once the mixture had
+// aggregated (20011 dumbbells: 13.1 us), as some then hold two rows.
+constexpr int kFusedOwn = 16;
+__global__ __launch_bounds__(kWave) void k_step_fused(StepArgs a) {
+    constexpr int OW = kFusedOwn;
+    extern __shared__ DevEntry s_tab[];
+    __shared__ float4 s_pos[OW];
+    __shared__ float s_S[OW];
+    __shared__ float s_w[2][kWave], s_c[3][kWave];
+    const int nt = a.tab.nt, lane = threadIdx.x;
+    const int ngr = (a.N + OW - 1) / OW;   // the grid
+    const int per = ngr / 8, bx = blockIdx.x;
+    const int gr = bx < per * 8 ? (bx & 7) * per + (bx >> 3) : bx;
+    constexpr int G = kWave / OW;
+    const int blk = gr / G, h = gr % G;    // the 64-particle block of the packed list and the group in it
+    const int base_m = gr * OW, m = base_m + lane;
+    const bool live = lane < OW && m < a.N;
+    const int mc = min(base_m + min(lane, OW - 1), a.N - 1);
+    const int m64 = blk * kWave + lane;
+    const float4 pm0 = a.pos_in[mc];
+    const float4 vm0 = a.vel[mc];
+    const int nn64 = a.nn[min(m64, a.N - 1)];
+    const uint64_t step = a.step + (a.step_base ? *a.step_base : 0ull);
+    load_table(s_tab, a.tab);
+    const float4 pm = live ? pm0 : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 vm = live ? vm0 : make_float4(0.f, 0.f, 0.f, 0.f);
+    // this group's entries within the block's
+    const int cnt64 = m64 < a.N ? nn_swap(nn64) + nn_other(nn64) : 0;
+    const int inc64 = wave_inclusive_scan(cnt64);
+    const int before = h > 0 ? __builtin_amdgcn_readlane(inc64, h * OW - 1) : 0;
+    const int T = __builtin_amdgcn_readlane(inc64, h * OW + OW - 1) - before;
+    const int from = h * OW + min(lane, OW - 1);
+    const int my_off = __shfl(inc64 - cnt64, from, kWave) - before;
+    const int packed_any = __shfl(nn64, from, kWave);
+    const int ns = live ? nn_swap(packed_any) : 0, cnt = live ? ns + nn_other(packed_any) : 0;
+    const size_t first = (size_t)blk * kWave * a.k_max + before;
+    if (lane < OW) s_pos[lane] = pm;
+    int2 bond = make_int2(-1, -1);
+    if (a.bonds && live) bond = a.bonds[ptag(pm.w)];
+    __syncthreads();
+
+    struct Entry {
+        int own, j, nnj;             // owner lane (-1: none), neighbour, its list lengths
+        float4 pj;
+        float dx, dy, dz, g, u, sl, u1r;
+    };
+    auto index = [&](int row, Entry& x) {
+        const int e = row * kWave + lane;
+        x.own = -1;
+        x.j = base_m;
+        if (e < T) {
+            x.own = a.pl_o[first + e] - h * OW;
+            x.j = a.pl_j[first + e];
+        }
+    };
+    auto request = [&](Entry& x) {
+        x.pj = pm;
+        x.nnj = 0;
+        if (x.own >= 0) {
+            const unsigned lj = (unsigned)(x.j - base_m);
+            if (lj < (unsigned)OW) {
+                x.pj = s_pos[lj];
+            } else {
+                x.pj = a.pos_in[x.j];
+                x.nnj = a.nn[x.j];
+            }
+        }
+    };
+    // the entry's terms (zero outside its cutoff) and its share of S
+    auto terms = [&](Entry& x) {
+        x.dx = x.dy = x.dz = x.g = x.u = x.sl = x.u1r = 0.0f;
+        if (x.own >= 0) {
+            const float4 po = s_pos[x.own];
+            const DevEntry& en = s_tab[ptype(po.w) * nt + ptype(x.pj.w)];
+            if (en.kind != RC_KIND_NONE) {
+                const PairGeom pg = pair_geom<false>(po, x.pj, a.box, en);
+                if (pg.cut) {
+                    float phi;
+                    pair_vhat_eval(en, en.kind == RC_KIND_SWAP, pg.inside, pg.r2, phi, x.g, x.u, x.u1r);
+                    x.dx = pg.dx;
+                    x.dy = pg.dy;
+                    x.dz = pg.dz;
+                    if (en.kind == RC_KIND_SWAP) x.sl = en.sqrt_lam;
+                }
+            }
+        }
+        s_w[0][lane] = x.sl;
+        s_w[1][lane] = x.u;
+    };
+    float S = 0.0f;
+    auto add_sums = [&](int row) {
+        __syncthreads();
+        const int b = row * kWave, lo = max(my_off, b) - b, hi = min(my_off + ns, b + kWave) - b;
+        for (int q = lo; q < hi; ++q) S = __fmaf_rn(s_w[0][q], s_w[1][q], S);
+        __syncthreads();
+    };
+
+    Entry x;   // the first row's; further ones are read again
+    index(0, x);
+    // while the indices are on their way: the spring partners' and the noise
+    int bi[2] = {-1, -1};
+    float4 bp[2] = {pm, pm};
+    float nz[3] = {0.f, 0.f, 0.f};
+    if (a.bonds) {
+        if (bond.x >= 0) bi[0] = a.rtag[bond.x];
+        if (bond.y >= 0) bi[1] = a.rtag[bond.y];
+    }
+    if (a.langevin) {
+        thermostat_normals(a.seed, (uint32_t)ptag(pm.w), step, nz[0], nz[1], nz[2]);
+        asm volatile("" : "+v"(nz[0]), "+v"(nz[1]), "+v"(nz[2]));   // drawn here, not where they are used
+    }
+    request(x);
+    if (a.bonds) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (bi[q] >= 0) bp[q] = a.pos_in[bi[q]];
+    }
+    terms(x);
+    add_sums(0);
+    for (int r = 1; r * kWave < T; ++r) {
+        Entry y;
+        index(r, y);
+        request(y);
+        terms(y);
+        add_sums(r);
+    }
+    if (lane < OW) s_S[lane] = S;
+    __syncthreads();
+
+    Acc acc = {};
+    auto force = [&](int row, const Entry& x) {
+        float f = x.g;
+        if (x.u1r != 0.0f && x.sl != 0.0f) {
+            const unsigned lj = (unsigned)(x.j - base_m);
+            const float Sj = lj < (unsigned)OW
+                                 ? s_S[lj]
+                                 : swap_sum(x.j, x.pj, x.nnj, a.pos_in, a.nlist, a.N, s_tab, nt, a.box);
+            const float k1 = x.sl * x.u1r;
+            // the terms centred on the owner and on j, rounded as in wave_gather
+            const float so = __fmaf_rn(-x.u, x.sl, s_S[x.own]), sj = __fmaf_rn(-x.u, x.sl, Sj);
+            f += __fmaf_rn(k1, so, k1 * sj);
+        }
+        s_c[0][lane] = f * x.dx;
+        s_c[1][lane] = f * x.dy;
+        s_c[2][lane] = f * x.dz;
+        __syncthreads();
+        const int b = row * kWave, lo = max(my_off, b) - b, hi = min(my_off + cnt, b + kWave) - b;
+        for (int q = lo; q < hi; ++q) {
+            acc.fx += s_c[0][q];
+            acc.fy += s_c[1][q];
+            acc.fz += s_c[2][q];
+        }
+        __syncthreads();
+    };
+    force(0, x);
+    for (int r = 1; r * kWave < T; ++r) {
+        Entry y;
+        index(r, y);
+        request(y);
+        terms(y);
+        force(r, y);
+    }
+    if (a.bonds && live) fene_pair(bi, bp, pm, a.box, a.fene_k, a.fene_r02, acc);
+    step_finish<false, true, true>(a, a.pos_out, m, blk, live, pm, vm, acc, a.box, 0, a.seed, step, nz);
+    if (a.reset_status && blockIdx.x == 0 && threadIdx.x == 0) chunk_reset(a.reset_status, a.reset_base, a.reset_to);
+}
+
 // Step kernels by (ev, batch, width, form); log steps use the default width.
 template <bool BATCH, bool SF>
 static const void* step_fn_form(bool ev, int width) {
@@ -668,9 +844,21 @@ static const void* sums_fn(bool batch, int ow) {
     }
 }
 
+// Whether the two-pass form takes one launch: while 16 particles' entries fill about half a row, so that a row
+// holds them in a denser spot too, and the wavefronts are at most five per SIMD.  us per step, two launches and
+// one: dumbbells (2.1 entries per particle at the largest list radius) as generated 1500 9.1, 7.4; 20011 9.3, 8.0;
+// 80000 11.1, 10.4; aggregated 1500 10.4, 8.8; 20011 11.9, 10.0; 65536 13.1, 11.5; reactive particles of density
+// 0.25 (6.1) 1000 10.3, 19.4; 30000 13.4, 22.1 (with 8 per wavefront 12.8 and 15.9).
+static bool fused_sums(int N, float list_est) { return kFusedOwn * list_est <= 40.0f && N <= 5120 * kFusedOwn; }
+
 StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_est) {
     StepKernel k;
     const int few = batch ? kStepBlock : step_particles(N, list_est);
+    if (!batch && !ev && form == RC_FORM_SUMS && fused_sums(N, list_est)) {
+        k.particles = kFusedOwn;
+        k.fn = reinterpret_cast<const void*>(&k_step_fused);
+        return k;
+    }
     if (!ev) k.particles = few;
     if (k.particles < kStepBlock)
         k.fn = form == RC_FORM_SUMS ? few_fn<true>(few) : few_fn<false>(few);

@@ -161,3 +161,23 @@ def test_list_holds_every_pair_once(N, cells):
     first = (S.pos.clone(), S.nn.clone(), S.nlist.clone())
     S.build()
     assert all(torch.equal(a, b) for a, b in zip(first, (S.pos, S.nn, S.nlist)))
+
+
+@pytest.mark.parametrize("N,grow", [(1100, 1.45), (3001, 1.6), (40953, 1.7), (81921, 1.7)])
+def test_one_launch_of_the_two_pass_form_equals_two(N, grow):
+    # a dense drop in a large box: short lists by the mean density, so the one-launch form runs, but rows of
+    # entries past those it keeps in registers and swap ranges longer than a walk's first four slots; against
+    # log steps, which take two launches, bit for bit
+    from paper_1912_08569_amd import System
+    s = W.small_reactive(N=N, density=0.3, seed=N, min_dist=0.95)
+    L = float(np.float32(s.L * grow))
+    print(f"case: N={N} grow={grow}", flush=True)
+    out = []
+    for period, graph in ((1, False), (0, False), (0, True)):
+        S = System(s.pos, s.types, L, s.table, vel=s.vel, mass=s.mass, step_form="sums")
+        cfg = S.integrator(dt=0.001, kT=0.1, gamma=1.0, seed=12)
+        S.run(40, cfg, log_period=period, use_graph=graph, max_chunk=18, adapt=False)
+        out.append((S.pos.clone(), S.vel.clone(), S.image.clone()))
+    assert S.mean_swap_length() > 4.0
+    for other in out[1:]:
+        assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(out[0], other))
