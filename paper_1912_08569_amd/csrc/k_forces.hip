@@ -652,7 +652,7 @@ __global__ __launch_bounds__(kWave) void k_step_fused(StepArgs a) {
     struct Entry {
         int own, j, nnj;             // owner lane (-1: none), neighbour, its list lengths
         float4 pj;
-        float dx, dy, dz, g, u, sl, u1r;
+        SwapEntry t;
     };
     auto index = [&](int row, Entry& x) {
         const int e = row * kWave + lane;
@@ -678,24 +678,10 @@ __global__ __launch_bounds__(kWave) void k_step_fused(StepArgs a) {
     };
     // the entry's terms (zero outside its cutoff) and its share of S
     auto terms = [&](Entry& x) {
-        x.dx = x.dy = x.dz = x.g = x.u = x.sl = x.u1r = 0.0f;
-        if (x.own >= 0) {
-            const float4 po = s_pos[x.own];
-            const DevEntry& en = s_tab[ptype(po.w) * nt + ptype(x.pj.w)];
-            if (en.kind != RC_KIND_NONE) {
-                const PairGeom pg = pair_geom<false>(po, x.pj, a.box, en);
-                if (pg.cut) {
-                    float phi;
-                    pair_vhat_eval(en, en.kind == RC_KIND_SWAP, pg.inside, pg.r2, phi, x.g, x.u, x.u1r);
-                    x.dx = pg.dx;
-                    x.dy = pg.dy;
-                    x.dz = pg.dz;
-                    if (en.kind == RC_KIND_SWAP) x.sl = en.sqrt_lam;
-                }
-            }
-        }
-        s_w[0][lane] = x.sl;
-        s_w[1][lane] = x.u;
+        x.t = SwapEntry{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if (x.own >= 0) x.t = swap_entry(s_pos[x.own], x.pj, s_tab, nt, a.box);
+        s_w[0][lane] = x.t.sl;
+        s_w[1][lane] = x.t.u;
     };
     float S = 0.0f;
     auto add_sums = [&](int row) {
@@ -739,20 +725,17 @@ __global__ __launch_bounds__(kWave) void k_step_fused(StepArgs a) {
 
     Acc acc = {};
     auto force = [&](int row, const Entry& x) {
-        float f = x.g;
-        if (x.u1r != 0.0f && x.sl != 0.0f) {
+        float f = x.t.g;
+        if (needs_sums(x.t)) {
             const unsigned lj = (unsigned)(x.j - base_m);
             const float Sj = lj < (unsigned)OW
                                  ? s_S[lj]
                                  : swap_sum(x.j, x.pj, x.nnj, a.pos_in, a.nlist, a.N, s_tab, nt, a.box);
-            const float k1 = x.sl * x.u1r;
-            // the terms centred on the owner and on j, rounded as in wave_gather
-            const float so = __fmaf_rn(-x.u, x.sl, s_S[x.own]), sj = __fmaf_rn(-x.u, x.sl, Sj);
-            f += __fmaf_rn(k1, so, k1 * sj);
+            f = swap_factor(x.t, s_S[x.own], Sj);
         }
-        s_c[0][lane] = f * x.dx;
-        s_c[1][lane] = f * x.dy;
-        s_c[2][lane] = f * x.dz;
+        s_c[0][lane] = f * x.t.dx;
+        s_c[1][lane] = f * x.t.dy;
+        s_c[2][lane] = f * x.t.dz;
         __syncthreads();
         const int b = row * kWave, lo = max(my_off, b) - b, hi = min(my_off + cnt, b + kWave) - b;
         for (int q = lo; q < hi; ++q) {

@@ -376,6 +376,39 @@ __device__ __forceinline__ float swap_sum(int m, const float4& pm, int packed, c
     return s;
 }
 
+// One entry of the two-pass form, evaluated once for its share of S and its
+// force (zero outside the cutoff; u and sl are zero unless it is a swap pair).
+struct SwapEntry {
+    float dx, dy, dz, g, u, sl, u1r;   // separation, pair factor, vhat, sqrt(lambda eps), vhat'/r
+};
+
+__device__ __forceinline__ SwapEntry swap_entry(const float4& po, const float4& pj, const DevEntry* tab, int nt,
+                                                const Box& box) {
+    SwapEntry x{0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    const DevEntry& en = tab[ptype(po.w) * nt + ptype(pj.w)];
+    if (en.kind != RC_KIND_NONE) {
+        const PairGeom pg = pair_geom<false>(po, pj, box, en);
+        if (pg.cut) {
+            float phi;
+            pair_vhat_eval(en, en.kind == RC_KIND_SWAP, pg.inside, pg.r2, phi, x.g, x.u, x.u1r);
+            x.dx = pg.dx;
+            x.dy = pg.dy;
+            x.dz = pg.dz;
+            if (en.kind == RC_KIND_SWAP) x.sl = en.sqrt_lam;
+        }
+    }
+    return x;
+}
+
+// whether the entry's force needs the sums S of its owner and its neighbour, and the force factor with them: the
+// terms centred on the owner and on the neighbour, rounded as in wave_gather
+__device__ __forceinline__ bool needs_sums(const SwapEntry& x) { return x.u1r != 0.0f && x.sl != 0.0f; }
+__device__ __forceinline__ float swap_factor(const SwapEntry& x, float S_owner, float S_j) {
+    const float k1 = x.sl * x.u1r;
+    const float so = __fmaf_rn(-x.u, x.sl, S_owner), sj = __fmaf_rn(-x.u, x.sl, S_j);
+    return x.g + __fmaf_rn(k1, so, __fmul_rn(k1, sj));
+}
+
 // swap_sum of the OW particles of a wavefront, bit for bit, from its T entries
 // of the packed list (from pl_first on, owner lane lane0 the first's): the
 // entries evaluated flat, 64 PL per pass, and every owner's swap entries (ns of

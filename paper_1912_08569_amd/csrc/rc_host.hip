@@ -739,6 +739,7 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
     // runs of 2^20 particles: 6-7 us less per run than with one replay, paired medians over 18 runs;
     // long runs and smaller systems keep the replays: 12.9 against 14.6 us per step at 2048 particles).
     const bool big = (int64_t)N >= (int64_t)1 << 19;
+    constexpr int64_t kBlockSteps = 64;   // steps of a one-workgroup launch at most
     // run `count` steps from the state at absolute step `from` (in P[cur])
     auto run_steps = [&](uint64_t from, int64_t count) -> int {
         const bool replays = graphs && (count >= 2 * (int64_t)G || !big);
@@ -750,11 +751,12 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
                 int rr = log_now(cur);
                 if (rr) return rr;
             }
-            if (replays && !first && !ev && count - k >= G) {
-                // a graph replay must not cross a logging step
-                bool clear = true;
-                for (int64_t q = 1; q < G && clear; ++q) clear = !log_at(step + (uint64_t)q);
-                if (clear) {
+            if (replays && !first && !ev && (count - k >= G || blockrun)) {
+                // a replay must not cross a logging step; a one-workgroup launch takes any number of steps
+                int64_t n = 1;
+                const int64_t most = blockrun ? std::min<int64_t>(count - k, kBlockSteps) : G;
+                while (n < most && !log_at(step + (uint64_t)n)) ++n;
+                if (n == most || (blockrun && n > 1)) {
                     int rr = pay_reset();
                     if (rr) return rr;
                     if (dev_base != step) HIP_TRY(c, launch_set_step(c->d_step_base, step, s));
@@ -766,13 +768,13 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
                         a.step = 0;
                         a.step_base = c->d_step_base;
                         a.ev_part = nullptr;
-                        HIP_TRY(c, ops.launch_block(a, reinterpret_cast<float4*>(P[cur]), G));
+                        HIP_TRY(c, ops.launch_block(a, reinterpret_cast<float4*>(P[cur]), (int)n));
                     } else {
                         HIP_TRY(c, hipGraphLaunch(c->gc.exec[cur], s));
                     }
-                    dev_base = step + G;
-                    k += G;
-                    continue;  // G is even: cur is unchanged
+                    dev_base = step + (uint64_t)n;
+                    k += n;
+                    continue;  // G is even, and a one-workgroup launch leaves the state in P[cur]: cur is unchanged
                 }
             }
             int rr = direct(step, first ? RC_STEP_START : RC_STEP_CONT, ev);

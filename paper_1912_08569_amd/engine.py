@@ -318,8 +318,8 @@ class System:
         Log rows are taken at the step indices in [step0, step0 + n_steps) that are multiples of
         log_period (none for 0) and at the end; a continued run (keep_list) does not repeat the last
         run's final row.
-        one_block: with use_graph, systems of at most 1024 particles run each replay of graph_steps
-        steps in one workgroup launch (same results, bit for bit).
+        one_block: with use_graph, systems of at most 1024 particles and short lists run the steps between
+        log rows in one-workgroup launches (same results, bit for bit).
         keep_list: a run that starts where the last one ended (step0 = its last step) continues on
         its neighbour list instead of building one at entry; code that writes the state tensors
         directly calls invalidate() first.

@@ -181,3 +181,36 @@ def test_one_launch_of_the_two_pass_form_equals_two(N, grow):
     assert S.mean_swap_length() > 4.0
     for other in out[1:]:
         assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(out[0], other))
+
+
+@pytest.mark.parametrize("N,kind", [(40, "pair"), (512, "drop"), (600, "drop"), (1024, "mix"), (512, "types")])
+def test_one_workgroup_steps_equal_launched_ones(N, kind):
+    # the one-workgroup form (rows of entries in registers, noise drawn a step ahead, any number of steps per
+    # launch) against launches, bit for bit: one short row, wavefronts past the rows kept (a dense drop), two
+    # rows and a half, a table that leaves no room for the staging; odd stretches between log rows
+    from paper_1912_08569_amd import System
+    if kind == "drop":
+        s = W.small_reactive(N=N, density=0.3, seed=N, min_dist=0.95)
+        L, types, table, mass = float(np.float32(s.L * 2.2)), s.types, s.table, s.mass
+    else:
+        s = W.dumbbell_mixture(N=N, seed=N)
+        L, types, table, mass = s.L, s.types, s.table, s.mass
+        if kind == "types":     # the same two species spread over 16 types
+            types = (s.types + 2 * (np.arange(N) % 8)).astype(np.int32)
+            table = W.PairTable.empty(16)
+            for a in range(16):
+                for b in range(a, 16):
+                    p, q = a % 2, b % 2
+                    table.set(a, b, int(s.table.kind[p, q]), s.table.epsilon[p, q], s.table.sigma[p, q],
+                              int(s.table.n[p, q]), s.table.rcut[p, q], s.table.lam[p, q])
+            mass = np.ones(16)
+    print(f"case: N={N} {kind}", flush=True)
+    out = []
+    for one in (False, True):
+        S = System(s.pos, types, L, table, vel=s.vel, mass=mass, step_form="sums")
+        cfg = S.integrator(dt=0.001, kT=0.05, gamma=1.0, seed=13)
+        for k, n in enumerate((37, 1, 90)):
+            r = S.run(n, cfg, step0=(0, 37, 38)[k], log_period=17, one_block=one, max_chunk=29, adapt=False)
+            out.append((S.pos.clone(), S.vel.clone(), S.image.clone(), torch.from_numpy(r.ev.copy())))
+    for a, b in zip(out[:3], out[3:]):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
