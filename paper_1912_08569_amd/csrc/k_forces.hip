@@ -363,10 +363,10 @@ __global__ __launch_bounds__(kWave) void k_swap_sums(ForceArgs a) {
 // wavefront as in k_step_few.  A lane per particle took the wavefront's longest
 // swap range in fours (8.6 us per launch at 5000 particles of density 0.25; now
 // 4.8, about a launch's own time).
-template <bool BATCH, int OW>
+template <bool BATCH, int OW, int PL = 2>   // PL: entries per lane and pass
 __global__ __launch_bounds__(kWave) void k_swap_sums_packed(ForceArgs a) {
     static_assert(!BATCH || OW == kWave, "a batch chunk has 64 slots");
-    constexpr int PL = 2, G = kWave / OW;
+    constexpr int G = kWave / OW;
     extern __shared__ DevEntry s_tab[];
     __shared__ float4 s_pos[OW];
     __shared__ float s_w[2][PL * kWave];
@@ -817,8 +817,12 @@ static int step_particles(int N, float list_est) {
     return ow;
 }
 
-static const void* sums_fn(bool batch, int ow) {
-    if (batch) return reinterpret_cast<const void*>(&k_swap_sums_packed<true, kWave>);
+// Batches of lists longer than a pass of two entries per lane holds take four (16.8 -> 15.6 us per launch at 96
+// replicas, five entries per particle; 131072 dumbbells, 1.7 entries: 12.5 -> 12.7 per step).
+static const void* sums_fn(bool batch, int ow, float list_est) {
+    if (batch)
+        return list_est > 3.0f ? reinterpret_cast<const void*>(&k_swap_sums_packed<true, kWave, 4>)
+                               : reinterpret_cast<const void*>(&k_swap_sums_packed<true, kWave>);
     switch (ow) {
         case 8: return reinterpret_cast<const void*>(&k_swap_sums_packed<false, 8>);
         case 16: return reinterpret_cast<const void*>(&k_swap_sums_packed<false, 16>);
@@ -848,7 +852,7 @@ StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float li
     else
         k.fn = batch ? step_fn<true>(ev, width, form) : step_fn<false>(ev, width, form);
     if (form == RC_FORM_SUMS) {
-        k.sums_fn = sums_fn(batch, few);
+        k.sums_fn = sums_fn(batch, few, list_est);
         k.sums_particles = few;
     }
     return k;

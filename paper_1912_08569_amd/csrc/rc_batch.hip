@@ -15,6 +15,7 @@ struct rc_batch {
     rc_ctx c;                     // error text, tables, partial rows, status slots, graphs
     int R = 0;
     int n_slots = 0;
+    float list_est = 0.0f;              // list entries per particle at its replica's largest list radius, on average
     uint32_t nkeys = 0;
     std::vector<int> counts;
     std::vector<int> offsets;     // [R + 1]
@@ -117,6 +118,7 @@ int fill_step_args_batch(rc_batch* b, StepArgs& a, const float* pos_in, float* p
         return r;
     a.pl_j = c->d_pl_j;
     a.pl_o = c->d_pl_o;
+    a.list_est = b->list_est;
     return RC_OK;
 }
 
@@ -144,7 +146,7 @@ int rc_batch_create(rc_batch** out, int R, int ntypes, const rc_pair_coeff* tabl
     b->desc.resize(R);
     int64_t slots = 0;
     uint64_t keys = 0;
-    double rmax_all = 0.0;
+    double rmax_all = 0.0, entries = 0.0, particles = 0.0;
     for (int r = 0; r < R; ++r) {
         double rl = 0.0;
         if (compile_table(ntypes, tables + (size_t)r * nt2, r_buff, c->host_tab.data() + (size_t)r * nt2, &rl,
@@ -164,6 +166,9 @@ int rc_batch_create(rc_batch** out, int R, int ntypes, const rc_pair_coeff* tabl
         d.tab = r * nt2;
         b->offsets[r] = (int)slots;
         keys += d.grid.nkeys;
+        const Box& x = d.box;
+        entries += (double)counts[r] * ((double)counts[r] / (x.L[0] * x.L[1] * x.L[2]) * 4.18879 * rl * rl * rl);
+        particles += (double)counts[r];
         slots += (int64_t)kWave * ((counts[r] + kWave - 1) / kWave);
         if (slots >= RC_MAX_TAG || keys > (uint64_t)8192 * kScanTile) {
             free_batch(b);
@@ -171,6 +176,7 @@ int rc_batch_create(rc_batch** out, int R, int ntypes, const rc_pair_coeff* tabl
         }
     }
     b->offsets[R] = (int)slots;
+    b->list_est = (float)(entries / particles);
     b->n_slots = (int)slots;
     b->nkeys = (uint32_t)keys;
     c->rlist_max = rmax_all;
@@ -593,7 +599,7 @@ struct BatchOps final : DriveOps {
                                                 buf->ev_log + (size_t)row * b->R * kEvWords, kEvWords, s));
         return RC_OK;
     }
-    StepKernel plain_step() override { return step_kernel(true, false, b->c.gather_width, b->c.step_form, b->n_slots, 0.0f); }
+    StepKernel plain_step() override { return step_kernel(true, false, b->c.gather_width, b->c.step_form, b->n_slots, b->list_est); }
     // the batch cell sort also permutes (pos, vel, image) of every slot through
     // the workspace's temporaries and copies them back
     bool rebuild_snapshot(const float4** p, const float4** v, const int4** im) override {

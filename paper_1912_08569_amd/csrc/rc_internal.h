@@ -454,7 +454,7 @@ struct StepArgs {
     const RepDesc* rep;        // [R]
     const int* chunk_rep;      // [N / 64] replica of each 64-slot chunk
     const uint64_t* seeds;     // [R] thermostat keys
-    float list_est;            // single systems: list entries per particle at the largest list radius (launcher)
+    float list_est;            // list entries per particle at the largest list radius (read by the launcher)
     int width;                 // gather width of the non-logging steps: 1, 2 or 4 (read by the launcher)
     int form;                  // RC_FORM_WALK or RC_FORM_SUMS (read by the launcher)
     float* ssum;               // [N] per-particle switching sums (RC_FORM_SUMS)
