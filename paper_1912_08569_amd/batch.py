@@ -88,6 +88,7 @@ class Batch:
         self.bc.set_rebuild_margin(rebuild_margin)
         self.built = False
         self._continues = False     # the state is what the last run left (its list may be kept)
+        self._log = None            # log rows of the last run (ev rows, then bond counts), kept between runs
         self._attach_workspace()
 
     @classmethod
@@ -182,8 +183,12 @@ class Batch:
         """Advance every replica n_steps under the chunked driver (log rows and keep_list as
         System.run)."""
         rows = (n_steps // log_period + 2) if log_period > 0 else 1
-        ev_log = torch.zeros((rows, self.R, 13), dtype=torch.float64, device=self.device)
-        bonds_log = torch.zeros((rows, self.R), dtype=torch.int64, device=self.device)
+        # pinned host memory, which the driver's kernels write directly (as System.run's log rows)
+        words = rows * self.R * 14
+        if self._log is None or self._log.shape[0] < words:
+            self._log = torch.zeros(max(words, 1024), dtype=torch.float64, pin_memory=True)
+        ev_log = self._log[:rows * self.R * 13].view(rows, self.R, 13)
+        bonds_log = self._log[rows * self.R * 13:words].view(torch.int64).view(rows, self.R)
         opts = rcl.MdOptions(int(use_graph), int(graph_steps), int(max_chunk), int(log_period), float(soft_frac),
                              int(adapt), 0, 0, int(keep_list and self._continues), int(time_kernels))
         self._continues = False
@@ -205,7 +210,7 @@ class Batch:
         self.built = True
         self._continues = True
         n = int(st.log_rows)
-        return BatchResult(stats=st, ev=ev_log[:n].cpu().numpy(), bonds=bonds_log[:n].cpu().numpy())
+        return BatchResult(stats=st, ev=ev_log[:n].numpy().copy(), bonds=bonds_log[:n].numpy().copy())
 
     # ---- per-replica views in tag order ------------------------------------------------------
     def slots(self, r: int) -> slice:

@@ -1345,13 +1345,28 @@ hipError_t launch_reduce_rows(const double* part, int nblocks, int first, int co
 
 // The same fixed-order sum per replica over its own chunk rows (grid: words x
 // replicas), so a replica's sums equal those of the system run on its own.
+// bonds: per-chunk bond counts, summed by one more column of blocks (NULL: none).
 __global__ __launch_bounds__(kBlock) void k_reduce_rows_batch(const double* __restrict__ part,
                                                              const RepDesc* __restrict__ rep, int first,
-                                                             double* __restrict__ out, int out_stride) {
+                                                             double* __restrict__ out, int out_stride,
+                                                             const unsigned* __restrict__ bonds,
+                                                             unsigned long long* __restrict__ bonds_out) {
     __shared__ double red[kBlock];
     const RepDesc& d = rep[blockIdx.y];
     const double* p = part + (size_t)(d.off / kWave) * kEvWords;
     const int nblocks = (d.n + kWave - 1) / kWave;
+    if (bonds && blockIdx.x == gridDim.x - 1) {   // whole numbers below 2^53: exact in FP64
+        double t = 0.0;
+        for (int b = threadIdx.x; b < nblocks; b += blockDim.x) t += (double)bonds[d.off / kWave + b];
+        t = wave_sum(t);
+        if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = t;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kBlock / kWave; ++w) t += red[w];
+            bonds_out[blockIdx.y] = (unsigned long long)t;
+        }
+        return;
+    }
     const int q = first + blockIdx.x;
     const double s = strided_row_sum(p, nblocks, q);
     red[threadIdx.x] = s;
@@ -1364,8 +1379,10 @@ __global__ __launch_bounds__(kBlock) void k_reduce_rows_batch(const double* __re
 }
 
 hipError_t launch_reduce_rows_batch(const double* part, const RepDesc* rep, int R, int first, int count,
-                                    double* out, int out_stride, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce_rows_batch, dim3(count, R), dim3(kBlock), 0, s, part, rep, first, out, out_stride);
+                                    double* out, int out_stride, hipStream_t s, const unsigned* bonds,
+                                    unsigned long long* bonds_out) {
+    hipLaunchKernelGGL(k_reduce_rows_batch, dim3(count + (bonds ? 1 : 0), R), dim3(kBlock), 0, s, part, rep, first, out,
+                       out_stride, bonds, bonds_out);
     return hipGetLastError();
 }
 

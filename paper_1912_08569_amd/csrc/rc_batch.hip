@@ -583,20 +583,33 @@ struct BatchOps final : DriveOps {
         *growth = g / (double)std::max<int64_t>(C, 1);
         return true;
     }
+    // With both logs a row's bond counts come from the ev step on the same positions, as for one system
+    bool fused_bonds() const { return buf->ev_log != nullptr && buf->bonds_log != nullptr; }
+    unsigned* bond_part() const {
+        return reinterpret_cast<unsigned*>(b->c.d_part + (size_t)kEvWords * nblocks(b->n_slots, kStepBlock));
+    }
     int bonds(const float* pos, int row) override {
+        if (fused_bonds()) return RC_OK;
         HIP_TRY(&b->c, launch_bonds_batch(reinterpret_cast<const float4*>(pos), buf->nlist, buf->nn, buf->k_max,
                                           b->n_slots, all_tables(b), b->d_desc, b->d_chunk_rep, b->R,
                                           buf->bonds_log + (size_t)row * b->R,
                                           reinterpret_cast<unsigned long long*>(b->c.d_part), s));
         return RC_OK;
     }
-    hipError_t launch(const StepArgs& a, bool ev) override { return launch_step_batch(a, ev, s); }
+    hipError_t launch(const StepArgs& a, bool ev) override {
+        if (!ev || !fused_bonds()) return launch_step_batch(a, ev, s);
+        StepArgs e = a;
+        e.bond_part = bond_part();
+        return launch_step_batch(e, ev, s);
+    }
     hipError_t launch_timed(const StepArgs& a, hipEvent_t* sums, hipEvent_t* step) override {
         return launch_step_timed(a, true, s, sums, step);
     }
     int reduce_ev(int row) override {
         HIP_TRY(&b->c, launch_reduce_rows_batch(b->c.d_part, b->d_desc, b->R, 0, kEvWords,
-                                                buf->ev_log + (size_t)row * b->R * kEvWords, kEvWords, s));
+                                                buf->ev_log + (size_t)row * b->R * kEvWords, kEvWords, s,
+                                                fused_bonds() ? bond_part() : nullptr,
+                                                fused_bonds() ? buf->bonds_log + (size_t)row * b->R : nullptr));
         return RC_OK;
     }
     StepKernel plain_step() override { return step_kernel(true, false, b->c.gather_width, b->c.step_form, b->n_slots, b->list_est); }
@@ -632,7 +645,8 @@ extern "C" int rc_batch_run(rc_batch* b, const rc_md_buffers* buf, const rc_inte
     if (!(opt.soft_frac > 0.0 && opt.soft_frac <= 1.0)) opt.soft_frac = 0.8;
     hipStream_t s = S(stream);
     const int nb = nblocks(b->n_slots, kStepBlock);
-    if ((r = ensure_part(c, sizeof(double) * kEvWords * (size_t)nb))) return r;
+    // the ev steps' rows, then their per-chunk bond counts (BatchOps::bond_part)
+    if ((r = ensure_part(c, (sizeof(double) * kEvWords + sizeof(unsigned)) * (size_t)nb))) return r;
     StepArgs tmpl{};
     if ((r = fill_step_args_batch(b, tmpl, buf->pos, buf->pos_alt, buf->vel, buf->image, buf->nlist, buf->nn,
                                   buf->k_max, cfg, opt.soft_frac, buf->status, s, false)))

@@ -744,6 +744,7 @@ hipError_t launch_bonds_batch(const float4* pos, const int* nlist, const int* nn
                               unsigned long long* part, hipStream_t s);
 // per-replica fixed-order sums of chunk rows: out[r * out_stride + q], q < count
 hipError_t launch_reduce_rows_batch(const double* part, const RepDesc* rep, int R, int first, int count,
-                                    double* out, int out_stride, hipStream_t s);
+                                    double* out, int out_stride, hipStream_t s, const unsigned* bonds = nullptr,
+                                    unsigned long long* bonds_out = nullptr);
 
 }  // namespace rc
