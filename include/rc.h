@@ -447,6 +447,12 @@ int rc_partner_counts(rc_ctx* ctx, const int* p0, const int* pt, const unsigned 
                       int N, unsigned long long* counts /* device [3] */, void* stream);
 int rc_stress_autocorrelation(rc_ctx* ctx, const double* rows /* device [T][13] */, int T, double volume,
                               double kT, int max_lag, double* G /* device [max_lag+1] */, void* stream);
+/* rc_stress_autocorrelation_ws: the same with caller-owned scratch (device, of
+ * rc_stress_workspace_bytes, 8-byte aligned, free again once the call's work on
+ * the stream is done; NULL: none), which past 256 lags is faster. */
+int rc_stress_workspace_bytes(int T, int max_lag, size_t* bytes /* host */);
+int rc_stress_autocorrelation_ws(rc_ctx* ctx, const double* rows, int T, double volume, double kT, int max_lag,
+                                 double* G, void* ws /* NULL ok */, size_t ws_bytes, void* stream);
 
 /* ---- bond count (hot-path step a4) -------------------------------------------
  * Number of swap pairs i<j with r^2 < r_min^2 (canonical FP64 predicate, the

@@ -142,6 +142,8 @@ _SIGS = {
     "rc_load_moved": ([_VP, ctypes.POINTER(_I)], _I),
     "rc_to_tags": ([_VP, _VP, _VP, _I, _I, _VP, _VP], _I),
     "rc_from_tags": ([_VP, _VP, _VP, _I, _VP, _VP], _I),
+    "rc_stress_workspace_bytes": ([_I, _I, ctypes.POINTER(ctypes.c_size_t)], _I),
+    "rc_stress_autocorrelation_ws": ([_VP, _VP, _I, _D, _D, _I, _VP, _VP, ctypes.c_size_t, _VP], _I),
     "rc_stress_autocorrelation": ([_VP, _VP, _I, ctypes.c_double, ctypes.c_double, _I, _VP, _VP], _I),
     "rc_param_grad": ([_VP, _VP, _VP, _VP, _I, _I, Box, _VP, _VP], _I),
     "rc_param_vjp": ([_VP, _VP, _VP, _VP, _I, _I, Box, _VP, _VP, _VP], _I),

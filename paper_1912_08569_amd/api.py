@@ -396,8 +396,14 @@ def rc_stress_autocorrelation(ctx: Context, rows, volume, kT, max_lag, G, stream
     """G (max_lag + 1,) float64 device <- stress autocorrelation of logged rows (T, 13) float64 device."""
     if rows.dim() != 2 or rows.shape[1] != 13 or G.numel() < max_lag + 1:
         raise ValueError("rows must be (T, 13), G at least max_lag + 1 long")
-    check(L.load().rc_stress_autocorrelation(ctx.handle, _ptr(rows), int(rows.shape[0]), float(volume), float(kT),
-                                             int(max_lag), _ptr(G), _stream(stream)), ctx.handle)
+    T, need = int(rows.shape[0]), ctypes.c_size_t()
+    ws = None
+    if L.load().rc_stress_workspace_bytes(T, int(max_lag), ctypes.byref(need)) == L.RC_OK and need.value:
+        ws = torch.empty(need.value, dtype=torch.uint8, device=rows.device)
+        if stream is not None:
+            ws.record_stream(stream)
+    check(L.load().rc_stress_autocorrelation_ws(ctx.handle, _ptr(rows), T, float(volume), float(kT), int(max_lag),
+                                                _ptr(G), _ptr(ws), need.value, _stream(stream)), ctx.handle)
 
 
 def rc_param_vjp(ctx: Context, pos, nlist, nn, bx, adj, out, stream=None):

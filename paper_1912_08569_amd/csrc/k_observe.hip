@@ -74,8 +74,21 @@ hipError_t launch_partner_counts(const int* p0, const int* pt, const unsigned ch
     return hipGetLastError();
 }
 
-// One block per lag: the better form for at most one lag per CU (100000 rows, 101 lags: 148 us against 266 us
-// with tiles of lags; equal, 8 us, at 500 to 2000 rows).
+// The off-diagonal stresses of the rows, s[c][t] for c = xy, xz, yz (W at 4 + c, K at 10 + c of a row)
+__device__ __forceinline__ double row_stress(const double* r, int c, double inv_v) {
+    return -(r[10 + c] + r[4 + c]) * inv_v;
+}
+
+__global__ __launch_bounds__(kBlock) void k_stress_rows(const double* __restrict__ rows, int T, double inv_v,
+                                                        double* __restrict__ s) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= T) return;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s[(size_t)c * T + t] = row_stress(rows + (size_t)t * kEvWords, c, inv_v);
+}
+
+// One block per lag, from the rows: the better form for at most one lag per CU (100000 rows, 101 lags 148 us,
+// 2000 rows 7.7; from the stresses of a launch before 156 and 11).
 __global__ __launch_bounds__(kBlock) void k_stress_acf_few(const double* __restrict__ rows, int T, double inv_v,
                                                            double v_over_kt, double* __restrict__ G) {
     const int t = blockIdx.x;  // lag
@@ -83,11 +96,7 @@ __global__ __launch_bounds__(kBlock) void k_stress_acf_few(const double* __restr
     for (int t0 = threadIdx.x; t0 < T - t; t0 += blockDim.x) {
         const double* a = rows + (size_t)t0 * kEvWords;
         const double* b = rows + (size_t)(t0 + t) * kEvWords;
-        for (int c = 0; c < 3; ++c) {  // xy, xz, yz: W at 4 + c, K at 10 + c
-            const double sa = -(a[10 + c] + a[4 + c]) * inv_v;
-            const double sb = -(b[10 + c] + b[4 + c]) * inv_v;
-            acc += sa * sb;
-        }
+        for (int c = 0; c < 3; ++c) acc += row_stress(a, c, inv_v) * row_stress(b, c, inv_v);
     }
     __shared__ double red[kBlock];
     red[threadIdx.x] = acc;
@@ -99,99 +108,90 @@ __global__ __launch_bounds__(kBlock) void k_stress_acf_few(const double* __restr
     if (threadIdx.x == 0) G[t] = v_over_kt * red[0] / (3.0 * (double)(T - t));
 }
 
-// A block of 512 threads computes LG * kAcfLags consecutive lags (LG groups of
-// threads).  It walks the time origins in chunks: the stresses of the chunk's
-// origins and of the rows its lags reach are formed once in LDS, and each
-// thread multiplies OWN consecutive origins with kAcfLags lags out of a
-// register window.  Bound by reading the 104-byte rows, which each block does
-// twice (against once per lag before): an address unit takes a cycle for each
-// lane of such a stride, about 6 cycles per row and block, four times the
-// products.  The next chunk's rows are requested before this one is multiplied.
-// Whole rows read 16 bytes per lane and spread over LDS were slower (150
-// against 43 us at 20000 rows, 1001 lags).  The LDS index skips one double in
-// every OWN, so that lanes OWN apart fall on different banks.
-// us, a block per lag against this (rows, lags): (8000, 2001) 96, 21; (20000, 1001) 126, 43; (20000, 5001) 549, 55.
+// A block of 512 threads computes 32 consecutive lags of one component (two
+// groups of threads, 16 lags each).  It walks the time origins in chunks: the
+// stresses of the chunk's origins and of the rows its lags reach are staged in
+// LDS, and each thread multiplies 8 consecutive origins with 16 lags out of a
+// register window: 31 LDS reads for 128 products, about what the LDS and the
+// FP64 units of a CU take the same time for.  Read from the 104-byte rows, a
+// block per 32 lags for the three components, the reads took four times the
+// products (an address unit takes a cycle for each lane of such a stride) and
+// 5001 lags made 157 blocks.  The next chunk is requested before this one is
+// multiplied.  The LDS index skips one double in every 8, so that lanes 8 apart
+// fall on different banks.
+// us, a block per lag, from the rows, and this with its two small launches (rows, lags): (8000, 2001) 96, 21, 15;
+// (20000, 1001) 126, 43, 21; (20000, 5001) 549, 56, 37.
 constexpr int kAcfThreads = 512;
 constexpr int kAcfLags = 16;
 constexpr int kAcfRows = 2048;   // rows of each series in LDS
 
-template <int LG>
-__global__ __launch_bounds__(kAcfThreads) void k_stress_acf(const double* __restrict__ rows, int T, int max_lag,
-                                                            double inv_v, double v_over_kt, double* __restrict__ G) {
+// ROWS: without scratch, a block per 32 lags takes the three components from the rows, one after the other.
+template <bool ROWS>
+__global__ __launch_bounds__(kAcfThreads) void k_stress_acf(const double* __restrict__ src, int T, int max_lag,
+                                                            double inv_v, double v_over_kt, double* __restrict__ out) {
+    constexpr int LG = 2;
     constexpr int kGroup = kAcfThreads / LG;           // threads per group of lags
     constexpr int kOwn = kAcfRows / kGroup;            // origins per thread
     constexpr int kChunk = kAcfRows - LG * kAcfLags;   // origins per chunk
     constexpr int kFlight = kAcfRows / kAcfThreads;    // rows per thread and series
     auto at = [](int i) { return i + i / kOwn; };
     constexpr int kS = kAcfRows + kAcfRows / kOwn;
-    __shared__ double s_a[3][kS];
-    __shared__ double s_b[3][kS];
+    __shared__ double s_a[kS];
+    __shared__ double s_b[kS];
     __shared__ double s_sum[kAcfThreads / kWave][kAcfLags];
     const int l0 = blockIdx.x * (LG * kAcfLags);   // the block's first lag (<= max_lag < T)
     const int grp = threadIdx.x / kGroup, own = (threadIdx.x % kGroup) * kOwn;
     const int off = own + grp * kAcfLags;
-    struct Rows {
-        double v[kFlight][6];
-    };
-    // kAcfRows rows from r0 on (the last row in place of those past the end)
-    auto request = [&](int r0, Rows& x) {
+    // kAcfRows stresses from r0 on (the last one in place of those past the end)
+    auto request = [&](int c, int r0, double (&v)[kFlight]) {
 #pragma unroll
-        for (int u = 0; u < kFlight; ++u) {   // xy, xz, yz: W at 4 + c, K at 10 + c
-            const double* r = rows + (size_t)min(r0 + (int)threadIdx.x + u * kAcfThreads, T - 1) * kEvWords;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                x.v[u][c] = r[4 + c];
-                x.v[u][3 + c] = r[10 + c];
-            }
+        for (int u = 0; u < kFlight; ++u) {
+            const size_t t = min(r0 + (int)threadIdx.x + u * kAcfThreads, T - 1);
+            v[u] = ROWS ? row_stress(src + t * kEvWords, c, inv_v) : src[(size_t)c * T + t];
         }
     };
-    auto store = [&](const Rows& x, double(*s)[kS]) {
+    auto store = [&](const double (&v)[kFlight], double* d) {
 #pragma unroll
-        for (int u = 0; u < kFlight; ++u)
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                s[c][at(threadIdx.x + u * kAcfThreads)] = -(x.v[u][3 + c] + x.v[u][c]) * inv_v;
+        for (int u = 0; u < kFlight; ++u) d[at(threadIdx.x + u * kAcfThreads)] = v[u];
     };
     double acc[kAcfLags] = {};
-    Rows ra, rb;
-    request(0, ra);
-    request(l0, rb);
-    for (int t0 = 0; t0 < T - l0; t0 += kChunk) {
-        __syncthreads();
-        store(ra, s_a);
-        store(rb, s_b);
-        __syncthreads();
-        if (t0 + kChunk < T - l0) {
-            request(t0 + kChunk, ra);
-            request(t0 + kChunk + l0, rb);
-        }
-        const int i0 = t0 + own, lag = l0 + grp * kAcfLags;   // the thread's first origin and lag
-        if (own >= kChunk || i0 + lag >= T) continue;
-        if (i0 + kOwn - 1 + lag + kAcfLags - 1 < T) {   // every product of the thread exists
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                double a[kOwn], b[kOwn + kAcfLags - 1];
-#pragma unroll
-                for (int u = 0; u < kOwn; ++u) a[u] = s_a[c][at(own) + u];
-#pragma unroll
-                for (int u = 0; u < kOwn + kAcfLags - 1; ++u) b[u] = s_b[c][at(off) + at(u)];
-#pragma unroll
-                for (int u = 0; u < kOwn; ++u)
-#pragma unroll
-                    for (int l = 0; l < kAcfLags; ++l) acc[l] += a[u] * b[u + l];
+    for (int c = ROWS ? 0 : blockIdx.y, end = ROWS ? 3 : c + 1; c < end; ++c) {
+        double ra[kFlight], rb[kFlight];
+        request(c, 0, ra);
+        request(c, l0, rb);
+        for (int t0 = 0; t0 < T - l0; t0 += kChunk) {
+            __syncthreads();
+            store(ra, s_a);
+            store(rb, s_b);
+            __syncthreads();
+            if (t0 + kChunk < T - l0) {
+                request(c, t0 + kChunk, ra);
+                request(c, t0 + kChunk + l0, rb);
             }
-        } else {   // products past the series' end are cleared bitwise (whatever they are; no branches)
-            const int live = T - i0 - lag;   // row u + l of the thread's lags exists when below this
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
+            const int i0 = t0 + own, lag = l0 + grp * kAcfLags;   // the thread's first origin and lag
+            if (own >= kChunk || i0 + lag >= T) continue;
+            if (i0 + kOwn - 1 + lag + kAcfLags - 1 < T) {   // every product of the thread exists
+                double a[kOwn], b[kOwn + kAcfLags - 1];
+    #pragma unroll
+                for (int u = 0; u < kOwn; ++u) a[u] = s_a[at(own) + u];
+    #pragma unroll
+                for (int u = 0; u < kOwn + kAcfLags - 1; ++u) b[u] = s_b[at(off) + at(u)];
+    #pragma unroll
+                for (int u = 0; u < kOwn; ++u)
+    #pragma unroll
+                    for (int l = 0; l < kAcfLags; ++l) acc[l] += a[u] * b[u + l];
+            } else {   // products past the series' end are cleared bitwise (whatever they are; no branches)
+                const int live = T - i0 - lag;   // row u + l of the thread's lags exists when below this
+    #pragma unroll
                 for (int u = 0; u < kOwn; ++u) {
-                    const double a = s_a[c][at(own) + u];
-#pragma unroll
+                    const double a = s_a[at(own) + u];
+    #pragma unroll
                     for (int l = 0; l < kAcfLags; ++l) {
-                        const long long p = __double_as_longlong(a * s_b[c][at(off) + at(u + l)]);
+                        const long long p = __double_as_longlong(a * s_b[at(off) + at(u + l)]);
                         acc[l] += __longlong_as_double(p & (long long)((u + l - live) >> 31));
                     }
                 }
+            }
         }
     }
     // fixed order: the wavefront's sums, then the group's wavefronts one after the other
@@ -203,22 +203,36 @@ __global__ __launch_bounds__(kAcfThreads) void k_stress_acf(const double* __rest
         const int g = threadIdx.x / kAcfLags, l = threadIdx.x % kAcfLags;
         double sum = 0.0;
         for (int w = 0; w < nw; ++w) sum += s_sum[g * nw + w][l];
-        G[t] = v_over_kt * sum / (3.0 * (double)(T - t));
+        if (ROWS) out[t] = v_over_kt * sum / (3.0 * (double)(T - t));
+        else out[(size_t)blockIdx.y * (max_lag + 1) + t] = sum;
     }
 }
 
+__global__ __launch_bounds__(kBlock) void k_stress_sum(const double* __restrict__ part, int T, int n, double v_over_kt,
+                                                       double* __restrict__ G) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) G[t] = v_over_kt * (part[t] + part[n + t] + part[2 * (size_t)n + t]) / (3.0 * (double)(T - t));
+}
+
+size_t stress_scratch_doubles(int T, int max_lag) {
+    return max_lag < 256 ? 0 : 3 * ((size_t)T + (size_t)max_lag + 1);
+}
+
 hipError_t launch_stress_acf(const double* rows, int T, double volume, double kT, int max_lag, double* G,
-                             hipStream_t s) {
+                             double* scratch, hipStream_t s) {
     const int n = max_lag + 1;
     const double inv_v = 1.0 / volume, v_over_kt = volume / kT;
-    if (n <= 256)
+    const dim3 tiles(nblk(n, 2 * kAcfLags), 3), threads(kAcfThreads);
+    if (n <= 256) {
         hipLaunchKernelGGL(k_stress_acf_few, dim3(n), dim3(kBlock), 0, s, rows, T, inv_v, v_over_kt, G);
-    else if (n <= 256 * kAcfLags)   // a block holds a CU's LDS: 16 lags each while that makes at most one per CU
-        hipLaunchKernelGGL(k_stress_acf<1>, dim3(nblk(n, kAcfLags)), dim3(kAcfThreads), 0, s, rows, T, max_lag, inv_v,
-                           v_over_kt, G);
-    else
-        hipLaunchKernelGGL(k_stress_acf<2>, dim3(nblk(n, 2 * kAcfLags)), dim3(kAcfThreads), 0, s, rows, T, max_lag,
-                           inv_v, v_over_kt, G);
+    } else if (!scratch) {
+        hipLaunchKernelGGL(k_stress_acf<true>, dim3(tiles.x), threads, 0, s, rows, T, max_lag, inv_v, v_over_kt, G);
+    } else {
+        double* part = scratch + 3 * (size_t)T;
+        hipLaunchKernelGGL(k_stress_rows, dim3(nblk(T, kBlock)), dim3(kBlock), 0, s, rows, T, inv_v, scratch);
+        hipLaunchKernelGGL(k_stress_acf<false>, tiles, threads, 0, s, scratch, T, max_lag, inv_v, v_over_kt, part);
+        hipLaunchKernelGGL(k_stress_sum, dim3(nblk(n, kBlock)), dim3(kBlock), 0, s, part, T, n, v_over_kt, G);
+    }
     return hipGetLastError();
 }
 

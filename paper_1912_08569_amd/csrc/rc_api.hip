@@ -690,15 +690,29 @@ int rc_partner_counts(rc_ctx* c, const int* p0, const int* pt, const unsigned ch
     return RC_OK;
 }
 
-int rc_stress_autocorrelation(rc_ctx* c, const double* rows, int T, double volume, double kT, int max_lag,
-                              double* G, void* stream) {
+int rc_stress_workspace_bytes(int T, int max_lag, size_t* bytes) {
+    if (!bytes || T < 1 || max_lag < 0 || max_lag >= T) return RC_ERR_ARG;
+    *bytes = sizeof(double) * stress_scratch_doubles(T, max_lag);
+    return RC_OK;
+}
+
+int rc_stress_autocorrelation_ws(rc_ctx* c, const double* rows, int T, double volume, double kT, int max_lag,
+                                 double* G, void* ws, size_t ws_bytes, void* stream) {
     if (!c) return RC_ERR_ARG;
     if (!rows || !G) return fail(c, RC_ERR_ARG, "rows / G are NULL");
     if (T < 1 || max_lag < 0 || max_lag >= T)
         return fail(c, RC_ERR_ARG, "need 0 <= max_lag < T (T = %d, max_lag = %d)", T, max_lag);
     if (!(volume > 0.0) || !(kT > 0.0)) return fail(c, RC_ERR_ARG, "volume and kT must be > 0");
-    HIP_TRY(c, launch_stress_acf(rows, T, volume, kT, max_lag, G, S(stream)));
+    const size_t need = sizeof(double) * stress_scratch_doubles(T, max_lag);
+    if (ws && (ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 7)))
+        return fail(c, RC_ERR_WORKSPACE, "the stress workspace needs %zu bytes, 8-byte aligned (got %zu)", need, ws_bytes);
+    HIP_TRY(c, launch_stress_acf(rows, T, volume, kT, max_lag, G, static_cast<double*>(ws), S(stream)));
     return RC_OK;
+}
+
+int rc_stress_autocorrelation(rc_ctx* c, const double* rows, int T, double volume, double kT, int max_lag,
+                              double* G, void* stream) {
+    return rc_stress_autocorrelation_ws(c, rows, T, volume, kT, max_lag, G, nullptr, 0, stream);
 }
 
 int rc_force_hvp(rc_ctx* c, const float* pos, const int* nlist, const int* nn, int k_max, int N, rc_box box, const float* v,

@@ -35,6 +35,27 @@ def test_stress_autocorrelation_tiles(T, max_lag):
             assert abs(G[t] - ref) <= 2 * (n + 8) * 2.0 ** -53 * V / 0.7 * np.abs(p).sum() / n, (t, G[t], ref)
 
 
+@pytest.mark.parametrize("T,max_lag", [(300, 256), (2049, 2048), (4111, 287), (9000, 1000)])
+def test_stress_autocorrelation_without_scratch(T, max_lag):
+    # the form that reads the rows (no scratch given) against the one with scratch: the same products in another
+    # order, |difference| <= 2 n u sum |products|; a scratch of the wrong size is refused
+    from paper_1912_08569_amd import System, api
+    from paper_1912_08569_amd import _lib as rcl
+    S = System.from_workload(W.small_reactive(N=300, density=0.2, seed=1))
+    V = float(S.edges[0]) ** 3
+    r = torch.from_numpy(np.random.default_rng(T).standard_normal((T, 13)) * 50.0).cuda()
+    G, H = (torch.empty(max_lag + 1, dtype=torch.float64, device="cuda") for _ in range(2))
+    api.rc_stress_autocorrelation(S.ctx, r, V, 0.7, max_lag, G)
+    args = (S.ctx.handle, api._ptr(r), T, V, 0.7, max_lag, api._ptr(H))
+    assert rcl.load().rc_stress_autocorrelation(*args, api._stream()) == rcl.RC_OK
+    s = torch.from_numpy(np.abs(observables_ref.shear_stress(r.cpu().numpy(), V)))
+    t = torch.arange(max_lag + 1)
+    size = torch.stack([(s[:T - k] * s[k:]).sum() for k in t.tolist()]) * V / 0.7 / (3 * (T - t))
+    bound = 2 * (3 * (T - t) + 8) * 2.0 ** -53 * size
+    assert bool(((G - H).abs().cpu() <= bound).all())
+    assert rcl.load().rc_stress_autocorrelation_ws(*args, api._ptr(r), 8, api._stream()) == rcl.RC_ERR_WORKSPACE
+
+
 @pytest.mark.parametrize("nvec", [33, 65])
 def test_hvp_vectors_per_thread(nvec):
     # two and four vectors per thread with one vector left over, a ragged last block, several types: each
