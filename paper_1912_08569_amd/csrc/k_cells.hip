@@ -30,16 +30,19 @@ __global__ __launch_bounds__(kBlock) void k_clear_counts(int* __restrict__ p, in
 __global__ void k_status_begin(int* status, int mode) { status_begin(status, mode); }
 
 // cell key of every particle and its arrival rank inside the cell
+__device__ __forceinline__ int cell_key(const float4& p, const Box& b, const Grid& g) {
+    const int cx = cell_coord(p.x, b.hf[0], g.inv_w[0], g.nc[0]);
+    const int cy = cell_coord(p.y, b.hf[1], g.inv_w[1], g.nc[1]);
+    const int cz = cell_coord(p.z, b.hf[2], g.inv_w[2], g.nc[2]);
+    return (int)morton3(cx, cy, cz);
+}
+
 __global__ __launch_bounds__(kBlock) void k_bin(const float4* __restrict__ pos, int N, Box b, Grid g,
                                                int* __restrict__ counts, int* __restrict__ keys,
                                                int* __restrict__ rank) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
-    float4 p = pos[i];
-    int cx = cell_coord(p.x, b.hf[0], g.inv_w[0], g.nc[0]);
-    int cy = cell_coord(p.y, b.hf[1], g.inv_w[1], g.nc[1]);
-    int cz = cell_coord(p.z, b.hf[2], g.inv_w[2], g.nc[2]);
-    int key = (int)morton3(cx, cy, cz);
+    const int key = cell_key(pos[i], b, g);
     keys[i] = key;
     rank[i] = atomicAdd(&counts[key], 1);
 }
@@ -193,16 +196,20 @@ __global__ __launch_bounds__(kBlock) void k_scatter(const int* __restrict__ keys
 // is the number of smaller ones among the cell's few, counted here instead of in
 // a sorting launch of its own.  Writes are coalesced but for the order inside a
 // cell; the reads follow the previous order, which is close to the new one after
-// the first build.  The path lengths since the last list build (vel.w) restart at
+// the first build.  The particle's key is formed again from the position it has
+// read: another read in the previous order would fetch a line per particle when
+// that order is a new state's (1M of the assembly mixture in random order: 106 us
+// with the stored keys, 73.5 so; sorted, 28.5 and 27).  The path lengths since the last list build (vel.w) restart at
 // zero for the particles whose list is rebuilt; a batch replica that keeps its
 // list (build[r] == 0) keeps its order (order[q] == q) and its path lengths.
 // The temporaries are the state the rebuild leaves, which the driver restores
 // on a rollback.
 struct PermuteArgs {
     const int* order;
-    const int* keys;
     const int* cell_start;
     int N;
+    Box box;                // single systems; a batch's are its replicas'
+    Grid grid;
     const float4* pos;
     const float4* vel;
     const int4* image;
@@ -241,7 +248,13 @@ __global__ __launch_bounds__(kBlock) void k_permute(PermuteArgs a) {
     int d = q;
     if (rebuilt) {
         v.w = 0.0f;
-        const int k = a.keys[o];
+        int k;
+        if constexpr (BATCH) {
+            const RepDesc& d = a.rep[a.chunk_rep[q / kWave]];
+            k = (int)d.key_base + cell_key(p, d.box, d.grid);
+        } else {
+            k = cell_key(p, a.box, a.grid);
+        }
         const int s = a.cell_start[k] + shift, e = a.cell_start[k + 1] + shift;
         if (e - s > 1) {
             d = s;
@@ -282,11 +295,7 @@ __global__ __launch_bounds__(kBlock) void k_bin_batch(CellsArgsB a) {
     if (!rep_builds(a.build, r)) return;
     const RepDesc& d = a.rep[r];
     if (i >= d.off + d.n) return;
-    const float4 p = a.pos[i];
-    const int cx = cell_coord(p.x, d.box.hf[0], d.grid.inv_w[0], d.grid.nc[0]);
-    const int cy = cell_coord(p.y, d.box.hf[1], d.grid.inv_w[1], d.grid.nc[1]);
-    const int cz = cell_coord(p.z, d.box.hf[2], d.grid.inv_w[2], d.grid.nc[2]);
-    const int key = (int)(d.key_base + morton3(cx, cy, cz));
+    const int key = (int)d.key_base + cell_key(a.pos[i], d.box, d.grid);
     a.keys[i] = key;
     a.rank[i] = atomicAdd(&a.counts[key], 1);
 }
@@ -319,7 +328,6 @@ template <class Args>
 static PermuteArgs permute_args(const Args& a) {
     PermuteArgs p{};
     p.order = a.order;
-    p.keys = a.keys;
     p.cell_start = a.cell_start;
     p.N = a.N;
     p.pos = a.pos;
@@ -362,7 +370,10 @@ hipError_t launch_cells(const CellsArgs& a, hipStream_t s) {
     launch_scan(a.counts, nk, a.block_sums, a.cell_start, s);
     hipLaunchKernelGGL(k_scatter, dim3(nblk(a.N, kBlock)), dim3(kBlock), 0, s, a.keys, a.rank,
                        a.cell_start, a.N, a.order);
-    hipLaunchKernelGGL(k_permute<false>, dim3(nblk(a.N, kBlock)), dim3(kBlock), 0, s, permute_args(a));
+    PermuteArgs p = permute_args(a);
+    p.box = a.box;
+    p.grid = a.g;
+    hipLaunchKernelGGL(k_permute<false>, dim3(nblk(a.N, kBlock)), dim3(kBlock), 0, s, p);
     if (!a.list_follows)
         hipLaunchKernelGGL(k_copy_back, dim3(nblk(a.N, kBlock)), dim3(kBlock), 0, s, a.tpos, a.tvel, a.timage, a.pos,
                            a.vel, a.image, a.N);
