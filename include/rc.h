@@ -518,9 +518,10 @@ typedef struct rc_md_options {
                            max_chunk steps (rollbacks repair stale chunks)    */
     int one_block;      /* 1: with use_graph, a system of at most 1024 particles
                            (walk or sums form) with lists short enough for that
-                           to be faster runs each graph_steps-step replay as one
-                           launch of one workgroup that keeps the positions in
-                           LDS (same results, bit for bit); 0:
+                           to be faster runs the steps between log rows as
+                           launches of one workgroup, any number of steps each,
+                           that keep the positions in LDS (same results, bit for
+                           bit); 0:
                            hipGraphs only.  Ignored by rc_batch_run.          */
     int resume;         /* 1: the state owes its last step's final half kick
                            (it is what an earlier call left when it returned an

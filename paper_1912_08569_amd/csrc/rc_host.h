@@ -230,8 +230,8 @@ struct DriveOps {
     virtual int reduce_ev(int row) = 0;
     // the kernels of a plain step (launched and replayed)
     virtual StepKernel plain_step() = 0;
-    // whether graph replays may run as one-workgroup launches of G steps, and
-    // such a launch (a: launch arguments of the replay's first step)
+    // whether stretches of plain steps may run as one-workgroup launches, and such a
+    // launch of any number of steps (a: launch arguments of its first step)
     virtual bool block_ok() { return false; }
     // where the last rebuild left a copy of the state it produced (positions,
     // velocities with stale path lengths, images or NULL), if it does: the
