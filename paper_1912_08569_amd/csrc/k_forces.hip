@@ -77,18 +77,23 @@ __global__ __launch_bounds__(kWave) void k_forces_gather(ForceArgs a) {
 // one product.  It leaves with global atomics, or stays in LDS for a partner
 // among the wavefront's own 64.  Those atomics bound the kernel: with the six
 // of every triplet it took 142 us at 200003 particles of three types, 90 of
-// them in the atomics; now 71 (20 without them).  The pool is filled while the
-// entries are summed when the wavefront's swap ranges fit it, else in rounds
-// by walks of the lists.
+// them in the atomics (20 without any).  An instruction's atomics go out as one
+// request per line they touch, so the centres' rows leave as 64 consecutive
+// floats per instruction, and (SPREAD) the partners' rows by four lanes each: 71
+// -> 60 us, and 1000003 of the assembly mixture, which has few partners, 88 -> 69
+// per call.  The XCD-aware block order gained nothing on top.  The pool is filled
+// while the entries are summed when the wavefront's swap ranges fit it, else in
+// rounds by walks of the lists.
 // ---------------------------------------------------------------------------
 constexpr int kPool = 512;   // staged partners per wave and round
 
+template <bool SPREAD>
 __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_ev) {
     constexpr int PL = 2, W = PL * kWave;   // entries per lane and pass
     extern __shared__ DevEntry s_tab[];
     __shared__ int p_j[kPool];
     __shared__ float p_w[kPool], p_g[kPool], p_dx[kPool], p_dy[kPool], p_dz[kPool], p_s[kPool];
-    __shared__ int l_pool[kWave], l_k[kWave], l_tri[kWave + 1];
+    __shared__ int l_pool[kWave], l_k[kWave], l_tri[kWave + 1], l_out;
     __shared__ float l_f[kWave][4];
     __shared__ int s_off[kWave], s_ns[kWave], s_j[W];
     __shared__ unsigned char s_own[W];
@@ -241,6 +246,7 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
         if (mine)
             for (int q = pool; q < pool + k; ++q) p_s[q] = 0.0f;
         l_k[lane] = mine ? k : 0;
+        if (SPREAD && lane == 0) l_out = 0;
         __syncthreads();
         const int T = l_tri[kWave];
         for (int t = lane; t < T; t += kWave) {
@@ -270,21 +276,37 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
             w6[5] += ca * p_dy[qa] * p_dz[qa] + cb * p_dy[qb] * p_dz[qb];
         }
         __syncthreads();
+        int* out = reinterpret_cast<int*>(p_w);   // read for the last time above
         if (mine) {   // the forces on the centre's partners, and minus their sum on the centre
             for (int q = pool; q < pool + k; ++q) {
                 const float c = -p_g[q] * p_s[q];
                 if (c == 0.0f) continue;   // a bonded partner (w' = 0): most of them
                 const float gx = c * p_dx[q], gy = c * p_dy[q], gz = c * p_dz[q];
                 const unsigned lj = (unsigned)(p_j[q] - (i - lane));
-                float* F = lj < (unsigned)kWave ? l_f[lj] : reinterpret_cast<float*>(a.force + p_j[q]);
-                atomicAdd(F + 0, gx);
-                atomicAdd(F + 1, gy);
-                atomicAdd(F + 2, gz);
+                if (!SPREAD || lj < (unsigned)kWave) {
+                    float* F = lj < (unsigned)kWave ? l_f[lj] : reinterpret_cast<float*>(a.force + p_j[q]);
+                    atomicAdd(F + 0, gx);
+                    atomicAdd(F + 1, gy);
+                    atomicAdd(F + 2, gz);
+                } else {   // noted for the wavefront to send
+                    p_dx[q] = gx;
+                    p_dy[q] = gy;
+                    p_dz[q] = gz;
+                    out[atomicAdd(&l_out, 1)] = q;
+                }
                 fx -= gx;
                 fy -= gy;
                 fz -= gz;
             }
             done = true;
+        }
+        if constexpr (SPREAD) {
+            __syncthreads();
+            for (int t = lane; t < 4 * l_out; t += kWave) {
+                const int q = out[t >> 2], x = t & 3;
+                const float g = x == 0 ? p_dx[q] : x == 1 ? p_dy[q] : p_dz[q];
+                if (x < 3) atomicAdd(reinterpret_cast<float*>(a.force + p_j[q]) + x, g);
+            }
         }
         __syncthreads();
         round_start = next;
@@ -294,14 +316,20 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     fy += l_f[lane][1];
     fz += l_f[lane][2];
     en += l_f[lane][3];
-    if (live) {
-        float* Fi = reinterpret_cast<float*>(a.force + i);
-        atomicAdd(Fi + 0, fx);
-        atomicAdd(Fi + 1, fy);
-        atomicAdd(Fi + 2, fz);
-        atomicAdd(Fi + 3, en);
-        if (a.status && !(isfinite(fx) && isfinite(fy) && isfinite(fz)))
-            atomicOr(&a.status[RC_ST_FLAGS], RC_FLAG_NONFINITE);
+    if (live && a.status && !(isfinite(fx) && isfinite(fy) && isfinite(fz)))
+        atomicOr(&a.status[RC_ST_FLAGS], RC_FLAG_NONFINITE);
+    // the wavefront's 64 rows as they lie in memory, 64 consecutive floats per instruction
+    l_f[lane][0] = fx;
+    l_f[lane][1] = fy;
+    l_f[lane][2] = fz;
+    l_f[lane][3] = en;
+    __syncthreads();
+    float* F0 = reinterpret_cast<float*>(a.force + (i - lane));
+    const int words = 4 * min(kWave, a.N - (i - lane));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int at = q * kWave + lane;
+        if (at < words) atomicAdd(F0 + at, (&l_f[0][0])[at]);
     }
     if (want_ev) {
         double v[7] = {en, w6[0], w6[1], w6[2], w6[3], w6[4], w6[5]};
@@ -324,8 +352,12 @@ hipError_t launch_forces_triplet(const ForceArgs& a, hipStream_t s) {
         hipLaunchKernelGGL(k_zero_f4, dim3(std::min(nblk(a.N, kBlock), 4096)), dim3(kBlock), 0, s,
                            a.force, a.N);
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
-    hipLaunchKernelGGL(k_forces_triplet, dim3(nblk(a.N, kWave)), dim3(kWave), shm, s, a,
-                       a.ev_part ? 1 : 0);
+    // sending the partners' forces together costs a barrier and pays where the atomics are the bound: us per call
+    // apart and together, 32768 unequal 24.2, 24.8, 8000 22.7, 23.4; 200003 unequal 73.3, 68.0, reactive 53.8, 50.4
+    if (a.N >= 65536)
+        hipLaunchKernelGGL(k_forces_triplet<true>, dim3(nblk(a.N, kWave)), dim3(kWave), shm, s, a, a.ev_part ? 1 : 0);
+    else
+        hipLaunchKernelGGL(k_forces_triplet<false>, dim3(nblk(a.N, kWave)), dim3(kWave), shm, s, a, a.ev_part ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -91,6 +91,29 @@ def test_forces_per_wavefront(N, density, gather):
     assert_virial(ev[1:7].cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("N,density", [(65535, 0.25), (65536, 0.25), (65601, 0.25), (65537, 0.6)])
+def test_triplet_kernel_sends_partner_forces(N, density):
+    # partners' forces sent one by one (below 65536 particles) and a row at a time: ragged last wavefronts,
+    # swap ranges that fit the pools and (density 0.6) do not, adding to what is there
+    from oracle import swap_ref
+    from paper_1912_08569_amd import System, api
+    from paper_1912_08569_amd import _lib as rcl
+    from parity_util import assert_energy, assert_forces, assert_pe, assert_virial
+    s = W.small_reactive(N=N, density=density, seed=N, min_dist=0.85)
+    S = System.from_workload(s)
+    F, ev = S.compute_forces(gather=False)
+    x, _, _, ty = S.state_by_tag()
+    ref = swap_ref.evaluate(x, ty, s.L, s.table)
+    f = S.by_tag(F)
+    assert_forces(f, ref)
+    assert_pe(f[:, 3], ref)
+    assert_energy(float(ev[0]), ref)
+    assert_virial(ev[1:7].cpu().numpy(), ref)
+    A = F.clone()
+    api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, A, None, rcl.RC_FORCE_ACCUMULATE, S.status)
+    assert_forces(S.by_tag(A * 0.5), ref)
+
+
 def _step_system(name):
     kind, n = name.split("-")
     n = int(n)
