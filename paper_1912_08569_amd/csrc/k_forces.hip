@@ -1440,6 +1440,14 @@ hipError_t launch_add_step(unsigned long long* p, unsigned long long v, hipStrea
     hipLaunchKernelGGL(k_add_step, dim3(1), dim3(1), 0, s, p, v);
     return hipGetLastError();
 }
+// The module is loaded with the first use of one of its functions: 2.7 ms once per process, and a run that follows
+// within half a millisecond was seen to stall for 0.14 ms (20 steps of 1048576 particles after 5: 31.2-32.0 us per
+// step with the module loaded before, else 38.1-39.3 in most processes).  A context's creation asks for it, so that
+// no run pays.
+hipError_t load_step_kernels() {
+    hipFuncAttributes at{};
+    return hipFuncGetAttributes(&at, reinterpret_cast<const void*>(&k_add_step));
+}
 void add_step_kernel_info(const void** fn) { *fn = reinterpret_cast<const void*>(&k_add_step); }
 
 __global__ void k_set_step(unsigned long long* p, unsigned long long v) { *p = v; }

@@ -143,7 +143,7 @@ int rc_create(rc_ctx** out, int ntypes, const rc_pair_coeff* table, double r_buf
                   hipMemcpyHostToDevice) != hipSuccess ||
         hipMalloc(&c->d_step_base, 2 * sizeof(unsigned long long)) != hipSuccess ||
         hipMalloc(&c->d_slices, sizeof(double) * kRowSlices) != hipSuccess ||
-        noalloc_scratch_here(c->device, &c->noalloc_scratch) != hipSuccess ||
+        noalloc_scratch_here(c->device, &c->noalloc_scratch) != hipSuccess || load_step_kernels() != hipSuccess ||
         // the private stream the driver's rebuild graphs are recorded on: created here, as creating a
         // stream takes milliseconds (3-5 ms measured), which a run recording its first graph would pay
         hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) {

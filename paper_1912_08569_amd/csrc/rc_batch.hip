@@ -185,7 +185,7 @@ int rc_batch_create(rc_batch** out, int R, int ntypes, const rc_pair_coeff* tabl
         for (int q = b->offsets[r] / kWave; q < b->offsets[r + 1] / kWave; ++q) chunk_rep[q] = r;
     }
     b->seeds.assign(R, 0);
-    bool ok = hipGetDevice(&c->device) == hipSuccess &&
+    bool ok = hipGetDevice(&c->device) == hipSuccess && load_step_kernels() == hipSuccess &&
               hipMalloc(&c->d_tab, sizeof(DevEntry) * (size_t)R * nt2) == hipSuccess &&
               hipMemcpy(c->d_tab, c->host_tab.data(), sizeof(DevEntry) * (size_t)R * nt2, hipMemcpyHostToDevice) ==
                   hipSuccess &&

@@ -469,6 +469,8 @@ struct StepArgs {
 };
 
 hipError_t launch_step(const StepArgs& a, bool ev, hipStream_t s);
+// loads the module of the step, force and status kernels, which else the process's first launch of one of them does
+hipError_t load_step_kernels();
 // a plain step launch with its kernels between event pairs (sums: [2] or NULL, step: [2])
 hipError_t launch_step_timed(const StepArgs& a, bool batch, hipStream_t s, hipEvent_t* sums, hipEvent_t* step);
 // Small systems (at most kBlockMaxN particles, single system, walk or sums
