@@ -7,6 +7,7 @@ current HIP stream; all arithmetic happens in ``librc.so``.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 from typing import Optional, Sequence
 
@@ -42,6 +43,16 @@ def _ptr(t: Optional[torch.Tensor]):
 def _stream(stream=None):
     s = torch.cuda.current_stream() if stream is None else stream
     return ctypes.c_void_p(s.cuda_stream)
+
+
+def _on(stream):
+    """The context in which tensors for a call on `stream` are made: their memory then comes from that stream's
+    share of torch's pool, not from blocks that work still queued on the caller's current stream may be using."""
+    if stream is None:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    return torch.cuda.stream(stream)
 
 
 def box(edges) -> L.Box:
@@ -253,7 +264,8 @@ def rc_to_tags(ctx: Context, arr, rtag, negate=False, stream=None) -> torch.Tens
     N = rtag.shape[0]
     if arr.shape != (N, 4) or arr.dtype != torch.float32:
         raise ValueError("arr must be (N, 4) float32")
-    out = torch.empty((N, 3), dtype=torch.float32, device=arr.device)
+    with _on(stream):
+        out = torch.empty((N, 3), dtype=torch.float32, device=arr.device)
     check(L.load().rc_to_tags(ctx.handle, _ptr(arr), _ptr(rtag), N, int(negate), _ptr(out), _stream(stream)), ctx.handle)
     return out
 
@@ -262,7 +274,8 @@ def rc_from_tags(ctx: Context, v, pos, stream=None) -> torch.Tensor:
     """(N, 4) in engine order (w = 0) from v (N, 3) float32 by tag."""
     if v.shape != (pos.shape[0], 3) or v.dtype != torch.float32:
         raise ValueError("v must be (N, 3) float32")
-    out = torch.empty_like(pos)
+    with _on(stream):
+        out = torch.empty_like(pos)
     check(L.load().rc_from_tags(ctx.handle, _ptr(v), _ptr(pos), pos.shape[0], _ptr(out), _stream(stream)), ctx.handle)
     return out
 
@@ -313,7 +326,8 @@ def rc_batch_set_workspace(bc: "BatchContext", ws: Optional[torch.Tensor], k_max
 def rc_thermostat_normals(seed, step0, steps, N, dim=3, device="cuda", stream=None) -> torch.Tensor:
     """(steps, N, 4) float32 device tensor: the integrators' thermostat normals of tags 0..N-1 at steps
     step0 .. step0 + steps - 1 (w = 0)."""
-    out = torch.empty((int(steps), int(N), 4), dtype=torch.float32, device=device)
+    with _on(stream):
+        out = torch.empty((int(steps), int(N), 4), dtype=torch.float32, device=device)
     code = L.load().rc_thermostat_normals(int(seed), int(step0), int(steps), int(N), int(dim), _ptr(out),
                                           _stream(stream))
     if code != L.RC_OK:
@@ -399,9 +413,8 @@ def rc_stress_autocorrelation(ctx: Context, rows, volume, kT, max_lag, G, stream
     T, need = int(rows.shape[0]), ctypes.c_size_t()
     ws = None
     if L.load().rc_stress_workspace_bytes(T, int(max_lag), ctypes.byref(need)) == L.RC_OK and need.value:
-        ws = torch.empty(need.value, dtype=torch.uint8, device=rows.device)
-        if stream is not None:
-            ws.record_stream(stream)
+        with _on(stream):
+            ws = torch.empty(need.value, dtype=torch.uint8, device=rows.device)
     check(L.load().rc_stress_autocorrelation_ws(ctx.handle, _ptr(rows), T, float(volume), float(kT), int(max_lag),
                                                 _ptr(G), _ptr(ws), need.value, _stream(stream)), ctx.handle)
 

@@ -1,0 +1,50 @@
+"""Calls on a stream other than the current one: what they allocate belongs to that stream, and the results are the
+same as on the current one."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from paper_1912_08569_amd import System, api
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def system():
+    S = System.from_workload(W.small_reactive(N=1000, density=0.2, seed=9))
+    S.build()
+    return S
+
+
+CALLS = {
+    # 3000 rows and 700 lags: the form of the autocorrelation that takes scratch
+    "stress": lambda S, x, stream: api.rc_stress_autocorrelation(S.ctx, x["rows"], 900.0, 1.0, 700, x["G"],
+                                                                 stream=stream) or x["G"],
+    "to_tags": lambda S, x, stream: api.rc_to_tags(S.ctx, S.pos, S.rtag, stream=stream),
+    "from_tags": lambda S, x, stream: api.rc_from_tags(S.ctx, x["v"], S.pos, stream=stream),
+    "normals": lambda S, x, stream: api.rc_thermostat_normals(3, 0, 2, 1000, stream=stream),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CALLS))
+def test_side_stream(system, name, monkeypatch):
+    S = system
+    rng = np.random.default_rng(2)
+    x = dict(rows=torch.from_numpy(rng.standard_normal((3000, 13))).cuda(),
+             G=torch.zeros(701, dtype=torch.float64, device="cuda"),
+             v=torch.from_numpy(rng.standard_normal((S.N, 3)).astype(np.float32)).cuda())
+    want = CALLS[name](S, x, None).clone()
+    side = torch.cuda.Stream()
+    made = []
+    for fn in ("empty", "empty_like"):
+        real = getattr(torch, fn)
+        monkeypatch.setattr(torch, fn, lambda *a, _real=real, **k: (made.append(torch.cuda.current_stream()),
+                                                                    _real(*a, **k))[1])
+    side.wait_stream(torch.cuda.current_stream())
+    got = CALLS[name](S, x, side)
+    monkeypatch.undo()
+    torch.cuda.current_stream().wait_stream(side)
+    assert made and all(s == side for s in made)
+    assert torch.equal(got, want)
+    torch.cuda.synchronize()
