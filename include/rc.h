@@ -593,8 +593,9 @@ int rc_fene_forces(rc_ctx* ctx, const float* pos, int N, rc_box box, float* forc
 /* ---- tag-ordered views (device arrays of N particles) -------------------------
  * rc_load_by_tag: pos (float4, w = (tag << 4) | type, engine order) receives
  *   xyz [N*3] (by tag) folded into the box.
- * rc_load_moved: waits for the last rc_load_by_tag alone (not for work queued
- *   after it); *moved (host) is 1 when some particle was then farther than reach
+ * rc_load_moved: waits for the context's last rc_load_by_tag alone (not for
+ *   work queued after it, nor for another call's; RC_ERR_ARG when the context
+ *   made no load); *moved (host) is 1 when some particle was then farther than reach
  *   (minimum image) from ref [N*3] (by tag) and every distance was a number.
  * rc_to_tags: out[3t ..] = arr[rtag[t]] (float4 array in engine order, w dropped),
  *   negated if negate != 0.

@@ -322,14 +322,14 @@ extern "C" int rc_rigid_run(rc_ctx* c, float* pos, float* vel, float* force, int
     if (r) return r;
     if ((r = check_list(c, nlist, nn, k_max))) return r;
     if (reinterpret_cast<uintptr_t>(pos) & 15) return fail(c, RC_ERR_ARG, "positions not 16-byte aligned");
-    if ((r = ensure_host_words(c)) || (r = wait_event(c))) return r;
-    // every launch that writes the words has ended (a run waits for its own, a load's event was waited for)
-    volatile int* host = c->h_status + RC_STATUS_WORDS;
+    // (every launch that writes the words has ended: a run waits for its own)
+    if ((r = ensure_host_words(c)) || (r = wait_event(c, c->ev_sync))) return r;
+    volatile int* host = c->h_status + kRigidWords;
     host[0] = n_steps;
     host[1] = -1;
     host[2] = 0;
     a.stop = reinterpret_cast<int*>(c->d_step_base + 1);
-    a.host = c->h_status + RC_STATUS_WORDS;
+    a.host = c->h_status + kRigidWords;
     // p > soft in FP64 for an FP32 p: the largest FP32 value that is not above soft (never for NaN)
     a.soft = std::isnan(soft) ? INFINITY : (float)soft;
     if ((double)a.soft > soft) a.soft = std::nextafterf(a.soft, -INFINITY);

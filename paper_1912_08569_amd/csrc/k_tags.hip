@@ -92,22 +92,26 @@ extern "C" int rc_load_by_tag(rc_ctx* c, float* pos, const float* xyz, const flo
     int r = make_box(c, box, b);
     if (r || (r = ensure_host_words(c))) return r;
     hipStream_t s = S(stream);
-    if ((r = wait_event(c))) return r;   // an earlier load's words may not have been asked for
-    volatile int* host = c->h_status + RC_STATUS_WORDS;
+    if (c->ev_load) {   // an earlier load's words may not have been asked for
+        if ((r = wait_event(c, c->ev_load))) return r;
+    } else {
+        HIP_TRY(c, hipEventCreateWithFlags(&c->ev_load, hipEventDisableTiming));
+    }
+    volatile int* host = c->h_status + kLoadWords;
     host[0] = host[1] = 0;
     hipLaunchKernelGGL(k_load_by_tag, dim3(nblocks(N, kBlock)), dim3(kBlock), 0, s, reinterpret_cast<float4*>(pos), xyz,
-                       ref, N, b, (float)(reach * reach), c->h_status + RC_STATUS_WORDS);
+                       ref, N, b, (float)(reach * reach), c->h_status + kLoadWords);
     HIP_TRY(c, hipGetLastError());
-    HIP_TRY(c, hipEventRecord(c->ev_sync, s));
+    HIP_TRY(c, hipEventRecord(c->ev_load, s));
     return RC_OK;
 }
 
 extern "C" int rc_load_moved(rc_ctx* c, int* moved) {
     if (!c || !moved) return RC_ERR_ARG;
-    if (!c->h_status) return fail(c, RC_ERR_ARG, "rc_load_moved follows rc_load_by_tag");
-    int r = wait_event(c);
+    if (!c->ev_load) return fail(c, RC_ERR_ARG, "rc_load_moved follows rc_load_by_tag");
+    int r = wait_event(c, c->ev_load);
     if (r) return r;
-    const volatile int* host = c->h_status + RC_STATUS_WORDS;
+    const volatile int* host = c->h_status + kLoadWords;
     *moved = host[0] && !host[1];
     return RC_OK;
 }

@@ -107,6 +107,7 @@ struct rc_ctx {
     double fene_k = 0.0, fene_r0 = 0.0;
     int* h_status = nullptr;            // pinned: a status word's host copy (driver waits), then kHostWords more
     hipEvent_t ev_sync = nullptr;       // the driver's wait event (no timing)
+    hipEvent_t ev_load = nullptr;       // recorded behind the last rc_load_by_tag; NULL: none was made
     GraphCache gc;
     RebuildGraph rg[2];                 // the driver's rebuilds, one per position buffer
     hipStream_t cap_stream = nullptr;   // private stream the rebuild graphs are recorded on
@@ -168,12 +169,13 @@ int ensure_plist(rc_ctx* c, int N, int k_max);
 // the packed copy of (nlist, nn, k_max, N): made on the stream unless it is the current one
 int packed_list_for(rc_ctx* c, const int* nlist, const int* nn, int k_max, int N, hipStream_t s);
 void free_ctx_buffers(rc_ctx* c);       // every device buffer the context owns
-// the context's pinned host words (kHostWords that kernels write follow the status copy) and wait event
-constexpr int kHostWords = 8;
+// the context's pinned host words and wait event: the status copy, then kHostWords that kernels write,
+// a run of rigid bodies from kRigidWords on and a load by tag from kLoadWords on
+constexpr int kHostWords = 8, kRigidWords = RC_STATUS_WORDS, kLoadWords = RC_STATUS_WORDS + 4;
 int ensure_host_words(rc_ctx* c);
 // wait for everything queued on the stream so far
 int wait_spin(rc_ctx* c, hipStream_t s);
-int wait_event(rc_ctx* c);   // for what was queued when the wait event was last recorded
+int wait_event(rc_ctx* c, hipEvent_t ev);   // for what was queued when the event was last recorded
 // copy a device status word to the host and wait for it by spinning on an event
 int read_status_spin(rc_ctx* c, const int* d_status, int* hst, hipStream_t s);
 int ensure_blk(rc_ctx* c, int nb, hipStream_t s);

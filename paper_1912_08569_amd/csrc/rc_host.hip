@@ -171,13 +171,13 @@ int ensure_host_words(rc_ctx* c) {
 
 int wait_spin(rc_ctx* c, hipStream_t s) {
     HIP_TRY(c, hipEventRecord(c->ev_sync, s));
-    return wait_event(c);
+    return wait_event(c, c->ev_sync);
 }
 
-int wait_event(rc_ctx* c) {
+int wait_event(rc_ctx* c, hipEvent_t ev) {
     // a blocking synchronisation costs tens of microseconds of wake-up per call, so this spins on the event
     hipError_t e;
-    while ((e = hipEventQuery(c->ev_sync)) == hipErrorNotReady) {
+    while ((e = hipEventQuery(ev)) == hipErrorNotReady) {
     }
     if (e != hipSuccess) return hip_fail(c, e, "waiting for the stream");
     return RC_OK;
@@ -257,6 +257,8 @@ void free_ctx_buffers(rc_ctx* c) {
     c->pl_cap = 0;
     c->pl_nlist = nullptr;
     if (c->ev_sync) (void)hipEventDestroy(c->ev_sync);
+    if (c->ev_load) (void)hipEventDestroy(c->ev_load);
+    c->ev_load = nullptr;
     if (c->h_status) (void)hipHostFree(c->h_status);
     c->ev_sync = nullptr;
     c->h_status = nullptr;

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads as W
-from paper_1912_08569_amd import System, api
+from paper_1912_08569_amd import System, _lib as rcl, api
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +48,40 @@ def test_side_stream(system, name, monkeypatch):
     assert made and all(s == side for s in made)
     assert torch.equal(got, want)
     torch.cuda.synchronize()
+
+
+def test_moved_flag_is_the_last_loads(system):
+    """rc_load_moved answers for the context's last load, whatever other calls did to the words and events that they
+    share, and refuses a context that made none."""
+    S = system
+    cfg = S.integrator(dt=0.001, kT=0.1, gamma=1.0, seed=4)
+    S.run(4, cfg)
+    with pytest.raises(api.RcError) as e:
+        api.rc_load_moved(S.ctx)
+    assert e.value.code == rcl.RC_ERR_ARG
+    # a load that has not begun, and a status read on another stream meanwhile
+    pos = S.pos.clone()
+    ref = api.rc_to_tags(S.ctx, pos, S.rtag)
+    far = ref + 0.5
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(100_000_000)       # some tens of milliseconds
+        api.rc_load_by_tag(S.ctx, pos, far, ref, S.box, 0.1)
+    S.run(4, cfg, step0=4)
+    assert not side.query()                  # the load is still to come
+    assert api.rc_load_moved(S.ctx) is True
+    assert api.rc_load_moved(S.ctx) is True
+    torch.cuda.synchronize()
+
+
+def test_moved_flag_after_a_run_of_rigid_bodies():
+    from paper_1912_08569_amd import RigidBodies
+    s = W.patchy_mixture(seed=1014)
+    S = System.from_workload(s)
+    R = RigidBodies(S, s.meta["bodies"], s.meta["theta"], s.meta["omega"])
+    S.build()
+    x = api.rc_to_tags(S.ctx, S.pos, S.rtag)
+    api.rc_load_by_tag(S.ctx, S.pos, x, x, S.box, 0.1)
+    R.run(1, S.integrator(dt=0.001, kT=1.0, gamma=1.0, seed=21, dim=2))
+    assert api.rc_load_moved(S.ctx) is False
