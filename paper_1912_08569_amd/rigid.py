@@ -9,6 +9,7 @@ holds the body arrays and builds the lists in between.
 """
 from __future__ import annotations
 
+import operator
 import time
 
 import numpy as np
@@ -16,6 +17,10 @@ import torch
 
 from . import _lib as rcl
 from . import api
+
+
+#: steps of one library call at most: its count is a C int, and a signal is seen between calls only
+_CALL_STEPS = 1 << 20
 
 
 class RigidBodies:
@@ -35,6 +40,7 @@ class RigidBodies:
     def run(self, n_steps: int, cfg, step0: int = 0, soft_frac: float = 0.8) -> dict:
         """n_steps body steps (cfg: an integrator of dim 2); returns rebuild count and wall time."""
         S = self.S
+        n_steps = operator.index(n_steps)
         if not S.built:
             S.build()
         soft = 0.5 * S.r_buff * soft_frac
@@ -44,15 +50,16 @@ class RigidBodies:
         t0 = time.perf_counter()
         k, pending = 0, False
         while k < n_steps:
+            steps = min(n_steps - k, _CALL_STEPS)
             code, done = api.rc_rigid_run(S.ctx, S.pos, S.vel, S.force, S.image, S.rtag, S.nlist, S.nn, self.b,
-                                          self.theta, self.omega, S.box, cfg, step0 + k, n_steps - k, pending, soft,
+                                          self.theta, self.omega, S.box, cfg, step0 + k, steps, pending, soft,
                                           S.status)
             k += done
+            pending = done < steps
             if code != rcl.RC_OK:
                 raise RuntimeError(f"rigid bodies: non-finite state at step {step0 + k}")
-            if k < n_steps:      # step k has its first half and waits for a list
+            if pending:          # step k has its first half and waits for a list
                 S.build()
                 rebuilds += 1
-                pending = True
         torch.cuda.synchronize()
         return {"rebuilds": rebuilds, "seconds": time.perf_counter() - t0}

@@ -175,3 +175,34 @@ def test_rigid_run_equals_single_half_steps(B):
     for a, b in ((S.pos, T.pos), (S.vel, T.vel), (S.image, T.image), (R.theta, Q.theta), (R.omega, Q.omega),
                  (S.force, T.force)):
         assert bool((a == b).all())
+
+
+def test_rigid_run_step_counts(monkeypatch):
+    # a count that is no whole number is refused, a count past the library's is split, and a run split into
+    # short calls equals one call, bit for bit
+    from paper_1912_08569_amd import RigidBodies, System, api, rigid
+    bodies, theta, omega, pos, types, vel, L = _wheels(17, 1018)
+
+    def fresh():
+        S = System(pos, types, L, W.patchy_table(), vel=vel)
+        S.build()
+        return S, RigidBodies(S, bodies, theta, omega), S.integrator(dt=0.002, kT=1.0, gamma=1.0, seed=3, dim=2)
+
+    S, R, cfg = fresh()
+    for bad in (2.0, 2.5, "3"):
+        with pytest.raises(TypeError):
+            R.run(bad, cfg)
+    whole = R.run(np.int64(60), cfg)
+    T, Q, cfg = fresh()
+    monkeypatch.setattr(rigid, "_CALL_STEPS", 7)
+    parts = Q.run(60, cfg)
+    assert parts["rebuilds"] == whole["rebuilds"] >= 1
+    for a, b in ((S.pos, T.pos), (S.vel, T.vel), (S.image, T.image), (R.theta, Q.theta), (R.omega, Q.omega),
+                 (S.force, T.force)):
+        assert bool((a == b).all())
+    monkeypatch.undo()
+    asked = []
+    monkeypatch.setattr(api, "rc_rigid_run", lambda *a: (asked.append((a[13], a[14])), (0, a[14]))[1])
+    R.run(2 ** 31 + 5, cfg, step0=3)
+    assert max(n for _, n in asked) < 2 ** 31 and sum(n for _, n in asked) == 2 ** 31 + 5
+    assert [s for s, _ in asked] == list(range(3, 3 + 2 ** 31 + 5, asked[0][1]))
