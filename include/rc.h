@@ -449,7 +449,11 @@ int rc_stress_autocorrelation(rc_ctx* ctx, const double* rows /* device [T][13] 
                               double kT, int max_lag, double* G /* device [max_lag+1] */, void* stream);
 /* rc_stress_autocorrelation_ws: the same with caller-owned scratch (device, of
  * rc_stress_workspace_bytes, 8-byte aligned, free again once the call's work on
- * the stream is done; NULL: none), which past 256 lags is faster. */
+ * the stream is done; NULL: none).  It is used, and makes the call faster, past
+ * RC_STRESS_PLAIN_LAGS lags where T times the groups of that many lags (the last
+ * one counted whole) exceeds RC_STRESS_PLAIN_WORK. */
+#define RC_STRESS_PLAIN_LAGS 256
+#define RC_STRESS_PLAIN_WORK 10000
 int rc_stress_workspace_bytes(int T, int max_lag, size_t* bytes /* host */);
 int rc_stress_autocorrelation_ws(rc_ctx* ctx, const double* rows, int T, double volume, double kT, int max_lag,
                                  double* G, void* ws /* NULL ok */, size_t ws_bytes, void* stream);

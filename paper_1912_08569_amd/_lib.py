@@ -30,6 +30,7 @@ RC_MAX_TYPES = 16
 RC_STATUS_WORDS = 8
 RC_ST_NSWAP = 5
 RC_NOALLOC_MAX_N = 1048576
+RC_STRESS_PLAIN_LAGS, RC_STRESS_PLAIN_WORK = 256, 10000
 RC_ST_FLAGS, RC_ST_KMAX, RC_ST_MAXPATH, RC_ST_FIRST_SOFT, RC_ST_FIRST_HARD = 0, 1, 2, 3, 4
 RC_FLAG_NLIST_OVERFLOW, RC_FLAG_REBUILD, RC_FLAG_NONFINITE, RC_FLAG_LOST, RC_FLAG_STALE = 1, 2, 4, 8, 16
 RC_FORCE_ACCUMULATE, RC_FORCE_GATHER, RC_FORCE_SUMS = 1, 4, 8

@@ -411,8 +411,9 @@ def rc_stress_autocorrelation(ctx: Context, rows, volume, kT, max_lag, G, stream
     if rows.dim() != 2 or rows.shape[1] != 13 or G.numel() < max_lag + 1:
         raise ValueError("rows must be (T, 13), G at least max_lag + 1 long")
     T, need = int(rows.shape[0]), ctypes.c_size_t()
-    ws = None
-    if L.load().rc_stress_workspace_bytes(T, int(max_lag), ctypes.byref(need)) == L.RC_OK and need.value:
+    ws, groups = None, max_lag // L.RC_STRESS_PLAIN_LAGS + 1      # of the max_lag + 1 lags
+    if groups > 1 and T * groups > L.RC_STRESS_PLAIN_WORK and \
+            L.load().rc_stress_workspace_bytes(T, int(max_lag), ctypes.byref(need)) == L.RC_OK:
         with _on(stream):
             ws = torch.empty(need.value, dtype=torch.uint8, device=rows.device)
     check(L.load().rc_stress_autocorrelation_ws(ctx.handle, _ptr(rows), T, float(volume), float(kT), int(max_lag),

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kBlock) void k_stress_rows(const double* __restrict
 }
 
 // One block per lag, from the rows: the better form for at most one lag per CU (100000 rows, 101 lags 148 us,
-// 2000 rows 7.7; from the stresses of a launch before 156 and 11).
+// 2000 rows 7.7; from the stresses of a launch before 156 and 11), and for short series (plain_stress).
 __global__ __launch_bounds__(kBlock) void k_stress_acf_few(const double* __restrict__ rows, int T, double inv_v,
                                                            double v_over_kt, double* __restrict__ G) {
     const int t = blockIdx.x;  // lag
@@ -172,20 +172,20 @@ __global__ __launch_bounds__(kAcfThreads) void k_stress_acf(const double* __rest
             if (own >= kChunk || i0 + lag >= T) continue;
             if (i0 + kOwn - 1 + lag + kAcfLags - 1 < T) {   // every product of the thread exists
                 double a[kOwn], b[kOwn + kAcfLags - 1];
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < kOwn; ++u) a[u] = s_a[at(own) + u];
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < kOwn + kAcfLags - 1; ++u) b[u] = s_b[at(off) + at(u)];
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < kOwn; ++u)
-    #pragma unroll
+#pragma unroll
                     for (int l = 0; l < kAcfLags; ++l) acc[l] += a[u] * b[u + l];
             } else {   // products past the series' end are cleared bitwise (whatever they are; no branches)
                 const int live = T - i0 - lag;   // row u + l of the thread's lags exists when below this
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < kOwn; ++u) {
                     const double a = s_a[at(own) + u];
-    #pragma unroll
+#pragma unroll
                     for (int l = 0; l < kAcfLags; ++l) {
                         const long long p = __double_as_longlong(a * s_b[at(off) + at(u + l)]);
                         acc[l] += __longlong_as_double(p & (long long)((u + l - live) >> 31));
@@ -215,7 +215,17 @@ __global__ __launch_bounds__(kBlock) void k_stress_sum(const double* __restrict_
 }
 
 size_t stress_scratch_doubles(int T, int max_lag) {
-    return max_lag < 256 ? 0 : 3 * ((size_t)T + (size_t)max_lag + 1);
+    return max_lag < RC_STRESS_PLAIN_LAGS ? 0 : 3 * ((size_t)T + (size_t)max_lag + 1);
+}
+
+// Whether a block per lag takes the series.  Its time goes with the rows times the rounds of 256 lags; the tiles take
+// three launches and a scratch whatever the length, and a few dozen blocks when it is short.  us, kernels and whole
+// call from host rows, a block per lag and tiles: (rows, lags) (1000, 256) 4.3 and 52, 9.4 and 62; (2000, 500) 7.5 and
+// 58, 9.6 and 63; (3000, 750) 14.7 and 68, 10.9 and 68; (5000, 416) 15.3 and 75, 12.0 and 76; (5000, 625) 22 and 83,
+// 12.2 and 76; (7000, 256) 19 and 85, 13.2 and 83; (20000, 1000) 122 and 245, 21 and 137.
+static bool plain_stress(int T, int n) {
+    constexpr int g = RC_STRESS_PLAIN_LAGS;
+    return n <= g || (long long)T * nblk(n, g) <= RC_STRESS_PLAIN_WORK;
 }
 
 hipError_t launch_stress_acf(const double* rows, int T, double volume, double kT, int max_lag, double* G,
@@ -223,7 +233,7 @@ hipError_t launch_stress_acf(const double* rows, int T, double volume, double kT
     const int n = max_lag + 1;
     const double inv_v = 1.0 / volume, v_over_kt = volume / kT;
     const dim3 tiles(nblk(n, 2 * kAcfLags), 3), threads(kAcfThreads);
-    if (n <= 256) {
+    if (plain_stress(T, n)) {
         hipLaunchKernelGGL(k_stress_acf_few, dim3(n), dim3(kBlock), 0, s, rows, T, inv_v, v_over_kt, G);
     } else if (!scratch) {
         hipLaunchKernelGGL(k_stress_acf<true>, dim3(tiles.x), threads, 0, s, rows, T, max_lag, inv_v, v_over_kt, G);

@@ -655,7 +655,7 @@ hipError_t launch_hvp(const HvpArgs& a, hipStream_t s);
 // device counts) and the stress autocorrelation of T logged rows (G: max_lag + 1 device doubles)
 hipError_t launch_partner_counts(const int* p0, const int* pt, const unsigned char* sel, int N,
                                  unsigned long long* part, unsigned long long* out, hipStream_t s);
-// scratch: stress_scratch_doubles doubles, or NULL for the form that needs none (slower past 256 lags)
+// scratch: stress_scratch_doubles doubles, or NULL for the forms that need none (slower for long series)
 hipError_t launch_stress_acf(const double* rows, int T, double volume, double kT, int max_lag, double* G,
                              double* scratch, hipStream_t s);
 size_t stress_scratch_doubles(int T, int max_lag);

@@ -56,6 +56,26 @@ def test_stress_autocorrelation_without_scratch(T, max_lag):
     assert rcl.load().rc_stress_autocorrelation_ws(*args, api._ptr(r), 8, api._stream()) == rcl.RC_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("T,max_lag,plain", [
+    (1000, 256, True), (2000, 400, True), (5000, 511, True), (5001, 511, False), (5000, 512, False),
+    (3333, 767, True), (3334, 767, False), (10001, 255, True), (40, 30, True)])
+def test_stress_autocorrelation_of_short_series(T, max_lag, plain, monkeypatch):
+    # a block per lag (no scratch is made) or tiles of lags, at the limits of rows times groups of 256 lags; FP64
+    # sums of n = 3 (T - t) products in another order: |difference| <= 2 n u sum |products|
+    from paper_1912_08569_amd import System
+    S = System.from_workload(W.small_reactive(N=300, density=0.2, seed=1))
+    V = float(S.edges[0]) ** 3
+    rows = np.random.default_rng(T).standard_normal((T, 13)) * 50.0
+    made, real = [], torch.empty
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: (made.append(k.get("dtype")), real(*a, **k))[1])
+    G = S.stress_autocorrelation(rows, 0.7, max_lag)
+    assert (torch.uint8 in made) is not plain
+    s = observables_ref.shear_stress(rows, V)
+    for t in range(max_lag + 1):
+        p, n = s[:T - t] * s[t:], 3 * (T - t)
+        assert abs(G[t] - V / 0.7 * p.sum() / n) <= 2 * (n + 8) * 2.0 ** -53 * V / 0.7 * np.abs(p).sum() / n, t
+
+
 @pytest.mark.parametrize("nvec", [33, 65])
 def test_hvp_vectors_per_thread(nvec):
     # two and four vectors per thread with one vector left over, a ragged last block, several types: each

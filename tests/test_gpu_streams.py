@@ -18,7 +18,7 @@ def system():
 
 
 CALLS = {
-    # 3000 rows and 700 lags: the form of the autocorrelation that takes scratch
+    # 6000 rows and 700 lags: the form of the autocorrelation that takes scratch
     "stress": lambda S, x, stream: api.rc_stress_autocorrelation(S.ctx, x["rows"], 900.0, 1.0, 700, x["G"],
                                                                  stream=stream) or x["G"],
     "to_tags": lambda S, x, stream: api.rc_to_tags(S.ctx, S.pos, S.rtag, stream=stream),
@@ -31,7 +31,7 @@ CALLS = {
 def test_side_stream(system, name, monkeypatch):
     S = system
     rng = np.random.default_rng(2)
-    x = dict(rows=torch.from_numpy(rng.standard_normal((3000, 13))).cuda(),
+    x = dict(rows=torch.from_numpy(rng.standard_normal((6000, 13))).cuda(),
              G=torch.zeros(701, dtype=torch.float64, device="cuda"),
              v=torch.from_numpy(rng.standard_normal((S.N, 3)).astype(np.float32)).cuda())
     want = CALLS[name](S, x, None).clone()
