@@ -43,6 +43,8 @@ class System:
         self.device = torch.device(device)
         self.step_form = step_form
         self.ctx = api.Context(table, r_buff)
+        if step_form in ("walk", "sums"):
+            self.ctx.set_step_form(step_form)
         self.r_buff = float(r_buff)
         self.table = table
         self.N = int(np.asarray(pos).shape[0])
