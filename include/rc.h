@@ -94,6 +94,7 @@ extern "C" {
 #define RC_ST_FIRST_HARD 4   /* first step whose force used a stale list           */
 #define RC_ST_NSWAP      5   /* swap-range entries of the last list build (sum over
                                 particles, saturating at 2^31 - 1)                 */
+#define RC_ST_NLIST      6   /* all list entries of the last list build (as NSWAP) */
 #define RC_FLAG_NLIST_OVERFLOW 1
 #define RC_FLAG_REBUILD        2   /* a path length passed the soft skin threshold     */
 #define RC_FLAG_NONFINITE      4
@@ -163,6 +164,12 @@ int rc_get_rlist(const rc_ctx* ctx, int a, int b, double* r_list);
  * order, so results are bit-identical.  (Systems too small to fill the GPU
  * take one entry per lane whatever the width.)  RC_ERR_ARG for other values.        */
 int rc_set_gather_width(rc_ctx* ctx, int width);
+/* Mean list entries per particle (status[RC_ST_NLIST] / N) of the list that the
+ * context's next calls use, by which they choose among kernels of equal results:
+ * a tuning knob only.  rc_md_run goes on with those of the builds it does.
+ * Negative: not known (the value of a uniform system at the given N and box is
+ * guessed at), as for a new context.  RC_ERR_ARG for NaN.                     */
+int rc_set_list_length(rc_ctx* ctx, double entries);
 /* How the fused step (and rc_compute_forces with RC_FORCE_SUMS) evaluates
  * the three-body forces of eq. (3bp):
  *   RC_FORM_WALK (default): one pass; the part of the force on m that comes

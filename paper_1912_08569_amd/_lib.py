@@ -28,7 +28,7 @@ RC_KIND_NONE, RC_KIND_SWAP, RC_KIND_WCA = 0, 1, 2
 RC_TYPE_BITS = 4
 RC_MAX_TYPES = 16
 RC_STATUS_WORDS = 8
-RC_ST_NSWAP = 5
+RC_ST_NSWAP, RC_ST_NLIST = 5, 6
 RC_NOALLOC_MAX_N = 1048576
 RC_STRESS_PLAIN_LAGS, RC_STRESS_PLAIN_WORK = 256, 10000
 RC_ST_FLAGS, RC_ST_KMAX, RC_ST_MAXPATH, RC_ST_FIRST_SOFT, RC_ST_FIRST_HARD = 0, 1, 2, 3, 4
@@ -110,6 +110,7 @@ _SIGS = {
     "rc_set_gather_width": ([_VP, _I], _I),
     "rc_set_step_form": ([_VP, _I], _I),
     "rc_clear_status": ([_VP, _VP], _I),
+    "rc_set_list_length": ([_VP, _D], _I),
     "rc_read_status": ([_VP, ctypes.POINTER(_I), _VP], _I),
     "rc_cells_workspace_bytes": ([_VP, _I, Box, ctypes.POINTER(ctypes.c_size_t)], _I),
     "rc_build_cells": ([_VP, _VP, _VP, _VP, _VP, _I, Box, _VP, ctypes.c_size_t, _VP], _I),

@@ -143,6 +143,10 @@ class Context:
     def set_gather_width(self, width: int):
         check(L.load().rc_set_gather_width(self.handle, int(width)), self.handle)
 
+    def set_list_length(self, entries: float):
+        """Mean list entries per particle of the list in use (negative: not known): the choice of kernels only."""
+        check(L.load().rc_set_list_length(self.handle, float(entries)), self.handle)
+
     def workspace_bytes(self, N: int, k_max: int, nvec: int = 1) -> int:
         return rc_workspace_bytes(self, N, k_max, nvec)
 

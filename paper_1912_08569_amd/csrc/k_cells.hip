@@ -17,6 +17,7 @@ __device__ __forceinline__ void status_begin(int* st, int mode) {
         }
     }
     st[RC_ST_NSWAP] = 0;
+    st[RC_ST_NLIST] = 0;
 }
 
 // counts cleared (n a multiple of 4); with status, its words for the list build that follows
@@ -579,80 +580,89 @@ __device__ __forceinline__ int list_one(int i, const float4& pi, const Box& b, c
     return list_scan<true>(i, pi, b, g, key_base, shift, cell_start, pos, nt, k_max, N, nlist, nn, rl);
 }
 
-// The list's status words: KMAX and the overflow flag from the largest list, NSWAP the swap ranges' entries
-// (saturating).  A launch of at most kStatusBlocks blocks sets them by atomics as its blocks end; the blocks of
+// The list's status words: KMAX and the overflow flag from the largest list, NSWAP the swap ranges' entries and
+// NLIST all entries (saturating).  A launch of at most kStatusBlocks blocks sets them by atomics as its blocks end; the blocks of
 // a larger one leave their values to k_list_status, since atomics on one address follow each other about 45 ns
 // apart (the list kernel at 1M particles, 3907 blocks: 80 us with them left to a launch of 4 us, 262 with atomics).
 constexpr int kStatusBlocks = 64;
 
 template <int THREADS = kBlock>   // of the block, which take part
-__device__ __forceinline__ void block_list_status(int cnt, int ns, int* status, int k_max, int2* per_block) {
+__device__ __forceinline__ void block_list_status(int cnt, int packed, int* status, int k_max, int4* per_block) {
     constexpr int W = THREADS / kWave;
-    __shared__ int s_m[W], s_n[W];
-    int m = cnt, t_ns = ns;
+    __shared__ int s_m[W], s_n[W], s_a[W];
+    int m = cnt, t_ns = nn_swap(packed), t_all = t_ns + nn_other(packed);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         m = max(m, __shfl_xor(m, o, kWave));
         t_ns += __shfl_xor(t_ns, o, kWave);
+        t_all += __shfl_xor(t_all, o, kWave);
     }
     if (W > 1) {
         if ((threadIdx.x & (kWave - 1)) == 0) {
             s_m[threadIdx.x / kWave] = m;
             s_n[threadIdx.x / kWave] = t_ns;
+            s_a[threadIdx.x / kWave] = t_all;
         }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        int t = m, u = t_ns;
+        int t = m, u = t_ns, a = t_all;
 #pragma unroll
         for (int w = 1; w < W; ++w) {
             t = max(t, s_m[w]);
             u += s_n[w];
+            a += s_a[w];
         }
         if (gridDim.x > kStatusBlocks) {
-            per_block[blockIdx.x] = make_int2(t, u);
-        } else {   // at most 64 blocks of 256 lists of 512 entries: the sum fits
+            per_block[blockIdx.x] = make_int4(t, u, a, 0);
+        } else {   // at most 64 blocks of 256 lists of 512 entries: the sums fit
             atomicMax(&status[RC_ST_KMAX], t);
             if (t > k_max) atomicOr(&status[RC_ST_FLAGS], RC_FLAG_NLIST_OVERFLOW);
             atomicAdd(&status[RC_ST_NSWAP], u);
+            atomicAdd(&status[RC_ST_NLIST], a);
         }
     }
 }
 
-__global__ __launch_bounds__(1024) void k_list_status(const int2* __restrict__ per_block, int nb, int k_max,
+__global__ __launch_bounds__(1024) void k_list_status(const int4* __restrict__ per_block, int nb, int k_max,
                                                      int* __restrict__ status) {
     __shared__ int red[1024 / kWave];
-    __shared__ long long red_ns[1024 / kWave];
+    __shared__ long long red_ns[1024 / kWave], red_all[1024 / kWave];
     int m = 0;
-    long long t = 0;
+    long long t = 0, all = 0;
     for (int b = threadIdx.x; b < nb; b += 4 * 1024) {   // four reads under way
-        int2 v[4];
+        int4 v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = b + u * 1024 < nb ? per_block[b + u * 1024] : make_int2(0, 0);
+        for (int u = 0; u < 4; ++u) v[u] = b + u * 1024 < nb ? per_block[b + u * 1024] : make_int4(0, 0, 0, 0);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             m = max(m, v[u].x);
             t += v[u].y;
+            all += v[u].z;
         }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         m = max(m, __shfl_xor(m, o, kWave));
         t += __shfl_xor(t, o, kWave);
+        all += __shfl_xor(all, o, kWave);
     }
     if ((threadIdx.x & (kWave - 1)) == 0) {
         red[threadIdx.x / kWave] = m;
         red_ns[threadIdx.x / kWave] = t;
+        red_all[threadIdx.x / kWave] = all;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 1024 / kWave; ++w) {
             m = max(m, red[w]);
             t += red_ns[w];
+            all += red_all[w];
         }
         status[RC_ST_KMAX] = max(status[RC_ST_KMAX], m);
         if (m > k_max) status[RC_ST_FLAGS] |= RC_FLAG_NLIST_OVERFLOW;
         status[RC_ST_NSWAP] = (int)min(t, (long long)0x7fffffff);
+        status[RC_ST_NLIST] = (int)min(all, (long long)0x7fffffff);
     }
 }
 
@@ -689,7 +699,7 @@ __global__ __launch_bounds__(kBlock) void k_nlist(NlistArgs a) {
         if (!a.back.pos && a.vel) a.vel[i].w = 0.0f;
     }
     if (a.pl_j) pack_wave_lists(i, i < a.N, packed, a.nlist, a.k_max, a.N, a.pl_j, a.pl_o);
-    if (a.status) block_list_status(total, nn_swap(packed), a.status, a.k_max, a.per_block);
+    if (a.status) block_list_status(total, packed, a.status, a.k_max, a.per_block);
 }
 
 // LDS writes of a wavefront before its own reads, without the block's barrier
@@ -875,7 +885,7 @@ __global__ __launch_bounds__(kWave * (kWave / kFewOwn)) void k_nlist_few(NlistAr
     }
     if (wv == 0) {
         if (first + lane < a.N) a.nn[first + lane] = ns | (no << 16);
-        if (a.status) block_list_status<kWave>(total, ns, a.status, a.k_max, a.per_block);
+        if (a.status) block_list_status<kWave>(total, ns | (no << 16), a.status, a.k_max, a.per_block);
     }
     if (a.pl_j) {            // the packed copy (pack_wave_lists), SL lanes per particle
         const int before = wave_inclusive_scan(ns + no) - (ns + no);
@@ -946,7 +956,7 @@ __global__ __launch_bounds__(kBlock) void k_nlist_batch(NlistArgsB a) {
         if (!a.back.pos && builds && a.vel) a.vel[i].w = 0.0f;
     }
     if (a.pl_j && (builds || i >= a.N)) pack_wave_lists(i, i < a.N, packed, a.nlist, a.k_max, a.N, a.pl_j, a.pl_o);
-    if (a.status) block_list_status(total, nn_swap(packed), a.status, a.k_max, a.per_block);
+    if (a.status) block_list_status(total, packed, a.status, a.k_max, a.per_block);
 }
 
 // A list laid out for k_old slots per particle copied into the layout of
@@ -982,7 +992,7 @@ static void begin_status(int* status, int mode, bool begun, hipStream_t s) {
     if (status && !begun) hipLaunchKernelGGL(k_status_begin, dim3(1), dim3(1), 0, s, status, mode);
 }
 
-static void end_status(int* status, int k_max, const int2* per_block, int nb, hipStream_t s) {
+static void end_status(int* status, int k_max, const int4* per_block, int nb, hipStream_t s) {
     if (status && nb > kStatusBlocks)
         hipLaunchKernelGGL(k_list_status, dim3(1), dim3(1024), 0, s, per_block, nb, k_max, status);
 }

@@ -833,27 +833,32 @@ static const void* few_fn(int ow) {
     }
 }
 
-// Particles per wavefront of a plain step.  list_est is the number of list
-// entries a particle would have at the largest list radius.  k_step_few at the
-// most particles that hold about one row of 64 entries (8 to 32), while that
-// makes few wavefronts: past 2560 (2.5 per SIMD) the partly filled rows and
-// integrator lanes cost sparse lists more than they save (131072 dumbbells: 13.2
-// us per step with 32 particles per wavefront, 12.7 with 64; 65536: 11.6, 12.0),
-// lists of six passes or more per 64 particles gain up to twice as many
-// (67200 beads of a network, 4200 wavefronts: 24.2, 33.7).
-static int step_particles(int N, float list_est) {
-    const long most = 64.0f * list_est >= 384.0f ? 5120 : 2560;
+// Particles per wavefront of a plain step; list_len: mean list entries per particle.  k_step_few at the particles
+// that hold about half a row of 64 entries (8 to 32), as long as that makes at most 5120 wavefronts (five per SIMD);
+// lists of fewer entries than particles leave too little to share.  By the length, not by the density: the walk
+// kernel of the assembly mixture, whose colloids make the largest list radius a poor guide, was slower by 5-9 %.
+// us per step of a run with 64, 32, 16, 8 particles per wavefront:
+//   walk   0.8 entries (assembly mixture) 8000 particles 8.0, 8.1, 8.1, 8.1; 30000 8.4, 8.7, 9.0, 9.8; 80000 9.0,
+//          9.6, 10.7, 14.7
+//          1.2 (reactive, density 0.1) 4000 13.4, 10.3, 10.2, 9.8; 80000 14.7, 12.5, 13.4, 18.4; 160000 17.2, 15.3, ..
+//          2.3 (0.15) 4000 21.5, 16.2, 12.4, 12.2; 80000 23.8, 19.0, 17.2, 24.8; 110000 24.1, 20.3, 23.1, 30.5
+//          4.8 (0.25) 4000 47.8, 29.7, 22.5, 17.3; 45000 48.4, 33.2, 26.5, 29.0; 110000 52.5, 35.7, 42.5, 46.2
+//          10 (network) 4000 29.0, 23.3, 17.6, 15.1; 60000 31.1, 25.7, 21.1, 23.6; 160000 36.3, 31.7, 34.5, 43.3
+//   sums   0.9 (dumbbells) 110000 12.1, 12.4, 15.2, 21.7; 4.8 16000 20.4, 15.4, 12.8, 11.1; 80000 22.1, 18.3, 17.1, 19.6
+static int step_particles(int N, float list_len) {
+    if (list_len < 1.1f) return kStepBlock;
     int ow = 32;
-    while (ow > 8 && (float)ow * list_est > 72.0f) ow /= 2;
-    while (ow < kStepBlock && (long)N > most * ow) ow *= 2;
+    while (ow > 8 && (float)ow * list_len > 44.0f) ow /= 2;
+    while (ow < kStepBlock && (long)N > 5120L * ow) ow *= 2;
     return ow;
 }
 
 // Batches of lists longer than a pass of two entries per lane holds take four (16.8 -> 15.6 us per launch at 96
-// replicas, five entries per particle; 131072 dumbbells, 1.7 entries: 12.5 -> 12.7 per step).
-static const void* sums_fn(bool batch, int ow, float list_est) {
+// replicas, five entries per particle; 131072 dumbbells, 1.7 entries: 12.5 -> 12.7 per step).  (A batch's length is
+// that of uniform replicas at their largest list radii.)
+static const void* sums_fn(bool batch, int ow, float list_len) {
     if (batch)
-        return list_est > 3.0f ? reinterpret_cast<const void*>(&k_swap_sums_packed<true, kWave, 4>)
+        return list_len > 3.0f ? reinterpret_cast<const void*>(&k_swap_sums_packed<true, kWave, 4>)
                                : reinterpret_cast<const void*>(&k_swap_sums_packed<true, kWave>);
     switch (ow) {
         case 8: return reinterpret_cast<const void*>(&k_swap_sums_packed<false, 8>);
@@ -863,17 +868,17 @@ static const void* sums_fn(bool batch, int ow, float list_est) {
     }
 }
 
-// Whether the two-pass form takes one launch: while 16 particles' entries fill about half a row, so that a row
-// holds them in a denser spot too, and the wavefronts are at most five per SIMD.  us per step, two launches and
-// one: dumbbells (2.1 entries per particle at the largest list radius) as generated 1500 9.1, 7.4; 20011 9.3, 8.0;
-// 80000 11.1, 10.4; aggregated 1500 10.4, 8.8; 20011 11.9, 10.0; 65536 13.1, 11.5; reactive particles of density
-// 0.25 (6.1) 1000 10.3, 19.4; 30000 13.4, 22.1 (with 8 per wavefront 12.8 and 15.9).
-static bool fused_sums(int N, float list_est) { return kFusedOwn * list_est <= 40.0f && N <= 5120 * kFusedOwn; }
+// Whether the two-pass form takes one launch: while a row holds 16 particles' entries with some room for a denser spot,
+// and the wavefronts are at most five per SIMD.  us per step, two launches (best particles per wavefront) and one:
+// 0.8 entries per particle (assembly) 1500 8.6, 6.8; 80000 10.3, 9.5; 110000 10.6, 11.5; 0.9 (dumbbells) 20000 9.5, 8.1;
+// 80000 11.4, 10.7; 1.2 (reactive, density 0.1) 4000 9.4, 8.3; 80000 11.8, 11.4; 2.3 (0.15) 1500 9.4, 9.6; 30000 10.9,
+// 10.8; 80000 13.7, 13.1; 4.1 (a drop of density 0.25 in a box eight times as large) 1340 9.4, 16.5; 78000 16.1, 23.2.
+static bool fused_sums(int N, float list_len) { return list_len <= 2.5f && N <= 5120 * kFusedOwn; }
 
-StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_est) {
+StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_len) {
     StepKernel k;
-    const int few = batch ? kStepBlock : step_particles(N, list_est);
-    if (!batch && !ev && form == RC_FORM_SUMS && fused_sums(N, list_est)) {
+    const int few = batch ? kStepBlock : step_particles(N, list_len);
+    if (!batch && !ev && form == RC_FORM_SUMS && fused_sums(N, list_len)) {
         k.particles = kFusedOwn;
         k.fn = reinterpret_cast<const void*>(&k_step_fused);
         return k;
@@ -884,14 +889,14 @@ StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float li
     else
         k.fn = batch ? step_fn<true>(ev, width, form) : step_fn<false>(ev, width, form);
     if (form == RC_FORM_SUMS) {
-        k.sums_fn = sums_fn(batch, few, list_est);
+        k.sums_fn = sums_fn(batch, few, list_len);
         k.sums_particles = few;
     }
     return k;
 }
 
 static hipError_t launch_step_any(const StepArgs& a, bool batch, bool ev, hipStream_t s) {
-    const StepKernel k = step_kernel(batch, ev, a.width, a.form, a.N, a.list_est);
+    const StepKernel k = step_kernel(batch, ev, a.width, a.form, a.N, a.list_len);
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
     if (k.sums_fn) {
         ForceArgs f = sums_args(a);
@@ -911,7 +916,7 @@ hipError_t launch_step_batch(const StepArgs& a, bool ev, hipStream_t s) { return
 // (hipExtLaunchKernel records them around the kernel alone).
 hipError_t launch_step_timed(const StepArgs& a, bool batch, hipStream_t s, hipEvent_t* sums, hipEvent_t* step) {
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
-    const StepKernel k = step_kernel(batch, false, a.width, a.form, a.N, a.list_est);
+    const StepKernel k = step_kernel(batch, false, a.width, a.form, a.N, a.list_len);
     if (k.sums_fn) {
         ForceArgs f = sums_args(a);
         void* fargs[] = {&f};

@@ -233,13 +233,16 @@ static const void* block_fn(int N, int form) {
 
 // Whether a system fits: particle count, form and the LDS the kernel needs
 // (its static gather slices plus the dynamic part) within one workgroup.
-bool step_block_fits(int N, int nt, int form, float list_est) {
+bool step_block_fits(int N, int nt, int form, float list_len) {
     if (N < 1 || N > kBlockMaxN) return false;
-    // A wavefront here holds 32 or 64 particles, launches of k_step_few as few as 8: lists that make more than
-    // about two rows of entries (three in the walk form, one launch per step there) are faster launched (us per
-    // step here, launched: 1000 dumbbells 7.3, 9.3; 1000 of the assembly mixture 5.6, 8.2; reactive particles of
-    // density 0.25, 300 of them 9.9, 10.0 and 1000 16.1, 10.0)
-    if ((float)block_particles(N) * list_est > (form == RC_FORM_SUMS ? 160.0f : 240.0f)) return false;
+    // A wavefront here holds 32 or 64 particles, launches of k_step_few as few as 8.  The two-pass form is faster here
+    // while the entries of an average wavefront fit the registers (block_steps_row), the walk form, which evaluates
+    // every row by itself, up to about one row.  us per step here and launched (entries per wavefront): sums 1000
+    // of the assembly mixture (51) 4.1, 8.6; 1000 reactive of density 0.15 (148) 6.7, 9.6 and of density 0.25 (310) 16.1,
+    // 9.9; 433 in a drop (126) 8.1, 9.3; 500 of density 0.25 (158) 10.5, 9.7; walk 1000 dumbbells (62) 7.9, 8.8; 300
+    // reactive of density 0.1 (41) 7.9, 9.4; 1000 of them (79) 10.0, 9.4; 300 of density 0.15 (77) 13.1, 11.0
+    const int ow = block_particles(N);
+    if ((float)ow * list_len > (form == RC_FORM_SUMS ? (float)(block_rows(ow) * kWave) : 72.0f)) return false;
     const void* fn = block_fn(N, form);
     hipFuncAttributes at{};
     if (hipFuncGetAttributes(&at, fn) != hipSuccess) return false;

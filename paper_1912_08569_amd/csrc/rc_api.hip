@@ -68,10 +68,12 @@ int reduce_rows(rc_ctx* c, int nb, int first, int count, double* out, hipStream_
 
 Table dev_table(const rc_ctx* c) { return Table{c->d_tab, c->nt}; }
 
-// list entries per particle of a uniform system at the largest list radius
-float list_est(const rc_ctx* c, int N, const Box& b) {
+// list entries per particle: the last list's, or as many as the workloads have on average (0.2 to 1.0) of those that
+// a uniform system has at the largest list radius
+float list_len(const rc_ctx* c, int N, const Box& b) {
+    if (c->list_len >= 0.0f) return c->list_len;
     const double r = c->rlist_max;
-    return (float)((double)N / (b.L[0] * b.L[1] * b.L[2]) * 4.18879 * r * r * r);
+    return (float)(0.6 * (double)N / (b.L[0] * b.L[1] * b.L[2]) * 4.18879 * r * r * r);
 }
 
 // energy/virial rows of the force kernels: one per block, which is one wavefront
@@ -285,6 +287,14 @@ int rc_set_gather_width(rc_ctx* c, int width) {
     return RC_OK;
 }
 
+int rc_set_list_length(rc_ctx* c, double entries) {
+    if (!c) return RC_ERR_ARG;
+    if (std::isnan(entries)) return fail(c, RC_ERR_ARG, "the list length is not a number");
+    if (entries < 0.0) c->list_len = -1.0f;
+    else note_list_len(c, std::min(entries, 1e6));
+    return RC_OK;
+}
+
 int rc_set_step_form(rc_ctx* c, int form) {
     if (!c) return RC_ERR_ARG;
     if (form != RC_FORM_WALK && form != RC_FORM_SUMS)
@@ -399,7 +409,7 @@ static int build_nlist(rc_ctx* c, const float* pos, float* vel, int N, rc_box bo
     a.nn = nn;
     a.status = status;
     a.status_mode = status_mode;
-    a.per_block = reinterpret_cast<int2*>(const_cast<char*>(w) + l.bmax);
+    a.per_block = reinterpret_cast<int4*>(const_cast<char*>(w) + l.bmax);
     a.back = back;
     a.back.tvel = reinterpret_cast<const float4*>(w + l.tvel);
     a.back.timage = reinterpret_cast<const int4*>(w + l.timage);
@@ -538,7 +548,7 @@ static int fill_step_args(rc_ctx* c, StepArgs& a, const float* pos_in, float* po
     a.soft = (float)(0.5 * c->r_buff * soft_frac);
     a.seed = cfg->seed;
     a.status = status;
-    a.list_est = list_est(c, N, b);
+    a.list_len = list_len(c, N, b);
     a.width = c->gather_width;
     a.form = c->step_form;
     a.ssum = nullptr;
@@ -611,7 +621,7 @@ int rc_time_fused_steps(rc_ctx* c, float* pos_a, float* pos_b, float* vel, const
     hipStream_t s = S(stream);
     // every kernel launch carries its own start/stop events, which time its
     // execution alone (not the dispatch gaps between launches)
-    const StepKernel kn = step_kernel(false, false, a.width, a.form, N, a.list_est);
+    const StepKernel kn = step_kernel(false, false, a.width, a.form, N, a.list_len);
     const int nk = kn.sums_fn ? 2 : 1;
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
     std::vector<hipEvent_t> ev((size_t)2 * nk * reps, nullptr);
@@ -887,8 +897,9 @@ struct PlainOps final : DriveOps {
                                       buf->bonds_log + row));
         return RC_OK;
     }
-    StepKernel plain_step() override { return step_kernel(false, false, c->gather_width, c->step_form, N, list_est(c, N, b)); }
-    bool block_ok() override { return step_block_fits(N, c->nt, c->step_form, list_est(c, N, b)); }
+    StepKernel plain_step(const StepArgs& a) override { return step_kernel(false, false, a.width, a.form, a.N, a.list_len); }
+    bool block_ok(const StepArgs& a) override { return step_block_fits(a.N, c->nt, a.form, a.list_len); }
+    float list_len() override { return ::list_len(c, N, b); }
     // the cell sort permutes pos, vel and image into the workspace's temporaries,
     // from where they are copied back, so those hold the rebuilt state
     bool rebuild_snapshot(const float4** p, const float4** v, const int4** im) override {

@@ -118,7 +118,7 @@ int fill_step_args_batch(rc_batch* b, StepArgs& a, const float* pos_in, float* p
         return r;
     a.pl_j = c->d_pl_j;
     a.pl_o = c->d_pl_o;
-    a.list_est = b->list_est;
+    a.list_len = b->list_est;
     return RC_OK;
 }
 
@@ -335,7 +335,7 @@ static int batch_build_nlist(rc_batch* b, const float* pos, float* vel, const vo
     a.status = status;
     a.status_mode = status_mode;
     a.build = build;
-    a.per_block = reinterpret_cast<int2*>(const_cast<char*>(w) + l.bmax);
+    a.per_block = reinterpret_cast<int4*>(const_cast<char*>(w) + l.bmax);
     a.back = back;
     a.back.tvel = reinterpret_cast<const float4*>(w + l.tvel);
     a.back.timage = reinterpret_cast<const int4*>(w + l.timage);
@@ -612,7 +612,8 @@ struct BatchOps final : DriveOps {
                                                 fused_bonds() ? buf->bonds_log + (size_t)row * b->R : nullptr));
         return RC_OK;
     }
-    StepKernel plain_step() override { return step_kernel(true, false, b->c.gather_width, b->c.step_form, b->n_slots, b->list_est); }
+    StepKernel plain_step(const StepArgs& a) override { return step_kernel(true, false, a.width, a.form, a.N, a.list_len); }
+    float list_len() override { return b->list_est; }
     // the batch cell sort also permutes (pos, vel, image) of every slot through
     // the workspace's temporaries and copies them back
     bool rebuild_snapshot(const float4** p, const float4** v, const int4** im) override {

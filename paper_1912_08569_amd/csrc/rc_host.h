@@ -13,7 +13,7 @@ struct GraphCache {
     hipGraphExec_t exec[2] = {nullptr, nullptr};  // start parity 0 / 1
     hipGraph_t graph[2] = {nullptr, nullptr};
     rc::StepArgs key{};
-    const void* fn = nullptr;
+    const void *fn = nullptr, *sums_fn = nullptr;
     int steps = 0;
     bool valid = false;
 };
@@ -90,6 +90,7 @@ struct rc_ctx {
     int blk_cap = 0;                    // slots allocated (blocks)
     int gather_width = 2;               // flattened list entries per lane and pass of the step kernel
     int step_form = RC_FORM_WALK;       // RC_FORM_WALK | RC_FORM_SUMS
+    float list_len = -1.0f;             // mean list entries per particle (note_list_len); negative: not known
     float* d_ssum = nullptr;            // per-particle switching sums of the sums form
     size_t ssum_cap = 0;                // floats allocated
     double* d_hsum = nullptr;           // per-particle (S, dS) of the Hessian-vector product
@@ -169,6 +170,9 @@ int ensure_plist(rc_ctx* c, int N, int k_max);
 // the packed copy of (nlist, nn, k_max, N): made on the stream unless it is the current one
 int packed_list_for(rc_ctx* c, const int* nlist, const int* nn, int k_max, int N, hipStream_t s);
 void free_ctx_buffers(rc_ctx* c);       // every device buffer the context owns
+// a list's mean entries per particle, for the choice of kernels; within 15 % of the last one it is taken as the same,
+// so that a list that breathes does not move a system from one kernel to another at every build
+void note_list_len(rc_ctx* c, double len);
 // the context's pinned host words and wait event: the status copy, then kHostWords that kernels write,
 // a run of rigid bodies from kRigidWords on and a load by tag from kLoadWords on
 constexpr int kHostWords = 8, kRigidWords = RC_STATUS_WORDS, kLoadWords = RC_STATUS_WORDS + 4;
@@ -231,10 +235,12 @@ struct DriveOps {
     // reduce the partial rows of the last ev launch into log row `row`
     virtual int reduce_ev(int row) = 0;
     // the kernels of a plain step (launched and replayed)
-    virtual StepKernel plain_step() = 0;
+    virtual StepKernel plain_step(const StepArgs& a) = 0;
     // whether stretches of plain steps may run as one-workgroup launches, and such a
     // launch of any number of steps (a: launch arguments of its first step)
-    virtual bool block_ok() { return false; }
+    virtual bool block_ok(const StepArgs&) { return false; }
+    // mean list entries per particle, as far as known
+    virtual float list_len() = 0;
     // where the last rebuild left a copy of the state it produced (positions,
     // velocities with stale path lengths, images or NULL), if it does: the
     // driver then restores from there instead of taking its own snapshot
@@ -249,7 +255,7 @@ struct DriveOps {
 // log step intervenes), one status read per chunk, rollback and replay of
 // stale chunks, rebuilds, the final half kick and the logs.  tmpl holds every
 // launch argument except positions, mode, step and ev_part; N counts slots.
-int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const StepArgs& tmpl, uint64_t step0,
+int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, StepArgs tmpl, uint64_t step0,
              int n_steps, rc_md_options opt, rc_md_stats* stats, hipStream_t s);
 
 }  // namespace host

@@ -71,7 +71,7 @@ CellsLayout cells_layout(int N, uint32_t nkeys) {
     l.rank = o; o = al(o + 4 * (size_t)N);
     l.order = o; o = al(o + 4 * (size_t)N);
     l.bsums = o; o = al(o + 4 * (nk / kScanTile + 2));
-    l.bmax = o; o = al(o + 8 * ((size_t)N / kWave + 2));   // per block: largest list and swap-range sum
+    l.bmax = o; o = al(o + 16 * ((size_t)N / kWave + 2));   // per block: largest list, swap entries, entries
     l.tpos = o; o = al(o + 16 * (size_t)N);
     l.tvel = o; o = al(o + 16 * (size_t)N);
     l.timage = o; o = al(o + 16 * (size_t)N);
@@ -160,6 +160,11 @@ int ensure_ssum(rc_ctx* c, size_t n) {
     HIP_TRY(c, hipMalloc(&c->d_ssum, sizeof(float) * n));
     c->ssum_cap = n;
     return RC_OK;
+}
+
+void note_list_len(rc_ctx* c, double len) {
+    if (c->list_len > 0.0f && len > 0.85 * c->list_len && len < 1.15 * c->list_len) return;
+    c->list_len = (float)len;
 }
 
 int ensure_host_words(rc_ctx* c) {
@@ -504,6 +509,7 @@ static int build_graphs(rc_ctx* c, const StepKernel& kn, const StepArgs& tmpl, i
     }
     c->gc.key = tmpl;
     c->gc.fn = kn.fn;
+    c->gc.sums_fn = kn.sums_fn;
     c->gc.steps = G;
     c->gc.valid = true;
     return RC_OK;
@@ -540,7 +546,7 @@ static bool same_buffers(const rc_md_buffers& x, const rc_md_buffers& y) {
            x.snap_image == y.snap_image && x.status == y.status;
 }
 
-int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const StepArgs& tmpl, uint64_t step0,
+int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, StepArgs tmpl, uint64_t step0,
              int n_steps, rc_md_options opt, rc_md_stats* stats, hipStream_t s) {
     const bool can_roll = buf->snap_pos && buf->snap_vel && (buf->snap_image || !buf->image);
     const int nb = nblocks(N, kStepBlock);
@@ -691,7 +697,7 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
         }
         if (timing && !ev && (mode == RC_STEP_START || mode == RC_STEP_CONT)) {
             // the plain step launches (log steps and the finishing kick are other work)
-            const bool two = ops.plain_step().sums_fn != nullptr;
+            const bool two = ops.plain_step(tmpl).sums_fn != nullptr;
             size_t qk = 0, qs = 0;
             int rr = tk_take(&qk, 0);
             if (!rr && two) rr = tk_take(&qs, 1);
@@ -723,16 +729,21 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
     const float hard = tmpl.hard;
     const bool graphs = opt.use_graph != 0 && !timing;
     const int G = opt.graph_steps;
-    const bool blockrun = graphs && opt.one_block != 0 && ops.block_ok();
-    if (graphs && !blockrun) {
+    // The kernels go by the lists' mean length, which the status reads tell: looked at again with every chunk
+    // (every kernel gives the same bits).
+    bool blockrun = graphs && opt.one_block != 0 && ops.block_ok(tmpl);
+    auto ready = [&]() -> int {   // the graphs of the present kernels (built between chunks or before the first replay)
         StepArgs key = tmpl;
         key.pos_in = reinterpret_cast<const float4*>(buf->pos);
         key.pos_out = reinterpret_cast<float4*>(buf->pos_alt);
-        const StepKernel kn = ops.plain_step();
-        if (!c->gc.valid || c->gc.steps != G || c->gc.fn != kn.fn || !same_args(c->gc.key, key)) {
-            if ((r = build_graphs(c, kn, key, G, s))) return finish(r);
-        }
-    }
+        key.list_len = 0.0f;   // as far as it matters it is in the kernels
+        const StepKernel kn = ops.plain_step(tmpl);
+        if (c->gc.valid && c->gc.steps == G && c->gc.fn == kn.fn && c->gc.sums_fn == kn.sums_fn &&
+            same_args(c->gc.key, key))
+            return RC_OK;
+        return build_graphs(c, kn, key, G, s);
+    };
+    if (graphs && !blockrun && (r = ready())) return finish(r);
     uint64_t dev_base = ~0ull;   // value *d_step_base will hold once queued work ran
 
     // Graph replays pay a step-counter node and a wait at each end; direct launches cost the host
@@ -772,6 +783,7 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
                         a.ev_part = nullptr;
                         HIP_TRY(c, ops.launch_block(a, reinterpret_cast<float4*>(P[cur]), (int)n));
                     } else {
+                        if ((rr = ready())) return rr;
                         HIP_TRY(c, hipGraphLaunch(c->gc.exec[cur], s));
                     }
                     dev_base = step + (uint64_t)n;
@@ -826,6 +838,10 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
             C = std::min<int64_t>(C, 8);
         }
         first_chunk = false;
+        if (const float len = ops.list_len(); len != tmpl.list_len) {
+            tmpl.list_len = len;
+            blockrun = graphs && opt.one_block != 0 && ops.block_ok(tmpl);
+        }
         const uint64_t chunk_start = s_cur;
         if (can_roll && need_snap) {
             if (!snap_in_ws)
@@ -865,6 +881,7 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
         if (timing && (r = tk_collect())) return finish(r);
         ++st.chunks;
         const int f = hst[RC_ST_FLAGS];
+        note_list_len(c, hst[RC_ST_NLIST] / (double)N);
         check_pending = false;
         if (f & RC_FLAG_NLIST_OVERFLOW) {
             // the epoch ran on a truncated list (it began at a build of this run, whose
@@ -948,6 +965,7 @@ int md_drive(rc_ctx* c, DriveOps& ops, const rc_md_buffers* buf, int N, const St
         if ((r = finishing())) return finish(r);
         // the status read waits for all of the run's work (pinned copy and an event, no blocking sync)
         if ((r = read_status_spin(c, buf->status, hst, s))) return finish(r);
+        note_list_len(c, hst[RC_ST_NLIST] / (double)N);
         if (timing && (r = tk_collect())) return finish(r);
     }
     // what the next run needs to continue on this list

@@ -454,7 +454,7 @@ struct StepArgs {
     const RepDesc* rep;        // [R]
     const int* chunk_rep;      // [N / 64] replica of each 64-slot chunk
     const uint64_t* seeds;     // [R] thermostat keys
-    float list_est;            // list entries per particle at the largest list radius (read by the launcher)
+    float list_len;            // mean list entries per particle (read by the launcher)
     int width;                 // gather width of the non-logging steps: 1, 2 or 4 (read by the launcher)
     int form;                  // RC_FORM_WALK or RC_FORM_SUMS (read by the launcher)
     float* ssum;               // [N] per-particle switching sums (RC_FORM_SUMS)
@@ -479,7 +479,7 @@ hipError_t launch_step_timed(const StepArgs& a, bool batch, hipStream_t s, hipEv
 // (the buffer a.pos_in names), *step_base is read as the first step's index
 // and advanced by G.  step_block_fits says whether a system fits the kernel.
 constexpr int kBlockMaxN = 1024;
-bool step_block_fits(int N, int nt, int form, float list_est);
+bool step_block_fits(int N, int nt, int form, float list_len);
 hipError_t launch_step_block(const StepArgs& a, float4* pos_final, unsigned long long* step_base, int G,
                              hipStream_t s);
 hipError_t launch_step_batch(const StepArgs& a, bool ev, hipStream_t s);
@@ -490,7 +490,7 @@ struct StepKernel {
     const void* sums_fn = nullptr;
     int particles = kStepBlock, sums_particles = kStepBlock;
 };
-StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_est);
+StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_len);
 
 struct ForceArgs {
     const float4* pos;
@@ -593,7 +593,7 @@ struct NlistArgs {
     int* pl_j;         // packed copy of the list (NULL: none), see pack_wave_lists
     unsigned char* pl_o;
     int status_mode;
-    int2* per_block;   // [ceil(N / 64)] scratch: largest list and swap entries of each block
+    int4* per_block;   // [ceil(N / 64)] scratch: largest list, swap entries and entries of each block
     StateBack back;    // with back.pos, pos is the cell sort's copy and the status words are begun
 };
 hipError_t launch_nlist(const NlistArgs& a, hipStream_t s);
@@ -726,7 +726,7 @@ struct NlistArgsB {
     int* pl_j;              // packed copy of the list (NULL: none), see pack_wave_lists
     unsigned char* pl_o;
     int status_mode;        // as in NlistArgs, as the next two
-    int2* per_block;
+    int4* per_block;
     StateBack back;
     const int* build;       // [R] nonzero: the replica's list is rebuilt (NULL: every replica)
 };

@@ -130,6 +130,7 @@ class System:
                 raise RcError(code, "neighbour list build")
             self.built = True
             self._continues = False
+            self.ctx.set_list_length(int(st[rcl.RC_ST_NLIST]) / self.N)
             if self.step_form == "auto":
                 self.ctx.set_step_form(self._form_for(int(st[rcl.RC_ST_NSWAP])))
             return st[rcl.RC_ST_KMAX]

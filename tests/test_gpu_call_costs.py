@@ -39,3 +39,44 @@ def test_first_run_of_a_process_loads_no_kernels():
     assert out.returncode == 0, out.stderr[-2000:]
     t = json.loads(out.stdout.strip().splitlines()[-1])
     assert t[0] < min(t[1:]) + 1.35e-3, t
+
+
+def _us_per_step(S, cfg, relax=200, **kw):
+    import time
+    import torch
+    S.run(relax, cfg, **kw)
+    t = []
+    for k in range(7):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        S.run(200, cfg, step0=relax + 200 * k, **kw)
+        torch.cuda.synchronize()
+        t.append((time.perf_counter() - t0) / 200 * 1e6)
+    return sorted(t)[3]
+
+
+def test_short_lists_of_a_wide_table_run_in_one_workgroup():
+    """The assembly mixture's lists are short although its largest list radius is wide: the two-pass form of 1000
+    particles takes less time in one workgroup (4.1 us against 6.8 launched)."""
+    import workloads as W
+    from paper_1912_08569_amd import System
+    s = W.assembly_mixture(N=1000, seed=4)
+    t = {}
+    for one in (False, True):
+        S = System.from_workload(s, step_form="sums")
+        t[one] = _us_per_step(S, S.integrator(dt=0.001, kT=0.05, gamma=1.0, seed=3), 4000, one_block=one)
+    assert t[True] < 0.85 * t[False], t
+
+
+def test_a_drop_takes_the_kernels_of_its_own_density():
+    """Particles in a corner of a large box have the lists of their own density, not of the box's: a step takes no
+    longer than where they fill the box (22 us and 20; with the one-launch kernel, for short lists, 37)."""
+    import numpy as np
+    import workloads as W
+    from paper_1912_08569_amd import System
+    s = W.small_reactive(N=80000, density=0.35, seed=8, min_dist=0.95)
+    t = []
+    for L in (s.L, float(np.float32(2.0 * s.L))):
+        S = System(s.pos, s.types, L, s.table, vel=s.vel, mass=s.mass, step_form="sums")
+        t.append(_us_per_step(S, S.integrator(dt=0.001, kT=0.03, gamma=1.0, seed=3)))
+    assert t[1] < 1.35 * t[0], t

@@ -16,3 +16,59 @@ def test_system_is_made_in_its_form(form):
     assert (r.stats.sums_ms > 0.0) is (form == "sums")    # two launches a step, or one
     S.build()
     assert S.ctx.step_form == form
+
+
+@pytest.mark.parametrize("name", ["reactive-1000", "reactive-20481", "reactive-81921", "assembly-5003", "network-300"])
+def test_kernels_chosen_by_list_length_give_the_same_step(name):
+    # one step by every kernel that a list length can choose (64, 32, 16 and 8 particles per wavefront, the two-pass
+    # form in one launch), Langevin and NVE, bit for bit; the length is a hint, so wrong ones have to do as well
+    import torch
+    from test_gpu_kernel_edges import _step_system
+    from paper_1912_08569_amd import _lib as rcl, api
+    s = _step_system(name)
+    for form in ("walk", "sums"):
+        S = System.from_workload(s, step_form=form)
+        for kind in ("langevin", "nve"):
+            cfg = S.integrator(kind=kind, dt=2e-4, kT=0.1, gamma=1.0, seed=6)
+            S.build()
+            x0, v0, im0 = S.pos.clone(), S.vel.clone(), S.image.clone()
+            out = []
+            for entries in (0.0, 1.0, 1.2, 2.0, 2.4, 3.0, 5.0, 50.0, -1.0):
+                S.ctx.set_list_length(-1.0)
+                S.ctx.set_list_length(entries)
+                S.vel.copy_(v0)
+                S.image.copy_(im0)
+                S.pos_alt.fill_(float("nan"))
+                for k, (a, b) in enumerate(((x0, S.pos_alt), (S.pos_alt, S.pos))):
+                    api.rc_step_fused(S.ctx, a, b, S.vel, S.image, S.nlist, S.nn, S.box, cfg, 7 + k,
+                                      rcl.RC_STEP_CONT if k else rcl.RC_STEP_START, status=S.status)
+                out.append((S.pos.clone(), S.vel.clone(), S.image.clone()))
+                S.pos.copy_(x0)
+            S.vel.copy_(v0)
+            S.image.copy_(im0)
+            for other in out[1:]:
+                assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(out[0], other))
+
+
+def test_list_length_word():
+    # the status word of all list entries, by the few-particle and the one-thread list kernels and batches, and
+    # what it is refused for
+    import numpy as np
+    from paper_1912_08569_amd import Batch, RcError, _lib as rcl, api
+    for N in (1, 900, 5000, 80001):
+        s = W.small_reactive(N=N, density=0.25, seed=N, min_dist=0.9) if N > 1 else W.cluster([[0.0, 0.0, 0.0]])
+        S = System.from_workload(s)
+        S.build()
+        _, st = api.rc_read_status(S.status)
+        nn = S.nn.cpu().numpy()
+        assert st[rcl.RC_ST_NLIST] == int(((nn & 0xFFFF) + (nn >> 16)).sum())
+        assert st[rcl.RC_ST_NSWAP] == int((nn & 0xFFFF).sum())
+    B = Batch([W.small_reactive(N=n, density=0.3, seed=n) for n in (300, 64, 5000)])
+    B.build()
+    _, st = api.rc_read_status(B.status)
+    nn = B.nn.cpu().numpy()
+    assert st[rcl.RC_ST_NLIST] == int(((nn & 0xFFFF) + (nn >> 16)).sum())
+    with pytest.raises(RcError):
+        S.ctx.set_list_length(float("nan"))
+    S.ctx.set_list_length(float("inf"))
+    S.ctx.set_list_length(np.float64(3.0))
