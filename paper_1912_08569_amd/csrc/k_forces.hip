@@ -21,10 +21,12 @@ static inline int nblk(long n, int b) { return (int)((n + b - 1) / b); }
 // atomic-free gather force kernel (RC_FORCE_GATHER)
 // ---------------------------------------------------------------------------
 // A wavefront owns OW particles: 64, or fewer where 64 would leave most of
-// the chip without a wavefront (gather_owners).
-template <bool EV, bool BATCH, bool SF, int OW>
-__global__ __launch_bounds__(kWave) void k_forces_gather(ForceArgs a) {
-    static_assert(!BATCH || OW == kWave, "a batch chunk has 64 slots");
+// the chip without a wavefront (gather_owners).  A block is one wavefront, or
+// NW of them where that leaves the row reduction fewer partial sums of energy
+// and virial to read (gather_waves).
+template <bool EV, bool BATCH, bool SF, int OW, int NW>
+__global__ __launch_bounds__(kWave * NW) void k_forces_gather(ForceArgs a) {
+    static_assert(!BATCH || (OW == kWave && NW == 1), "a batch chunk has 64 slots");
     extern __shared__ DevEntry s_tab[];
     const int blk = xcd_block(gridDim.x);
     Box box_r;
@@ -38,14 +40,15 @@ __global__ __launch_bounds__(kWave) void k_forces_gather(ForceArgs a) {
         box_r = a.box;
         load_table(s_tab, a.tab);
     }
-    const int m = blk * OW + threadIdx.x;
-    const bool live = (int)threadIdx.x < OW && m < lim;
+    const int lane = threadIdx.x & (kWave - 1), wv = NW > 1 ? (int)threadIdx.x / kWave : 0;
+    const int m = (blk * NW + wv) * OW + lane;
+    const bool live = lane < OW && m < lim;
     const float4 pm = live ? a.pos[m] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int packed = live ? a.nn[m] : 0;
     Acc acc = {};
     const OneSystem sys{s_tab, a.tab.nt, box_r};
-    wave_gather<EV, kDefaultWidth, SF, OneSystem, false, false, 4, OW>(m - (int)threadIdx.x, live, pm, packed, a.pos,
-                                                                       a.nlist, a.nn, a.k_max, a.N, sys, acc, a.ssum);
+    wave_gather<EV, kDefaultWidth, SF, OneSystem, NW, false, 4, OW>(m - lane, live, pm, packed, a.pos, a.nlist, a.nn,
+                                                                    a.k_max, a.N, sys, acc, a.ssum);
     if (live) {
         float4 f = make_float4(acc.fx, acc.fy, acc.fz, acc.e);
         if (a.accumulate) {
@@ -59,9 +62,22 @@ __global__ __launch_bounds__(kWave) void k_forces_gather(ForceArgs a) {
         if (a.status && !(isfinite(f.x) && isfinite(f.y) && isfinite(f.z)))
             atomicOr(&a.status[RC_ST_FLAGS], RC_FLAG_NONFINITE);
     }
-    if (EV) {
+    if constexpr (EV) {
         double v[7] = {acc.e, acc.w[0], acc.w[1], acc.w[2], acc.w[3], acc.w[4], acc.w[5]};
-        wave_sum_store<7>(v, a.ev_part + (size_t)blk * kEvWords);
+        double* row = a.ev_part + (size_t)blk * kEvWords;
+        if constexpr (NW == 1) {
+            wave_sum_store<7>(v, row);
+        } else {   // the wavefronts' sums one after the other
+            __shared__ double s_ev[NW][7];
+            wave_sum_store<7>(v, s_ev[wv]);
+            __syncthreads();
+            if (threadIdx.x < 7) {
+                double t = s_ev[0][threadIdx.x];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) t += s_ev[w][threadIdx.x];
+                row[threadIdx.x] = t;
+            }
+        }
     }
 }
 
@@ -448,32 +464,55 @@ static hipError_t launch_sums(const ForceArgs& a, bool batch, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Particles per wavefront, by the lists' mean length: those that hold about half a row of 64 entries (8 to 32) while
+// that makes at most 4096 wavefronts (four per SIMD); lists shorter than a particle or so leave too little to share.
+// A wavefront's time is its rows of 64 entries one after the other, each as long as its longest partner walk, so a
+// chip with idle SIMDs wants more wavefronts with fewer rows.  us without ev at 8, 16, 32, 64 particles per wavefront
+// (entries per particle): 0.6 (assembly) 4000 particles 5.8, 5.7, 5.8, 6.0; 32000 6.9, 6.5, 6.4, 6.3; 128000 13.5, 9.9,
+// 7.5, 6.8; 0.9 (dumbbells) 4000 6.7, 6.6, 7.0, 8.0; 64000 10.8, 8.3, 7.8, 8.5; 4.8 (reactive, density 0.25) 4000 14.2,
+// 18.8, 26.0, 38.8; 32000 16.8, 20.8, 25.6, 38.7; 64000 28.3, 23.7, 27.7, 39.8; 256000 79.5, 65.0, 53.7, 48.8.
+static int gather_owners(int N, float list_len) {
+    if (list_len < 0.8f) return kWave;
+    int ow = 32;
+    while (ow > 8 && (float)ow * list_len > 44.0f) ow /= 2;
+    while (ow < kWave && (long)N > 4096L * ow) ow *= 2;
+    return ow;
+}
+
+// Wavefronts per block with ev: several from 768 wavefronts on, where the rows cost the reduction more than blocks of
+// one gain by spreading over the compute units.  us at blocks of one and of four: reactive particles of density 0.25
+// (8 per wavefront) 1000 16.4, 19.3; 4000 17.9, 18.9; 8000 19.3, 18.5; 32000 24.7, 21.1; 64000 (16) 32.1, 28.3;
+// 128000 (32, blocks of two) 40.0, 37.6.  (Without ev 1000 13.0, 15.6; 32000 16.8, 16.8.)
+constexpr int gather_waves(int ow) { return ow == kWave ? 1 : (ow == 32 ? 2 : 4); }
+static bool gather_wide(int N, int ow) { return (long)N > 768L * ow; }
+
+int gather_particles(int N, float list_len) {
+    const int ow = gather_owners(N, list_len);
+    return gather_wide(N, ow) ? ow * gather_waves(ow) : ow;
+}
+
 template <bool BATCH, int OW>
 static void launch_gather_ow(const ForceArgs& a, hipStream_t s) {
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
-    const dim3 g(nblk(a.N, OW)), b(kWave);
-    if (a.ssum) {
-        if (a.ev_part)
-            hipLaunchKernelGGL((k_forces_gather<true, BATCH, true, OW>), g, b, shm, s, a);
+    constexpr int NW = BATCH ? 1 : gather_waves(OW);
+    if (a.ev_part) {
+        const int w = !BATCH && gather_wide(a.N, OW) ? NW : 1;
+        const dim3 g(nblk(a.N, OW * w)), b(kWave * w);
+        if (w > 1 && a.ssum)
+            hipLaunchKernelGGL((k_forces_gather<true, BATCH, true, OW, NW>), g, b, shm, s, a);
+        else if (w > 1)
+            hipLaunchKernelGGL((k_forces_gather<true, BATCH, false, OW, NW>), g, b, shm, s, a);
+        else if (a.ssum)
+            hipLaunchKernelGGL((k_forces_gather<true, BATCH, true, OW, 1>), g, b, shm, s, a);
         else
-            hipLaunchKernelGGL((k_forces_gather<false, BATCH, true, OW>), g, b, shm, s, a);
+            hipLaunchKernelGGL((k_forces_gather<true, BATCH, false, OW, 1>), g, b, shm, s, a);
     } else {
-        if (a.ev_part)
-            hipLaunchKernelGGL((k_forces_gather<true, BATCH, false, OW>), g, b, shm, s, a);
+        const dim3 g(nblk(a.N, OW)), b(kWave);
+        if (a.ssum)
+            hipLaunchKernelGGL((k_forces_gather<false, BATCH, true, OW, 1>), g, b, shm, s, a);
         else
-            hipLaunchKernelGGL((k_forces_gather<false, BATCH, false, OW>), g, b, shm, s, a);
+            hipLaunchKernelGGL((k_forces_gather<false, BATCH, false, OW, 1>), g, b, shm, s, a);
     }
-}
-
-// The fewest particles per wavefront, 8 to 64, that make at most 4096 wavefronts (four per SIMD).  A
-// wavefront's time is its rows of 64 entries one after the other, each as long as its longest partner walk, so
-// a chip with idle SIMDs wants more wavefronts with fewer rows; past four per SIMD the energy/virial rows and
-// the partly filled rows of entries cost more (us without ev at 8, 16, 32, 64 particles per wavefront, density
-// 0.25: 16000 particles 15.6, 20.9, 25.8, 39.1; 65536: 28.5, 24.1, 27.5, 41.9; 131072: 47.8, 40.1, 32.1, 43.8).
-int gather_owners(int N) {
-    int ow = 8;
-    while (ow < kWave && (long)N > 4096L * ow) ow *= 2;
-    return ow;
 }
 
 hipError_t launch_forces_gather(const ForceArgs& a, hipStream_t s) {
@@ -481,7 +520,7 @@ hipError_t launch_forces_gather(const ForceArgs& a, hipStream_t s) {
         hipError_t e = launch_sums(a, false, s);
         if (e != hipSuccess) return e;
     }
-    switch (gather_owners(a.N)) {
+    switch (gather_owners(a.N, a.list_len)) {
         case 8: launch_gather_ow<false, 8>(a, s); break;
         case 16: launch_gather_ow<false, 16>(a, s); break;
         case 32: launch_gather_ow<false, 32>(a, s); break;
@@ -556,7 +595,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(7))) void
     const int packed = live ? packed0 : 0;
     const OneSystem sys{s_tab, nt, box};
     // the entries come from the packed copy of the list
-    wave_gather<EV, PL, SF, OneSystem, false, true>(m - (int)threadIdx.x, live, pm, packed, a.pos_in, a.nlist, a.nn,
+    wave_gather<EV, PL, SF, OneSystem, 1, true>(m - (int)threadIdx.x, live, pm, packed, a.pos_in, a.nlist, a.nn,
                                                      a.k_max, a.N, sys, acc, a.ssum, a.pl_j, a.pl_o);
     if (!BATCH && a.bonds && live)
         fene_add<EV>(ptag(pm.w), pm, a.bonds, a.rtag, a.pos_in, box, a.fene_k, a.fene_r02, acc);
@@ -608,7 +647,7 @@ __global__ __launch_bounds__(kWave) void k_step_few(StepArgs a) {
     float nz[3] = {0.f, 0.f, 0.f};
     int bi[2] = {-1, -1};
     float4 bp[2] = {pm, pm};
-    wave_gather<false, 1, SF, OneSystem, false, true, 4, OW>(
+    wave_gather<false, 1, SF, OneSystem, 1, true, 4, OW>(
         m - lane, live, pm, packed, a.pos_in, a.nlist, a.nn, a.k_max, a.N, sys, acc, a.ssum, a.pl_j, a.pl_o,
         (size_t)blk * kWave * a.k_max + before, h * OW, [&](int at) {
             if (at == 0) {

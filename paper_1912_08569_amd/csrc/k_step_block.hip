@@ -70,7 +70,7 @@ __device__ __forceinline__ void block_steps(const StepArgs& a, const DevEntry* s
             __syncthreads();
         }
         Acc acc = {};
-        wave_gather<false, kDefaultWidth, SF, OneSystem, true, true, 1, OW>(m - lane, live, pm, packed, pin, a.nlist, a.nn,
+        wave_gather<false, kDefaultWidth, SF, OneSystem, kGatherMaxWaves, true, 1, OW>(m - lane, live, pm, packed, pin, a.nlist, a.nn,
                                                                             a.k_max, a.N, sys, acc, s_S, ent_j, ent_o,
                                                                             first, lane0);
         if (a.bonds && live)

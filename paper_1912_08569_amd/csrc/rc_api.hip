@@ -76,9 +76,9 @@ float list_len(const rc_ctx* c, int N, const Box& b) {
     return (float)(0.6 * (double)N / (b.L[0] * b.L[1] * b.L[2]) * 4.18879 * r * r * r);
 }
 
-// energy/virial rows of the force kernels: one per block, which is one wavefront
-int force_rows(int N, unsigned flags) {
-    return nblocks(N, (flags & (RC_FORCE_GATHER | RC_FORCE_SUMS)) ? gather_owners(N) : kWave);
+// energy/virial rows of the force kernels: one per block
+int force_rows(int N, unsigned flags, float len) {
+    return nblocks(N, (flags & (RC_FORCE_GATHER | RC_FORCE_SUMS)) ? gather_particles(N, len) : kWave);
 }
 
 // rc_compute_forces on given scratch: part (per-block FP64 rows, kEvWords
@@ -95,8 +95,9 @@ int forces_into(rc_ctx* c, const float* pos, const int* nlist, const int* nn, in
     if ((r = check_list(c, nlist, nn, k_max))) return r;
     const bool sums = flags & RC_FORCE_SUMS;
     const bool gather = (flags & RC_FORCE_GATHER) || sums;
-    const int nb = force_rows(N, flags);
     ForceArgs a{};
+    a.list_len = list_len(c, N, b);
+    const int nb = force_rows(N, flags, a.list_len);
     a.pos = reinterpret_cast<const float4*>(pos);
     a.nlist = nlist;
     a.nn = nn;
@@ -454,7 +455,9 @@ int rc_compute_forces(rc_ctx* c, const float* pos, const int* nlist, const int* 
                       float* force, double* ev, unsigned flags, int* status, void* stream) {
     int r = check_common(c, N, pos);
     if (r) return r;
-    const int nb = force_rows(N, flags);
+    Box b;
+    if ((r = make_box(c, box, b))) return r;
+    const int nb = force_rows(N, flags, list_len(c, N, b));
     if ((flags & RC_FORCE_SUMS) && (r = ensure_ssum(c, (size_t)N))) return r;
     if (ev && (r = ensure_part(c, sizeof(double) * kEvWords * (size_t)nb))) return r;
     return forces_into(c, pos, nlist, nn, k_max, N, box, force, ev, flags, status, c->d_part, c->d_ssum,

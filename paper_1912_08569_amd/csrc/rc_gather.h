@@ -124,7 +124,7 @@ struct Stage {
 // PL = flattened entries each lane evaluates per pass (the gather width).
 constexpr int kDefaultWidth = 2;
 
-// Most wavefronts one workgroup of the multi-wave (WS) gather holds.
+// Most wavefronts one workgroup of the multi-wave (NWV > 1) gather holds.
 constexpr int kGatherMaxWaves = 16;
 
 // Barrier of the gather's LDS exchange.  With one wavefront per block (WS =
@@ -152,7 +152,8 @@ __device__ __forceinline__ void gather_sync() {
 struct NoMid {
     __device__ __forceinline__ void operator()(int) const {}
 };
-template <bool EV, int kPerLane, bool SF, class Ctx, bool WS = false, bool PK = false, int AHEAD = 1, int OW = kWave,
+// NWV: wavefronts of the workgroup at most, each with its own LDS slices and owners.
+template <bool EV, int kPerLane, bool SF, class Ctx, int NWV = 1, bool PK = false, int AHEAD = 1, int OW = kWave,
           class Mid = NoMid>
 __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4& pm, int packed,
                                             const float4* pos, const int* nlist, const int* nn, int k_max,
@@ -163,7 +164,8 @@ __device__ __forceinline__ void wave_gather(int base_m, bool live, const float4&
     constexpr int NC = Stage<EV, SF>::n;
     constexpr int CE = Stage<EV, SF>::e;
     constexpr int W = kPerLane * kWave;  // entries per pass
-    constexpr int NW = WS ? kGatherMaxWaves : 1;  // LDS slices, one per wavefront
+    constexpr bool WS = NWV > 1;
+    constexpr int NW = NWV;              // LDS slices, one per wavefront
     __shared__ int s_off_w[NW][kWave + 1];
     __shared__ int s_ns_w[NW][kWave];
     __shared__ unsigned char s_own_w[NW][W];  // owner lane of each entry of the current pass

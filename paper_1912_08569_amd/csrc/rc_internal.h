@@ -507,12 +507,13 @@ struct ForceArgs {
     const RepDesc* rep;    // batches only
     const int* chunk_rep;
     float* ssum;           // [N] switching sums: non-NULL selects the two-pass form
+    float list_len;        // mean list entries per particle (read by the gather's launcher)
     const int* pl_j;       // the packed list (a step's first pass only)
     const unsigned char* pl_o;
 };
 hipError_t launch_forces_triplet(const ForceArgs& a, hipStream_t s);
-// particles per wavefront (and per row of ev_part) of the gather kernel for N particles
-int gather_owners(int N);
+// particles per row of ev_part of the gather kernel for N particles with so many list entries on average
+int gather_particles(int N, float list_len);
 hipError_t launch_forces_gather(const ForceArgs& a, hipStream_t s);
 hipError_t launch_forces_gather_batch(const ForceArgs& a, hipStream_t s);
 // arguments of the first pass of the two-pass form for a step (positions pos_in)

@@ -80,3 +80,33 @@ def test_a_drop_takes_the_kernels_of_its_own_density():
         S = System(s.pos, s.types, L, s.table, vel=s.vel, mass=s.mass, step_form="sums")
         t.append(_us_per_step(S, S.integrator(dt=0.001, kT=0.03, gamma=1.0, seed=3)))
     assert t[1] < 1.35 * t[0], t
+
+
+def _gpu_us(fn, n=40):
+    import torch
+    for _ in range(5):
+        fn()
+    t = []
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda._sleep(2_000_000)     # the launches are queued meanwhile
+        a.record()
+        for _ in range(n):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b) / n * 1e3)
+    return sorted(t)[3]
+
+
+def test_energies_cost_short_lists_no_more_than_their_reduction():
+    """Energy and virial of 32000 particles of the assembly mixture by the gather kernel: a row of partial sums per
+    wavefront of 8 particles took 8.3 us on top of the forces, one per 64 particles takes 3.5."""
+    import workloads as W
+    from paper_1912_08569_amd import System, _lib as rcl, api
+    S = System.from_workload(W.assembly_mixture(N=32000, seed=4))
+    S.build()
+    call = lambda ev: api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, S.force, ev,  # noqa: E731
+                                            rcl.RC_FORCE_GATHER, S.status)
+    with_ev, without = _gpu_us(lambda: call(S.ev)), _gpu_us(lambda: call(None))
+    assert with_ev < without + 6.0, (with_ev, without)

@@ -72,3 +72,34 @@ def test_list_length_word():
         S.ctx.set_list_length(float("nan"))
     S.ctx.set_list_length(float("inf"))
     S.ctx.set_list_length(np.float64(3.0))
+
+
+@pytest.mark.parametrize("N", [1, 100, 6145, 12289, 24577, 32769, 65601])
+def test_forces_by_list_length(N):
+    # the gather kernel with 8, 16, 32 and 64 particles per wavefront, in blocks of one, two and four wavefronts
+    # (energies from 768 on) and ragged last blocks: forces and per-particle energies bit for bit, sums in FP64 of
+    # the same terms in another order (|difference| <= 2 N u sum |terms|), adding up or not, with a status word
+    import torch
+    from paper_1912_08569_amd import _lib as rcl, api
+    s = W.small_reactive(N=N, density=0.25, seed=N, min_dist=0.9) if N > 1 else W.cluster([[0.0, 0.0, 0.0]])
+    S = System.from_workload(s)
+    S.build()
+    for flag in (rcl.RC_FORCE_GATHER, rcl.RC_FORCE_SUMS):
+        out = []
+        for entries in (0.0, 1.0, 2.0, 5.0):
+            S.ctx.set_list_length(-1.0)
+            S.ctx.set_list_length(entries)
+            F, ev = torch.full_like(S.force, float("nan")), torch.full((7,), float("nan"), dtype=torch.float64,
+                                                                       device="cuda")
+            api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, F, ev, flag, S.status)
+            G = F.clone()
+            api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, G, None, flag | rcl.RC_FORCE_ACCUMULATE,
+                                  S.status)
+            H, ew = torch.empty_like(F), torch.empty_like(ev)
+            api.rc_compute_forces_noalloc(S.ctx, S.pos, S.nlist, S.nn, S.box, H, ew, flag, S.status)
+            assert torch.equal(F[:, :3], H[:, :3]) and torch.equal(ev, ew)
+            out.append((F[:, :3].clone(), G[:, :3].clone(), F[:, 3].double().clone(), ev.clone()))
+        bound = 2.0 * N * 2.0 ** -53 * (float(out[0][2].abs().sum()) + 1.0) * 50.0    # virials: terms up to 50 times E's
+        for o in out[1:]:
+            assert torch.equal(o[0], out[0][0]) and torch.equal(o[1], out[0][1])
+            assert bool(((o[3] - out[0][3]).abs() <= bound).all())
