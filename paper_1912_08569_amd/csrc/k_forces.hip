@@ -83,10 +83,15 @@ __global__ __launch_bounds__(kWave * NW) void k_forces_gather(ForceArgs a) {
 
 // ---------------------------------------------------------------------------
 // triplet kernel (default of rc_compute_forces): one wavefront per block.
-// The list entries of its 64 centres are evaluated flat, two per lane and
-// pass as in wave_gather (a lane per centre evaluated its own list before: the
+// The swap entries of its 64 centres are evaluated flat, two or eight per lane
+// and pass as in wave_gather (a lane per centre evaluated its own before: the
 // wavefront took its longest list's time), and every lane sums its centre's
-// terms from LDS in slot order.  The active partners of centres with two or
+// terms from LDS in slot order.  The ordinary entries, which need no sum over
+// them, stay with their centre's lane, four requested at a time and the first
+// four on their way beside the swap partners: flat they took passes that short
+// swap ranges leave no others for, 23.4 us against 14.5 at 4032 beads of the
+// network (9.6 entries each, few of them swap) and 26.9 against 16.9 at 67200.
+// The active partners of centres with two or
 // more of them are kept in an LDS pool; the wave then enumerates every (j<k)
 // triplet of its 64 centres across its lanes for the energy and the virial,
 // and adds up each partner's w of the others, which gives the force on it in
@@ -103,15 +108,15 @@ __global__ __launch_bounds__(kWave * NW) void k_forces_gather(ForceArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kPool = 512;   // staged partners per wave and round
 
-template <bool SPREAD>
+template <bool SPREAD, int PL>
 __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_ev) {
-    constexpr int PL = 2, W = PL * kWave;   // entries per lane and pass
+    constexpr int W = PL * kWave, AH = 4;   // swap entries per pass, other entries requested at a time
     extern __shared__ DevEntry s_tab[];
     __shared__ int p_j[kPool];
     __shared__ float p_w[kPool], p_g[kPool], p_dx[kPool], p_dy[kPool], p_dz[kPool], p_s[kPool];
     __shared__ int l_pool[kWave], l_k[kWave], l_tri[kWave + 1], l_out;
     __shared__ float l_f[kWave][4];
-    __shared__ int s_off[kWave], s_ns[kWave], s_j[W];
+    __shared__ int s_off[kWave], s_j[W];
     __shared__ unsigned char s_own[W];
     __shared__ float4 s_pos[kWave];
     __shared__ float s_c[8][W];   // phi'/r, phi, d, w, w'/r, 1 for an active swap partner
@@ -123,20 +128,38 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     float4 pi = live ? a.pos[i] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int ti = ptype(pi.w);
     const int packed = live ? a.nn[i] : 0;
-    const int ns = nn_swap(packed), cnt = ns + nn_other(packed);
-    const int inc = wave_inclusive_scan(cnt), my_off = inc - cnt;
+    const int ns = nn_swap(packed), no = nn_other(packed);
+    auto other = [&](int b, int (&j)[AH]) {   // the other range's entries from b on
+#pragma unroll
+        for (int u = 0; u < AH; ++u) j[u] = b + u < no ? a.nlist[(size_t)(a.k_max - 1 - (b + u)) * a.N + i] : i;
+    };
+    auto other_pos = [&](int b, const int (&j)[AH], float4 (&p)[AH]) {
+#pragma unroll
+        for (int u = 0; u < AH; ++u) p[u] = b + u < no ? a.pos[j[u]] : pi;
+    };
+    int oj[AH];
+    float4 op[AH];
+    other(0, oj);
+    const int inc = wave_inclusive_scan(ns), my_off = inc - ns;
     const int T = __builtin_amdgcn_readlane(inc, kWave - 1);
-    const int pinc = wave_inclusive_scan(ns), poff = pinc - ns;
-    const bool fits = __builtin_amdgcn_readlane(pinc, kWave - 1) <= kPool;
+    const bool fits = T <= kPool;
     s_off[lane] = my_off;
-    s_ns[lane] = ns;
     s_pos[lane] = pi;
     float fx = 0.f, fy = 0.f, fz = 0.f, en = 0.f;
     float w6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     int nact = 0;
+    auto add_pair = [&](float g, float phi, float dx, float dy, float dz) {
+        fx += g * dx;
+        fy += g * dy;
+        fz += g * dz;
+        en += 0.5f * phi;
+        const float c = -0.5f * g;
+        w6[0] += c * dx * dx; w6[1] += c * dy * dy; w6[2] += c * dz * dz;
+        w6[3] += c * dx * dy; w6[4] += c * dx * dz; w6[5] += c * dy * dz;
+    };
     __syncthreads();
     for (int base = 0; base < T; base += W) {
-        const int lo = max(my_off, base) - base, hi = min(my_off + cnt, base + W) - base;
+        const int lo = max(my_off, base) - base, hi = min(my_off + ns, base + W) - base;
         for (int q = lo; q < hi; ++q) s_own[q] = (unsigned char)lane;
         __syncthreads();
         int own[PL], jj[PL];
@@ -148,11 +171,10 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
             jj[u] = 0;
             if (e < T) {
                 own[u] = s_own[e - base];
-                const int sl = e - s_off[own[u]], nso = s_ns[own[u]];
-                const int slot = sl < nso ? sl : a.k_max - 1 - (sl - nso);
-                jj[u] = a.nlist[(size_t)slot * a.N + (i - lane) + own[u]];
+                jj[u] = a.nlist[(size_t)(e - s_off[own[u]]) * a.N + (i - lane) + own[u]];
             }
         }
+        if (base == 0) other_pos(0, oj, op);   // on their way beside the swap partners
 #pragma unroll
         for (int u = 0; u < PL; ++u) {
             pj[u] = pi;
@@ -191,17 +213,11 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
         }
         __syncthreads();
         for (int q = lo; q < hi; ++q) {
-            const float g = s_c[0][q], dx = s_c[2][q], dy = s_c[3][q], dz = s_c[4][q];
-            fx += g * dx;
-            fy += g * dy;
-            fz += g * dz;
-            en += 0.5f * s_c[1][q];
-            const float c = -0.5f * g;
-            w6[0] += c * dx * dx; w6[1] += c * dy * dy; w6[2] += c * dz * dz;
-            w6[3] += c * dx * dy; w6[4] += c * dx * dz; w6[5] += c * dy * dz;
+            const float dx = s_c[2][q], dy = s_c[3][q], dz = s_c[4][q];
+            add_pair(s_c[0][q], s_c[1][q], dx, dy, dz);
             if (s_c[7][q] != 0.0f) {
                 if (fits) {
-                    const int at = poff + nact;   // at most ns active partners
+                    const int at = my_off + nact;   // at most ns active partners
                     p_j[at] = s_j[q];
                     p_w[at] = s_c[5][q];
                     p_g[at] = s_c[6][q];
@@ -214,6 +230,23 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
         }
         __syncthreads();
     }
+    if (T == 0) other_pos(0, oj, op);
+    for (int b = 0; b < no; b += AH) {
+        if (b > 0) {
+            other(b, oj);
+            other_pos(b, oj, op);
+        }
+#pragma unroll
+        for (int u = 0; u < AH; ++u) {
+            const DevEntry& e = s_tab[ti * nt + ptype(op[u].w)];
+            if (b + u >= no || e.kind == RC_KIND_NONE) continue;
+            const PairGeom pg = pair_geom<true>(pi, op[u], a.box, e);
+            if (!pg.cut) continue;
+            float phi, g;
+            pair_eval(e, pg.r2, phi, g);
+            add_pair(g, phi, pg.dx, pg.dy, pg.dz);
+        }
+    }
     // ---- wave-wide triplet stage -------------------------------------------
     const int k = (nact >= 2) ? nact : 0;
     const int incl = wave_inclusive_scan(k);
@@ -224,7 +257,7 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     bool done = (k == 0);
     while (round_start < total) {
         bool mine = !done;
-        int next = total, pool = poff;
+        int next = total, pool = my_off;
         if (!fits) {
             // the admitted lanes form a run; the next round starts at the first lane left out
             mine = !done && off >= round_start && off + k <= round_start + kPool;
@@ -369,11 +402,14 @@ hipError_t launch_forces_triplet(const ForceArgs& a, hipStream_t s) {
                            a.force, a.N);
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
     // sending the partners' forces together costs a barrier and pays where the atomics are the bound: us per call
-    // apart and together, 32768 unequal 24.2, 24.8, 8000 22.7, 23.4; 200003 unequal 73.3, 68.0, reactive 53.8, 50.4
-    if (a.N >= 65536)
-        hipLaunchKernelGGL(k_forces_triplet<true>, dim3(nblk(a.N, kWave)), dim3(kWave), shm, s, a, a.ev_part ? 1 : 0);
-    else
-        hipLaunchKernelGGL(k_forces_triplet<false>, dim3(nblk(a.N, kWave)), dim3(kWave), shm, s, a, a.ev_part ? 1 : 0);
+    // apart and together, 32768 unequal 24.2, 24.8, 8000 22.7, 23.4; 200003 unequal 73.3, 68.0, reactive 53.8, 50.4.
+    // Eight entries per lane and pass where the lists are long: two passes more of a wavefront's entries cost 2 us,
+    // a lane's unused places 0.4.  us per call with two and eight, lists of 1.1 entries (4000) 8.8, 9.4, of 1.7 9.1,
+    // 9.7 (32000: 11.1, 10.9), of 2.4 11.6, 10.8, of 4.9 17.9, 15.2, of 7.3 28.7, 23.1.  Above 65536 the wavefronts
+    // hide the passes and eight entries' LDS takes their places: 100003 of 4.9 23.3, 32.2.
+    auto kernel = k_forces_triplet<true, 2>;
+    if (a.N < 65536) kernel = a.list_len < 2.2f ? k_forces_triplet<false, 2> : k_forces_triplet<false, 8>;
+    hipLaunchKernelGGL(kernel, dim3(nblk(a.N, kWave)), dim3(kWave), shm, s, a, a.ev_part ? 1 : 0);
     return hipGetLastError();
 }
 

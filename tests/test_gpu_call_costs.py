@@ -110,3 +110,16 @@ def test_energies_cost_short_lists_no_more_than_their_reduction():
                                             rcl.RC_FORCE_GATHER, S.status)
     with_ev, without = _gpu_us(lambda: call(S.ev)), _gpu_us(lambda: call(None))
     assert with_ev < without + 6.0, (with_ev, without)
+
+
+def test_ordinary_entries_cost_the_triplet_kernel_little():
+    """9.6 list entries per particle with few swap partners among them (a network of 4032) against half an entry
+    (the assembly mixture): forces by the triplet kernel take 14.5 us and 10.3; passes over all entries took 23.4."""
+    import workloads as W
+    from paper_1912_08569_amd import System, api
+    t = []
+    for s in (W.vitrimer_network(n_chains=240, n_dimers=96, seed=4), W.assembly_mixture(N=4032, seed=4)):
+        S = System.from_workload(s)
+        S.build()
+        t.append(_gpu_us(lambda: api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, S.force, None, 0, S.status)))
+    assert t[0] < 1.8 * t[1], t

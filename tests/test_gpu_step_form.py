@@ -103,3 +103,33 @@ def test_forces_by_list_length(N):
         for o in out[1:]:
             assert torch.equal(o[0], out[0][0]) and torch.equal(o[1], out[0][1])
             assert bool(((o[3] - out[0][3]).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("name", ["reactive-2003", "dense-1000", "network-21", "network-300"])
+def test_triplet_kernel_by_list_length(name):
+    # two and eight swap entries per lane and pass (lists named short and long), a lane's ordinary entries in
+    # several rounds of four (the network's), ragged last wavefronts, pools that hold the swap ranges and do not
+    from paper_1912_08569_amd import api
+    from oracle import swap_ref
+    from parity_util import assert_energy, assert_forces, assert_pe, assert_virial
+    from test_gpu_kernel_edges import _step_system
+    kind, n = name.split("-")
+    s = W.small_reactive(N=int(n), density=0.6, seed=9, min_dist=0.85) if kind == "dense" else _step_system(name)
+    S = System.from_workload(s)
+    S.build()
+    ns, no = S.nn.cpu() & 0xffff, S.nn.cpu() >> 16
+    if kind == "network":
+        assert int(no.max()) > 4
+    elif kind == "dense":
+        assert int(ns[:64].sum()) > 512
+    x, _, _, ty = S.state_by_tag()
+    ref = swap_ref.evaluate(x, ty, s.L, s.table)
+    for entries in (0.5, 50.0):
+        S.ctx.set_list_length(-1.0)
+        S.ctx.set_list_length(entries)
+        api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, S.force, S.ev, 0, S.status)   # without springs
+        F = S.by_tag(S.force)
+        assert_forces(F, ref)
+        assert_pe(F[:, 3], ref)
+        assert_energy(float(S.ev[0]), ref)
+        assert_virial(S.ev[1:7].cpu().numpy(), ref)
