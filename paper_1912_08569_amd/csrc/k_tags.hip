@@ -8,6 +8,8 @@
 // 0.60 ms).
 #include "rc_host.h"
 
+#include <climits>
+
 namespace rc {
 
 // Position of tag t folded into the box, rounded as x - L floor((x + L/2) / L)
@@ -25,10 +27,17 @@ __device__ __forceinline__ float nearest(float d, float L) {
     return d - L * rintf(d / L);
 }
 
-// host (pinned): [0] some particle farther than sqrt(far2) from its ref, [1] some distance not a number
+// host (pinned): [0] some particle farther than sqrt(far2) from its ref, [1] some distance not a number.  Stores
+// to host memory go over the bus one by one: from every wavefront that has such a particle they took 440 us at
+// 262144 particles which all moved, so only the first that sets mark[q] to this load's number stores.
+__device__ __forceinline__ void report_once(int* mark, int number, int* host) {
+    if (__hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == number) return;
+    if (atomicExch(mark, number) != number) __hip_atomic_store(host, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __global__ __launch_bounds__(kBlock) void k_load_by_tag(float4* __restrict__ pos, const float* __restrict__ xyz,
                                                         const float* __restrict__ ref, int N, Box box, float far2,
-                                                        int* host) {
+                                                        int* mark, int number, int* host) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     bool far = false, nan = false;
     if (i < N) {
@@ -49,8 +58,8 @@ __global__ __launch_bounds__(kBlock) void k_load_by_tag(float4* __restrict__ pos
     }
     const unsigned long long bf = __ballot(far), bn = __ballot(nan);
     if ((threadIdx.x & (kWave - 1)) == 0) {
-        if (bf) __hip_atomic_store(host, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        if (bn) __hip_atomic_store(host + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (bf) report_once(mark, number, host);
+        if (bn) report_once(mark + 1, number, host + 1);
     }
 }
 
@@ -99,8 +108,10 @@ extern "C" int rc_load_by_tag(rc_ctx* c, float* pos, const float* xyz, const flo
     }
     volatile int* host = c->h_status + kLoadWords;
     host[0] = host[1] = 0;
+    c->load_mark = c->load_mark == INT_MAX ? 1 : c->load_mark + 1;
     hipLaunchKernelGGL(k_load_by_tag, dim3(nblocks(N, kBlock)), dim3(kBlock), 0, s, reinterpret_cast<float4*>(pos), xyz,
-                       ref, N, b, (float)(reach * reach), c->h_status + kLoadWords);
+                       ref, N, b, (float)(reach * reach), reinterpret_cast<int*>(c->d_step_base + 2), c->load_mark,
+                       c->h_status + kLoadWords);
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipEventRecord(c->ev_load, s));
     return RC_OK;

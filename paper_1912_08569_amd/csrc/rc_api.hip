@@ -140,11 +140,13 @@ int rc_create(rc_ctx** out, int ntypes, const rc_pair_coeff* table, double r_buf
         delete c;
         return RC_ERR_ARG;
     }
+    const unsigned long long zeros[kStepWords] = {};
     if (hipGetDevice(&c->device) != hipSuccess ||
         hipMalloc(&c->d_tab, sizeof(DevEntry) * ntypes * ntypes) != hipSuccess ||
         hipMemcpy(c->d_tab, c->host_tab.data(), sizeof(DevEntry) * ntypes * ntypes,
                   hipMemcpyHostToDevice) != hipSuccess ||
-        hipMalloc(&c->d_step_base, 2 * sizeof(unsigned long long)) != hipSuccess ||
+        hipMalloc(&c->d_step_base, kStepWords * sizeof(unsigned long long)) != hipSuccess ||
+        hipMemcpy(c->d_step_base, zeros, sizeof(zeros), hipMemcpyHostToDevice) != hipSuccess ||
         hipMalloc(&c->d_slices, sizeof(double) * kRowSlices) != hipSuccess ||
         noalloc_scratch_here(c->device, &c->noalloc_scratch) != hipSuccess || load_step_kernels() != hipSuccess ||
         // the private stream the driver's rebuild graphs are recorded on: created here, as creating a

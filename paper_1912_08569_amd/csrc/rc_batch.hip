@@ -189,7 +189,7 @@ int rc_batch_create(rc_batch** out, int R, int ntypes, const rc_pair_coeff* tabl
               hipMalloc(&c->d_tab, sizeof(DevEntry) * (size_t)R * nt2) == hipSuccess &&
               hipMemcpy(c->d_tab, c->host_tab.data(), sizeof(DevEntry) * (size_t)R * nt2, hipMemcpyHostToDevice) ==
                   hipSuccess &&
-              hipMalloc(&c->d_step_base, 2 * sizeof(unsigned long long)) == hipSuccess &&
+              hipMalloc(&c->d_step_base, kStepWords * sizeof(unsigned long long)) == hipSuccess &&
               hipMalloc(&b->d_desc, sizeof(RepDesc) * R) == hipSuccess &&
               hipMemcpy(b->d_desc, b->desc.data(), sizeof(RepDesc) * R, hipMemcpyHostToDevice) == hipSuccess &&
               hipMalloc(&b->d_chunk_rep, sizeof(int) * chunk_rep.size()) == hipSuccess &&

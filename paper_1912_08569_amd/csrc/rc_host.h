@@ -84,7 +84,9 @@ struct rc_ctx {
     rc::DevEntry* d_tab = nullptr;
     double* d_part = nullptr;           // block partial rows (13 doubles each) or param partials
     size_t part_bytes = 0;
-    unsigned long long* d_step_base = nullptr;   // the replays' step counter, then a rigid run's stop word
+    // kStepWords: the replays' step counter, a rigid run's stop word, the marks of the last load by tag (two ints)
+    unsigned long long* d_step_base = nullptr;
+    int load_mark = 0;                  // the last load's number
     double* d_slices = nullptr;         // kRowSlices doubles: the two-launch row reduction
     int* d_blk = nullptr;               // per-block status slots of the step kernel
     int blk_cap = 0;                    // slots allocated (blocks)
@@ -175,6 +177,7 @@ void free_ctx_buffers(rc_ctx* c);       // every device buffer the context owns
 void note_list_len(rc_ctx* c, double len);
 // the context's pinned host words and wait event: the status copy, then kHostWords that kernels write,
 // a run of rigid bodies from kRigidWords on and a load by tag from kLoadWords on
+constexpr int kStepWords = 3;   // words of rc_ctx::d_step_base
 constexpr int kHostWords = 8, kRigidWords = RC_STATUS_WORDS, kLoadWords = RC_STATUS_WORDS + 4;
 int ensure_host_words(rc_ctx* c);
 // wait for everything queued on the stream so far

@@ -141,7 +141,7 @@ int set_workspace(rc_ctx* c, void* ws, size_t bytes, int N, int k_max, int nvec)
 }
 
 size_t ctx_device_bytes(const rc_ctx* c) {
-    size_t b = sizeof(DevEntry) * (size_t)c->nt * (size_t)c->nt + 2 * sizeof(unsigned long long) + c->part_bytes +
+    size_t b = sizeof(DevEntry) * (size_t)c->nt * (size_t)c->nt + kStepWords * sizeof(unsigned long long) + c->part_bytes +
                sizeof(int) * 3 * (size_t)c->blk_cap + (c->d_slices ? sizeof(double) * kRowSlices : 0);
     if (!c->ws_user) b += 5 * c->pl_cap + sizeof(float) * c->ssum_cap + 2 * sizeof(double) * c->hsum_cap;
     return b;

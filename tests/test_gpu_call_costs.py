@@ -123,3 +123,27 @@ def test_ordinary_entries_cost_the_triplet_kernel_little():
         S.build()
         t.append(_gpu_us(lambda: api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, S.force, None, 0, S.status)))
     assert t[0] < 1.8 * t[1], t
+
+
+def test_moved_particles_cost_a_load_nothing():
+    """Loading positions that all moved takes no longer than loading ones that did not, but for a store to host
+    memory (262144 particles: 440 us, when every wavefront stored)."""
+    import torch
+    import workloads as W
+    from paper_1912_08569_amd import System, api
+    S = System.from_workload(W.small_reactive(N=262144, density=0.25, seed=4, min_dist=0.9))
+    x = api.rc_to_tags(S.ctx, S.pos, S.rtag)
+    t = []
+    for ref in (x, x + 0.5):
+        y = []
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda._sleep(200_000)
+            a.record()
+            api.rc_load_by_tag(S.ctx, S.pos, x, ref, S.box, 0.1)
+            b.record()
+            assert api.rc_load_moved(S.ctx) is (ref is not x)
+            b.synchronize()
+            y.append(a.elapsed_time(b) * 1e3)
+        t.append(sorted(y)[10])
+    assert t[1] < t[0] + 60.0, t
