@@ -997,17 +997,21 @@ static void end_status(int* status, int k_max, const int4* per_block, int nb, hi
         hipLaunchKernelGGL(k_list_status, dim3(1), dim3(1024), 0, s, per_block, nb, k_max, status);
 }
 
-// Systems the list kernel of few particles per wavefront takes: past 9000 wavefronts (nine per SIMD) the
-// threads of the other fill the chip and it does without the flat layout (us, few and one per thread, at 67200
-// and 100000: reactive 23.7, 31.7 and 30.3, 31.4; dumbbells 18.9, 17.5 and 24.2, 19.0; assembly mixture 19.8,
-// 20.4 and 25.5, 20.9).
-static bool few_list(int N) { return N <= 9000 * kFewOwn; }
+// Systems the list kernel of few particles per wavefront takes; cand: mean particles within the largest list radius.
+// One thread per particle takes the time of its serial reads, the longer the more candidates there are, until its
+// wavefronts fill the chip; the flat layout's time goes by the particles.  They meet at (us, few and one per thread)
+// cand 2.1 (dumbbells) 60000 18.4, 19.4 and 72000 20.6, 19.2; 3.6 (assembly mixture) 72000 21.7, 22.1 and 90000 24.1,
+// 23.2; 6.1 (reactive, density 0.25) 110000 31.5, 31.5; 8.6 (three reactive types) 130000 39.3, 41.1 and 160000 45.8,
+// 44.1; 9.8 (reactive, 0.4) 160000 49.8, 50.9 and 200000 59.3, 55.2; 10.3 (network) 160000 49.6, 52.9 and 200000 62.0,
+// 59.5.  The line goes through those.
+static bool few_list(int N, float cand) { return (float)N <= 28000.0f + 13500.0f * cand; }
 
 hipError_t launch_nlist(const NlistArgs& a, hipStream_t s) {
     begin_status(a.status, a.status_mode, a.back.pos != nullptr, s);
     const size_t shm = 2 * sizeof(float) * a.tab.nt * a.tab.nt;
-    const int nb = nblk(a.N, few_list(a.N) ? kWave : kBlock);
-    if (few_list(a.N))
+    const bool few = few_list(a.N, a.cand);
+    const int nb = nblk(a.N, few ? kWave : kBlock);
+    if (few)
         hipLaunchKernelGGL(k_nlist_few, dim3(nb), dim3(kWave * (kWave / kFewOwn)), shm, s, a);
     else
         hipLaunchKernelGGL(k_nlist, dim3(nb), dim3(kBlock), shm, s, a);

@@ -68,12 +68,16 @@ int reduce_rows(rc_ctx* c, int nb, int first, int count, double* out, hipStream_
 
 Table dev_table(const rc_ctx* c) { return Table{c->d_tab, c->nt}; }
 
+// particles within the largest list radius in a uniform system
+double uniform_candidates(const rc_ctx* c, int N, const Box& b) {
+    const double r = c->rlist_max;
+    return (double)N / (b.L[0] * b.L[1] * b.L[2]) * 4.18879 * r * r * r;
+}
+
 // list entries per particle: the last list's, or as many as the workloads have on average (0.2 to 1.0) of those that
 // a uniform system has at the largest list radius
 float list_len(const rc_ctx* c, int N, const Box& b) {
-    if (c->list_len >= 0.0f) return c->list_len;
-    const double r = c->rlist_max;
-    return (float)(0.6 * (double)N / (b.L[0] * b.L[1] * b.L[2]) * 4.18879 * r * r * r);
+    return c->list_len >= 0.0f ? c->list_len : (float)(0.6 * uniform_candidates(c, N, b));
 }
 
 // energy/virial rows of the force kernels: one per block
@@ -413,6 +417,9 @@ static int build_nlist(rc_ctx* c, const float* pos, float* vel, int N, rc_box bo
     a.status = status;
     a.status_mode = status_mode;
     a.per_block = reinterpret_cast<int4*>(const_cast<char*>(w) + l.bmax);
+    // a part of the box denser than the rest shows in the last list: at least 4 in 5 of a pair type's candidates
+    // are entries where all pairs interact
+    a.cand = (float)std::max(uniform_candidates(c, N, b), 1.25 * c->list_len);
     a.back = back;
     a.back.tvel = reinterpret_cast<const float4*>(w + l.tvel);
     a.back.timage = reinterpret_cast<const int4*>(w + l.timage);

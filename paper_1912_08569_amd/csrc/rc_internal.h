@@ -596,6 +596,7 @@ struct NlistArgs {
     int status_mode;
     int4* per_block;   // [ceil(N / 64)] scratch: largest list, swap entries and entries of each block
     StateBack back;    // with back.pos, pos is the cell sort's copy and the status words are begun
+    float cand;        // mean particles within the largest list radius (read by the launcher)
 };
 hipError_t launch_nlist(const NlistArgs& a, hipStream_t s);
 // the packed copy of a list built elsewhere

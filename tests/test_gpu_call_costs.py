@@ -147,3 +147,25 @@ def test_moved_particles_cost_a_load_nothing():
             y.append(a.elapsed_time(b) * 1e3)
         t.append(sorted(y)[10])
     assert t[1] < t[0] + 60.0, t
+
+
+def test_builds_of_dense_lists_cost_no_step():
+    """78000 particles of density 0.4 take their list kernel by their candidates, not by a count that the short lists
+    set: a build costs little more than 70000 particles' (about 4 %; by the count alone another 15 us in 90)."""
+    import torch
+    import workloads as W
+    from paper_1912_08569_amd import System
+    t = []
+    for N in (70000, 78000):
+        S = System.from_workload(W.small_reactive(N=N, density=0.4, seed=4, min_dist=0.9))
+        y = []
+        for _ in range(60):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda._sleep(200_000)
+            a.record()
+            S.build()
+            b.record()
+            b.synchronize()
+            y.append(a.elapsed_time(b) * 1e3)
+        t.append(sorted(y[10:])[12])
+    assert t[1] < 1.12 * t[0], t

@@ -133,3 +133,30 @@ def test_triplet_kernel_by_list_length(name):
         assert_pe(F[:, 3], ref)
         assert_energy(float(S.ev[0]), ref)
         assert_virial(S.ev[1:7].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("N,density", [(1, 0.01), (63, 0.05), (4099, 0.2), (30001, 0.05), (72003, 0.2), (140003, 0.3)])
+def test_both_list_kernels_build_the_same_list(N, density):
+    # lists named short and long choose the kernel where the density does not: one thread per particle and few
+    # particles per wavefront, with and without a crowded corner, ragged last blocks; every word of the list alike
+    import numpy as np
+    import torch
+    rng = np.random.default_rng(N)
+    t = W.PairTable.empty(2)
+    t.set(0, 0, W.KIND_SWAP, 1.0, 1.0, 10, 1.5, 1.0)
+    t.set(0, 1, W.KIND_WCA, 1.0, 0.9, 6)
+    L = max(6.0, float(np.float32((N / density) ** (1.0 / 3.0))))
+    pos = (rng.uniform(-0.5, 0.5, (N, 3)) * L).astype(np.float32)
+    pos[: N // 20] *= np.float32(0.5)
+    types = (rng.random(N) < 0.3).astype(np.int32)
+    out = []
+    for entries in (0.0, 500.0):
+        S = System(pos, types, L, t, vel=rng.standard_normal((N, 3)).astype(np.float32) * 0, k_max=200)
+        S.ctx.set_list_length(entries)
+        S.build()
+        slots = torch.arange(S.nlist.numel() // N, device=S.nn.device)[:, None]
+        live = (slots < (S.nn & 0xffff)) | (slots >= slots.numel() - (S.nn >> 16))
+        out.append((S.pos.clone(), S.nn.clone(), torch.where(live, S.nlist.view(-1, N), -1), S.mean_list_length()))
+    for a, b in zip(out[0][:3], out[1][:3]):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert out[0][3] == out[1][3]
