@@ -30,6 +30,7 @@ class SwapModel:
 
     def __init__(self, system):
         self.S = system
+        self.L = torch.tensor(system.edges, dtype=torch.float32, device=system.device)
         self.half_skin = 0.5 * system.ctx.r_buff
         self.base = system.table.copy()
         self._theta = None
@@ -101,6 +102,7 @@ class SwapModel:
 
     # ---- evaluations (tag order) ---------------------------------------------------------------
     def load(self, xyz, theta):
+        """The state that hvp, param_grad and param_vjp are taken at."""
         self._load_theta(theta)
         self._on_list(xyz, lambda: None)
 

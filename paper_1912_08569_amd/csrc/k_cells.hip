@@ -381,6 +381,12 @@ hipError_t launch_cells(const CellsArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// p[i] by a 32-bit byte offset from the uniform base (i < 2^28 for 16-byte elements: N < 2^27)
+template <class T>
+__device__ __forceinline__ T at(const T* p, uint32_t i) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (size_t)(i * (uint32_t)sizeof(T)));
+}
+
 // ---------------------------------------------------------------------------
 // neighbour list
 // ---------------------------------------------------------------------------
@@ -417,12 +423,6 @@ hipError_t launch_cells(const CellsArgs& a, hipStream_t s) {
 // 2161 -> 1967 VALU instructions per wavefront at 1M particles and 80 -> 74 us,
 // the copy of the sorted state (14 us by itself) included.  Keeping the entries
 // found as bits and storing them after the test was slower (93 us).
-// p[i] by a 32-bit byte offset from the uniform base (i < 2^28 for 16-byte elements: N < 2^27)
-template <class T>
-__device__ __forceinline__ T at(const T* p, uint32_t i) {
-    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (size_t)(i * (uint32_t)sizeof(T)));
-}
-
 template <bool PAIR, class Radii>
 __device__ __forceinline__ int list_scan(int i, const float4& pi, const Box& b, const Grid& g, uint32_t key_base,
                                         int shift, const int* __restrict__ cell_start, const float4* __restrict__ pos,
@@ -443,7 +443,7 @@ __device__ __forceinline__ int list_scan(int i, const float4& pi, const Box& b, 
     // squared gaps from i to the cells at offsets -1, 0, +1 along an axis
     auto gaps = [&](float x, float h, float inv_w, int c, float& g0, float& g2) {
         const float f = (x + h) * inv_w - (float)c;  // place in the cell, in widths
-                const float w = __builtin_amdgcn_rcpf(inv_w);   // its last bit is far below the margin
+        const float w = __builtin_amdgcn_rcpf(inv_w);   // its last bit is far below the margin
         const float lo = fmaxf(f - 1e-3f, 0.0f) * w, hi = fmaxf(1.0f - f - 1e-3f, 0.0f) * w;
         g0 = lo * lo;
         g2 = hi * hi;

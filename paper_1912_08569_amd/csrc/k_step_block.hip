@@ -43,9 +43,9 @@ static size_t step_block_dyn_lds(int N, int nt, bool rows) {
 // OW particles per wavefront: 64, or 32 where that still fits one workgroup (a
 // wavefront's time is its rows of 64 entries one after the other).  The
 // velocities stay in registers; the wavefront's entries of the packed list are
-// kept in LDS when every wavefront's fit kBlockEntries (ENT), else read from
+// kept in LDS when every wavefront's fit kBlockEntries, else read from
 // the list every step.
-template <bool SF, int OW, bool ENT>
+template <bool SF, int OW>
 __device__ __forceinline__ void block_steps(const StepArgs& a, const DevEntry* s_tab, float4* s_p0, float4* s_p1,
                                             float* s_S, const int* ent_j, const unsigned char* ent_o, size_t first,
                                             int lane0, int T, int my_off, int packed, int m, int w, bool live,
@@ -213,11 +213,11 @@ __global__ __launch_bounds__(kBlockMaxN) void k_step_block(StepArgs a, float4* _
             s_eo[w * kBlockEntries + e] = a.pl_o[first + e];
         }
         __syncthreads();
-        block_steps<SF, OW, true>(a, s_tab, s_p0, s_p1, s_S, s_ej, s_eo, (size_t)w * kBlockEntries, lane0, T, my_off,
-                                  packed, m, w, live, base, G);
+        block_steps<SF, OW>(a, s_tab, s_p0, s_p1, s_S, s_ej, s_eo, (size_t)w * kBlockEntries, lane0, T, my_off, packed,
+                            m, w, live, base, G);
     } else {
-        block_steps<SF, OW, false>(a, s_tab, s_p0, s_p1, s_S, a.pl_j, a.pl_o, first, lane0, T, my_off, packed, m, w,
-                                   live, base, G);
+        block_steps<SF, OW>(a, s_tab, s_p0, s_p1, s_S, a.pl_j, a.pl_o, first, lane0, T, my_off, packed, m, w,
+                            live, base, G);
     }
     if (live) pos_final[m] = (G & 1) ? s_p1[m] : s_p0[m];   // the buffer the last step wrote
     if (threadIdx.x == 0) *step_base = base + (uint64_t)G;

@@ -299,3 +299,25 @@ def test_parameter_derivatives_over_type_counts(nt, N):
             act = sc[..., w][iu] > 0
             assert np.all(d[act] <= 1e-5 * sc[..., w][iu][act])
             assert np.all(d[~act & (tab.kind[iu] != W.KIND_SWAP)] == 0.0)
+
+
+def test_model_calls_at_a_loaded_state():
+    # load, then the products at that state, without autograd's functions: against them, with the positions
+    # within and beyond the list's reach and a changed theta
+    from paper_1912_08569_amd.autograd import swap_energy, swap_forces
+    s = _mixture()
+    M = _model(s)
+    assert M.L.dtype == torch.float32 and M.L.tolist() == [float(np.float32(s.L))] * 3 and M.L.device == M.S.pos.device
+    g = torch.Generator().manual_seed(3)
+    for shift, scale in ((0.01, 1.0), (0.7, 1.2)):
+        x = (M.positions() + shift).requires_grad_(True)
+        th = (M.theta() * scale).requires_grad_(True)
+        v = torch.randn(x.shape, generator=g).to(x.device)
+        F = swap_forces(M, x, th)
+        gx, gt = torch.autograd.grad((F * v).sum(), [x, th])
+        ge, = torch.autograd.grad(swap_energy(M, x, th), [th])
+        M.load(x, th)
+        assert torch.equal(M.hvp(v), -gx)
+        for got, want in ((M.param_vjp(v), gt), (M.param_grad(), ge)):
+            assert got.shape == want.shape and got.dtype == torch.float64
+            assert float((got - want).abs().max()) <= 1e-6 * float(want.abs().max())
