@@ -590,13 +590,11 @@ template <int THREADS = kBlock>   // of the block, which take part
 __device__ __forceinline__ void block_list_status(int cnt, int packed, int* status, int k_max, int4* per_block) {
     constexpr int W = THREADS / kWave;
     __shared__ int s_m[W], s_n[W], s_a[W];
-    int m = cnt, t_ns = nn_swap(packed), t_all = t_ns + nn_other(packed);
+    int m = cnt;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        m = max(m, __shfl_xor(m, o, kWave));
-        t_ns += __shfl_xor(t_ns, o, kWave);
-        t_all += __shfl_xor(t_all, o, kWave);
-    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
+    const int t_ns = __builtin_amdgcn_readlane(wave_inclusive_scan(nn_swap(packed)), kWave - 1);
+    const int t_all = t_ns + __builtin_amdgcn_readlane(wave_inclusive_scan(nn_other(packed)), kWave - 1);
     if (W > 1) {
         if ((threadIdx.x & (kWave - 1)) == 0) {
             s_m[threadIdx.x / kWave] = m;
@@ -627,9 +625,9 @@ __device__ __forceinline__ void block_list_status(int cnt, int packed, int* stat
 __global__ __launch_bounds__(1024) void k_list_status(const int4* __restrict__ per_block, int nb, int k_max,
                                                      int* __restrict__ status) {
     __shared__ int red[1024 / kWave];
-    __shared__ long long red_ns[1024 / kWave], red_all[1024 / kWave];
+    __shared__ double red_ns[1024 / kWave], red_all[1024 / kWave];
     int m = 0;
-    long long t = 0, all = 0;
+    double t = 0, all = 0;   // whole numbers below 2^53
     for (int b = threadIdx.x; b < nb; b += 4 * 1024) {   // four reads under way
         int4 v[4];
 #pragma unroll
@@ -642,27 +640,27 @@ __global__ __launch_bounds__(1024) void k_list_status(const int4* __restrict__ p
         }
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        m = max(m, __shfl_xor(m, o, kWave));
-        t += __shfl_xor(t, o, kWave);
-        all += __shfl_xor(all, o, kWave);
-    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
+    t = wave_sum(t);
+    all = wave_sum(all);
     if ((threadIdx.x & (kWave - 1)) == 0) {
         red[threadIdx.x / kWave] = m;
         red_ns[threadIdx.x / kWave] = t;
         red_all[threadIdx.x / kWave] = all;
     }
     __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    const bool in = threadIdx.x < 1024 / kWave;
+    m = in ? red[threadIdx.x] : 0;
+    t = wave_sum(in ? red_ns[threadIdx.x] : 0.0);
+    all = wave_sum(in ? red_all[threadIdx.x] : 0.0);
+#pragma unroll
+    for (int o = 1024 / kWave / 2; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 1024 / kWave; ++w) {
-            m = max(m, red[w]);
-            t += red_ns[w];
-            all += red_all[w];
-        }
         status[RC_ST_KMAX] = max(status[RC_ST_KMAX], m);
         if (m > k_max) status[RC_ST_FLAGS] |= RC_FLAG_NLIST_OVERFLOW;
-        status[RC_ST_NSWAP] = (int)min(t, (long long)0x7fffffff);
-        status[RC_ST_NLIST] = (int)min(all, (long long)0x7fffffff);
+        status[RC_ST_NSWAP] = (int)fmin(t, 2147483647.0);
+        status[RC_ST_NLIST] = (int)fmin(all, 2147483647.0);
     }
 }
 
