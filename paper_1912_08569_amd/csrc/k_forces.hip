@@ -501,14 +501,15 @@ static hipError_t launch_sums(const ForceArgs& a, bool batch, hipStream_t s) {
 }
 
 // Particles per wavefront, by the lists' mean length: those that hold about half a row of 64 entries (8 to 32) while
-// that makes at most 4096 wavefronts (four per SIMD); lists shorter than a particle or so leave too little to share.
+// that makes at most 4096 wavefronts (four per SIMD); lists shorter than a particle or so leave too little to share
+// once a few thousand particles fill the chip's compute units.
 // A wavefront's time is its rows of 64 entries one after the other, each as long as its longest partner walk, so a
 // chip with idle SIMDs wants more wavefronts with fewer rows.  us without ev at 8, 16, 32, 64 particles per wavefront
 // (entries per particle): 0.6 (assembly) 4000 particles 5.8, 5.7, 5.8, 6.0; 32000 6.9, 6.5, 6.4, 6.3; 128000 13.5, 9.9,
 // 7.5, 6.8; 0.9 (dumbbells) 4000 6.7, 6.6, 7.0, 8.0; 64000 10.8, 8.3, 7.8, 8.5; 4.8 (reactive, density 0.25) 4000 14.2,
 // 18.8, 26.0, 38.8; 32000 16.8, 20.8, 25.6, 38.7; 64000 28.3, 23.7, 27.7, 39.8; 256000 79.5, 65.0, 53.7, 48.8.
 static int gather_owners(int N, float list_len) {
-    if (list_len < 0.8f) return kWave;
+    if (list_len < 0.8f) return N <= 5120 ? 16 : kWave;
     int ow = 32;
     while (ow > 8 && (float)ow * list_len > 44.0f) ow /= 2;
     while (ow < kWave && (long)N > 4096L * ow) ow *= 2;
