@@ -161,8 +161,9 @@ int rc_get_rlist(const rc_ctx* ctx, int a, int b, double* r_list);
 /* Gather width of the fused step kernel: the flattened (particle, list slot)
  * entries each lane of a wavefront evaluates per pass (1, 2 or 4; default 2).
  * A tuning knob only: every width sums each particle's terms in the same
- * order, so results are bit-identical.  (Systems too small to fill the GPU
- * take one entry per lane whatever the width.)  RC_ERR_ARG for other values.        */
+ * order, so results are bit-identical.  (Where a wavefront holds fewer than 64
+ * particles, by the system's size and its lists' length, lanes take one entry
+ * whatever the width.)  RC_ERR_ARG for other values.                          */
 int rc_set_gather_width(rc_ctx* ctx, int width);
 /* Mean list entries per particle (status[RC_ST_NLIST] / N) of the list that the
  * context's next calls use, by which they choose among kernels of equal results:

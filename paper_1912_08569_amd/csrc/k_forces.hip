@@ -717,7 +717,8 @@ __global__ __launch_bounds__(kWave) void k_step_few(StepArgs a) {
 // Bound by one wavefront's instructions and reads.  Records of the entries with
 // fixed places and the partners' own partners, which take three dependent reads
 // out, gained 0.3 us; 32 particles per wavefront lost once the mixture had
-// aggregated (20011 dumbbells: 13.1 us), as some then hold two rows.
+// aggregated, as some then hold two rows (20011 dumbbells: 13.1 us per step; 10.0
+// with 16, 11.9 in two launches).
 constexpr int kFusedOwn = 16;
 __global__ __launch_bounds__(kWave) void k_step_fused(StepArgs a) {
     constexpr int OW = kFusedOwn;
@@ -921,8 +922,10 @@ static const void* few_fn(int ow) {
 //          4.8 (0.25) 4000 47.8, 29.7, 22.5, 17.3; 45000 48.4, 33.2, 26.5, 29.0; 110000 52.5, 35.7, 42.5, 46.2
 //          10 (network) 4000 29.0, 23.3, 17.6, 15.1; 60000 31.1, 25.7, 21.1, 23.6; 160000 36.3, 31.7, 34.5, 43.3
 //   sums   0.9 (dumbbells) 110000 12.1, 12.4, 15.2, 21.7; 4.8 16000 20.4, 15.4, 12.8, 11.1; 80000 22.1, 18.3, 17.1, 19.6
-static int step_particles(int N, float list_len) {
-    if (list_len < 1.1f) return kStepBlock;
+//          1.3 (dumbbells, aggregated) 90000 13.0, 13.1; 131072 13.8, 14.4; 150000 14.1, 15.1; 1.7 (reactive, 0.13)
+//          110000 12.1, 12.7; 2.1 (0.15) 96000 13.8, 13.1 (shorter ones up to 81920 take one launch, fused_sums)
+static int step_particles(int N, int form, float list_len) {
+    if (list_len < (form == RC_FORM_SUMS ? 1.9f : 1.1f)) return kStepBlock;
     int ow = 32;
     while (ow > 8 && (float)ow * list_len > 44.0f) ow /= 2;
     while (ow < kStepBlock && (long)N > 5120L * ow) ow *= 2;
@@ -953,7 +956,7 @@ static bool fused_sums(int N, float list_len) { return list_len <= 2.5f && N <= 
 
 StepKernel step_kernel(bool batch, bool ev, int width, int form, int N, float list_len) {
     StepKernel k;
-    const int few = batch ? kStepBlock : step_particles(N, list_len);
+    const int few = batch ? kStepBlock : step_particles(N, form, list_len);
     if (!batch && !ev && form == RC_FORM_SUMS && fused_sums(N, list_len)) {
         k.particles = kFusedOwn;
         k.fn = reinterpret_cast<const void*>(&k_step_fused);
