@@ -911,12 +911,16 @@ static const void* few_fn(int ow) {
 }
 
 // Particles per wavefront of a plain step; list_len: mean list entries per particle.  k_step_few at the particles
-// that hold about half a row of 64 entries (8 to 32), as long as that makes at most 5120 wavefronts (five per SIMD);
-// lists of fewer entries than particles leave too little to share.  By the length, not by the density: the walk
-// kernel of the assembly mixture, whose colloids make the largest list radius a poor guide, was slower by 5-9 %.
+// that hold about half a row of 64 entries (8 to 32), as long as that makes at most 5120 wavefronts (five per SIMD; 3584
+// for lists of about one entry, which have less to gain); lists of fewer entries than particles leave too little to
+// share.  By the length, not by the density: the walk kernel of the assembly mixture, whose colloids make the largest
+// list radius a poor guide, was slower by 5-9 %.
 // us per step of a run with 64, 32, 16, 8 particles per wavefront:
 //   walk   0.8 entries (assembly mixture) 8000 particles 8.0, 8.1, 8.1, 8.1; 30000 8.4, 8.7, 9.0, 9.8; 80000 9.0,
 //          9.6, 10.7, 14.7
+//          0.84 (dumbbells, thin skin) 8000 7.9, 8.4; 100000 9.8, 9.7; 160000 9.4, 11.0; 0.89 (dumbbells) 40000 10.3, 9.4;
+//          110000 10.1, 9.9; 0.93 (assembly, thick skin) 8000 7.8, 7.5, 7.5; 100000 9.3, 8.8; 131072 9.2, 9.4
+//          1.2 (assembly, aggregated) 8000 8.7, 7.8, 7.7; 80000 10.3, 8.9, 9.5; 160000 10.8, 10.4
 //          1.2 (reactive, density 0.1) 4000 13.4, 10.3, 10.2, 9.8; 80000 14.7, 12.5, 13.4, 18.4; 160000 17.2, 15.3, ..
 //          2.3 (0.15) 4000 21.5, 16.2, 12.4, 12.2; 80000 23.8, 19.0, 17.2, 24.8; 110000 24.1, 20.3, 23.1, 30.5
 //          4.8 (0.25) 4000 47.8, 29.7, 22.5, 17.3; 45000 48.4, 33.2, 26.5, 29.0; 110000 52.5, 35.7, 42.5, 46.2
@@ -925,10 +929,11 @@ static const void* few_fn(int ow) {
 //          1.3 (dumbbells, aggregated) 90000 13.0, 13.1; 131072 13.8, 14.4; 150000 14.1, 15.1; 1.7 (reactive, 0.13)
 //          110000 12.1, 12.7; 2.1 (0.15) 96000 13.8, 13.1 (shorter ones up to 81920 take one launch, fused_sums)
 static int step_particles(int N, int form, float list_len) {
-    if (list_len < (form == RC_FORM_SUMS ? 1.9f : 1.1f)) return kStepBlock;
+    if (list_len < (form == RC_FORM_SUMS ? 1.9f : 0.87f)) return kStepBlock;
     int ow = 32;
     while (ow > 8 && (float)ow * list_len > 44.0f) ow /= 2;
-    while (ow < kStepBlock && (long)N > 5120L * ow) ow *= 2;
+    const long wavefronts = list_len < 1.1f ? 3584 : 5120;
+    while (ow < kStepBlock && (long)N > wavefronts * ow) ow *= 2;
     return ow;
 }
 
