@@ -87,12 +87,12 @@ __global__ __launch_bounds__(kWave * NW) void k_forces_gather(ForceArgs a) {
 // and pass as in wave_gather (a lane per centre evaluated its own before: the
 // wavefront took its longest list's time), and every lane sums its centre's
 // terms from LDS in slot order.  The ordinary entries, which need no sum over
-// them, stay with their centre's lane, four requested at a time and the first
-// four on their way beside the swap partners: flat they took passes that short
-// swap ranges leave no others for, 23.4 us against 14.5 at 4032 beads of the
-// network (9.6 entries each, few of them swap) and 26.9 against 16.9 at 67200.
-// The active partners of centres with two or
-// more of them are kept in an LDS pool; the wave then enumerates every (j<k)
+// them, follow the same way in short lists (FLAT); else they stay with their
+// centre's lane, four requested at a time and the first four on their way beside
+// the swap partners: flat they took passes that short swap ranges leave no others
+// for, 23.4 us against 14.5 at 4032 beads of the network (9.6 entries each, few
+// of them swap) and 26.9 against 16.9 at 67200.  The active partners of centres
+// with two or more of them are kept in an LDS pool; the wave then enumerates every (j<k)
 // triplet of its 64 centres across its lanes for the energy and the virial,
 // and adds up each partner's w of the others, which gives the force on it in
 // one product.  It leaves with global atomics, or stays in LDS for a partner
@@ -108,15 +108,15 @@ __global__ __launch_bounds__(kWave * NW) void k_forces_gather(ForceArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kPool = 512;   // staged partners per wave and round
 
-template <bool SPREAD, int PL>
+template <bool SPREAD, int PL, bool FLAT>
 __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_ev) {
-    constexpr int W = PL * kWave, AH = 4;   // swap entries per pass, other entries requested at a time
+    constexpr int W = PL * kWave, AH = 4;   // flat entries per pass, a lane's own entries requested at a time
     extern __shared__ DevEntry s_tab[];
     __shared__ int p_j[kPool];
     __shared__ float p_w[kPool], p_g[kPool], p_dx[kPool], p_dy[kPool], p_dz[kPool], p_s[kPool];
     __shared__ int l_pool[kWave], l_k[kWave], l_tri[kWave + 1], l_out;
     __shared__ float l_f[kWave][4];
-    __shared__ int s_off[kWave], s_j[W];
+    __shared__ int s_off[kWave], s_ns[FLAT ? kWave : 1], s_j[W];
     __shared__ unsigned char s_own[W];
     __shared__ float4 s_pos[kWave];
     __shared__ float s_c[8][W];   // phi'/r, phi, d, w, w'/r, 1 for an active swap partner
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     float4 pi = live ? a.pos[i] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int ti = ptype(pi.w);
     const int packed = live ? a.nn[i] : 0;
-    const int ns = nn_swap(packed), no = nn_other(packed);
+    const int ns = nn_swap(packed), cnt = FLAT ? ns + nn_other(packed) : ns, no = FLAT ? 0 : nn_other(packed);
     auto other = [&](int b, int (&j)[AH]) {   // the other range's entries from b on
 #pragma unroll
         for (int u = 0; u < AH; ++u) j[u] = b + u < no ? a.nlist[(size_t)(a.k_max - 1 - (b + u)) * a.N + i] : i;
@@ -139,11 +139,13 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     };
     int oj[AH];
     float4 op[AH];
-    other(0, oj);
-    const int inc = wave_inclusive_scan(ns), my_off = inc - ns;
+    if (!FLAT) other(0, oj);
+    const int inc = wave_inclusive_scan(cnt), my_off = inc - cnt;
     const int T = __builtin_amdgcn_readlane(inc, kWave - 1);
-    const bool fits = T <= kPool;
+    const int pinc = FLAT ? wave_inclusive_scan(ns) : inc, poff = pinc - ns;   // in the pool
+    const bool fits = __builtin_amdgcn_readlane(pinc, kWave - 1) <= kPool;
     s_off[lane] = my_off;
+    if (FLAT) s_ns[lane] = ns;
     s_pos[lane] = pi;
     float fx = 0.f, fy = 0.f, fz = 0.f, en = 0.f;
     float w6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     };
     __syncthreads();
     for (int base = 0; base < T; base += W) {
-        const int lo = max(my_off, base) - base, hi = min(my_off + ns, base + W) - base;
+        const int lo = max(my_off, base) - base, hi = min(my_off + cnt, base + W) - base;
         for (int q = lo; q < hi; ++q) s_own[q] = (unsigned char)lane;
         __syncthreads();
         int own[PL], jj[PL];
@@ -171,10 +173,12 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
             jj[u] = 0;
             if (e < T) {
                 own[u] = s_own[e - base];
-                jj[u] = a.nlist[(size_t)(e - s_off[own[u]]) * a.N + (i - lane) + own[u]];
+                int slot = e - s_off[own[u]];
+                if (FLAT && slot >= s_ns[own[u]]) slot = a.k_max - 1 - (slot - s_ns[own[u]]);
+                jj[u] = a.nlist[(size_t)slot * a.N + (i - lane) + own[u]];
             }
         }
-        if (base == 0) other_pos(0, oj, op);   // on their way beside the swap partners
+        if (!FLAT && base == 0) other_pos(0, oj, op);   // on their way beside the swap partners
 #pragma unroll
         for (int u = 0; u < PL; ++u) {
             pj[u] = pi;
@@ -217,7 +221,7 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
             add_pair(s_c[0][q], s_c[1][q], dx, dy, dz);
             if (s_c[7][q] != 0.0f) {
                 if (fits) {
-                    const int at = my_off + nact;   // at most ns active partners
+                    const int at = poff + nact;   // at most ns active partners
                     p_j[at] = s_j[q];
                     p_w[at] = s_c[5][q];
                     p_g[at] = s_c[6][q];
@@ -230,7 +234,7 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
         }
         __syncthreads();
     }
-    if (T == 0) other_pos(0, oj, op);
+    if (!FLAT && T == 0) other_pos(0, oj, op);
     for (int b = 0; b < no; b += AH) {
         if (b > 0) {
             other(b, oj);
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(kWave) void k_forces_triplet(ForceArgs a, int want_
     bool done = (k == 0);
     while (round_start < total) {
         bool mine = !done;
-        int next = total, pool = my_off;
+        int next = total, pool = poff;
         if (!fits) {
             // the admitted lanes form a run; the next round starts at the first lane left out
             mine = !done && off >= round_start && off + k <= round_start + kPool;
@@ -403,12 +407,16 @@ hipError_t launch_forces_triplet(const ForceArgs& a, hipStream_t s) {
     const size_t shm = sizeof(DevEntry) * a.tab.nt * a.tab.nt;
     // sending the partners' forces together costs a barrier and pays where the atomics are the bound: us per call
     // apart and together, 32768 unequal 24.2, 24.8, 8000 22.7, 23.4; 200003 unequal 73.3, 68.0, reactive 53.8, 50.4.
-    // Eight entries per lane and pass where the lists are long: two passes more of a wavefront's entries cost 2 us,
-    // a lane's unused places 0.4.  us per call with two and eight, lists of 1.1 entries (4000) 8.8, 9.4, of 1.7 9.1,
-    // 9.7 (32000: 11.1, 10.9), of 2.4 11.6, 10.8, of 4.9 17.9, 15.2, of 7.3 28.7, 23.1.  Above 65536 the wavefronts
-    // hide the passes and eight entries' LDS takes their places: 100003 of 4.9 23.3, 32.2.
-    auto kernel = k_forces_triplet<true, 2>;
-    if (a.N < 65536) kernel = a.list_len < 2.2f ? k_forces_triplet<false, 2> : k_forces_triplet<false, 8>;
+    // Lists whose entries fill a pass or two stay flat: taking the kinds apart adds the reads of the ordinary ones to
+    // the chain.  us per call, flat and apart: 0.6 entries (assembly) 16000 7.7, 8.6, 1000003 46.7, 54.9; 0.9
+    // (dumbbells) 16000 8.6, 9.1; 1.7 (reactive) 16000 10.1, 10.2; 4.9 (unequal) 100003 39.0, 27.2; 5.9 (network) 16000
+    // 14.4, 9.4, 200003 33.0, 17.7.  The long ones take eight swap entries per lane and pass below 65536: two passes
+    // more of a wavefront's entries cost 2 us, a lane's unused places 0.4 (two and eight: lists of 2.4 entries 11.6,
+    // 10.8, of 4.9 17.9, 15.2, of 7.3 28.7, 23.1).  Above, the wavefronts hide the passes and eight entries' LDS takes
+    // their places: 100003 of 4.9 23.3, 32.2.
+    const bool flat = a.list_len < 2.2f;
+    auto kernel = flat ? k_forces_triplet<true, 2, true> : k_forces_triplet<true, 2, false>;
+    if (a.N < 65536) kernel = flat ? k_forces_triplet<false, 2, true> : k_forces_triplet<false, 8, false>;
     hipLaunchKernelGGL(kernel, dim3(nblk(a.N, kWave)), dim3(kWave), shm, s, a, a.ev_part ? 1 : 0);
     return hipGetLastError();
 }

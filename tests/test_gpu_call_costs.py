@@ -206,3 +206,18 @@ def test_walk_steps_of_one_entry_per_particle_share_wavefronts():
                    for _ in range(21))
         t.append(y[10] / 16 * 1e3)
     assert t[1] < 0.97 * t[0], t
+
+
+def test_short_lists_cost_the_triplet_kernel_one_pass():
+    """Half an entry per particle (16000 of the assembly mixture): forces by the triplet kernel take 7.7 us with the
+    entries of both kinds in one pass, 8.6 with the kinds apart and 9.2 as for long lists."""
+    import workloads as W
+    from paper_1912_08569_amd import System, api
+    S = System.from_workload(W.assembly_mixture(N=16000, seed=4))
+    S.build()
+    t = []
+    for entries in (50.0, 0.6):
+        S.ctx.set_list_length(-1.0)
+        S.ctx.set_list_length(entries)
+        t.append(_gpu_us(lambda: api.rc_compute_forces(S.ctx, S.pos, S.nlist, S.nn, S.box, S.force, None, 0, S.status)))
+    assert t[1] < 0.88 * t[0], t

@@ -105,9 +105,9 @@ def test_forces_by_list_length(N):
             assert bool(((o[3] - out[0][3]).abs() <= bound).all())
 
 
-@pytest.mark.parametrize("name", ["reactive-2003", "dense-1000", "network-21", "network-300"])
+@pytest.mark.parametrize("name", ["reactive-2003", "reactive-65601", "dense-1000", "network-21", "network-300"])
 def test_triplet_kernel_by_list_length(name):
-    # two and eight swap entries per lane and pass (lists named short and long), a lane's ordinary entries in
+    # entries of both kinds in flat passes and the kinds apart (lists named short and long), a lane's ordinary entries in
     # several rounds of four (the network's), ragged last wavefronts, pools that hold the swap ranges and do not
     from paper_1912_08569_amd import api
     from oracle import swap_ref
