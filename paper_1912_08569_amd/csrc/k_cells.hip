@@ -1002,7 +1002,7 @@ static void end_status(int* status, int k_max, const int4* per_block, int nb, hi
 // 23.2; 6.1 (reactive, density 0.25) 110000 31.5, 31.5; 8.6 (three reactive types) 130000 39.3, 41.1 and 160000 45.8,
 // 44.1; 9.8 (reactive, 0.4) 160000 49.8, 50.9 and 200000 59.3, 55.2; 10.3 (network) 160000 49.6, 52.9 and 200000 62.0,
 // 59.5.  The line goes through those.
-static bool few_list(int N, float cand) { return (float)N <= 28000.0f + 13500.0f * cand; }
+static bool few_list(int N, float cand) { return (float)N <= 33000.0f + 12800.0f * cand; }
 
 hipError_t launch_nlist(const NlistArgs& a, hipStream_t s) {
     begin_status(a.status, a.status_mode, a.back.pos != nullptr, s);
