@@ -236,13 +236,13 @@ static const void* block_fn(int N, int form) {
 bool step_block_fits(int N, int nt, int form, float list_len) {
     if (N < 1 || N > kBlockMaxN) return false;
     // A wavefront here holds 32 or 64 particles, launches of k_step_few as few as 8.  The two-pass form is faster here
-    // while the entries of an average wavefront fit the registers (block_steps_row), the walk form, which evaluates
-    // every row by itself, up to about one row.  us per step here and launched (entries per wavefront): sums 1000
-    // of the assembly mixture (51) 4.1, 8.6; 1000 reactive of density 0.15 (148) 6.7, 9.6 and of density 0.25 (310) 16.1,
-    // 9.9; 433 in a drop (126) 8.1, 9.3; 500 of density 0.25 (158) 10.5, 9.7; walk 1000 dumbbells (62) 7.9, 8.8; 300
+    // while the entries of an average wavefront fit the registers (block_steps_row) but for an eighth, the walk form,
+    // which evaluates every row by itself, up to about one row.  us per step here and launched (entries per wavefront):
+    // sums 1000 of the assembly mixture (51) 4.1, 8.6; 1000 reactive of density 0.15 (148) 6.7, 9.6 and of density 0.25 (310) 16.1,
+    // 9.9; 433 in a drop (126) 7.9, 9.3; 500 of density 0.25 (158) 10.5, 9.7; walk 1000 dumbbells (62) 7.9, 8.8; 300
     // reactive of density 0.1 (41) 7.9, 9.4; 1000 of them (79) 10.0, 9.4; 300 of density 0.15 (77) 13.1, 11.0
     const int ow = block_particles(N);
-    if ((float)ow * list_len > (form == RC_FORM_SUMS ? (float)(block_rows(ow) * kWave) : 72.0f)) return false;
+    if ((float)ow * list_len > (form == RC_FORM_SUMS ? 1.125f * (float)(block_rows(ow) * kWave) : 72.0f)) return false;
     const void* fn = block_fn(N, form);
     hipFuncAttributes at{};
     if (hipFuncGetAttributes(&at, fn) != hipSuccess) return false;
