@@ -172,7 +172,7 @@ int ensure_plist(rc_ctx* c, int N, int k_max);
 // the packed copy of (nlist, nn, k_max, N): made on the stream unless it is the current one
 int packed_list_for(rc_ctx* c, const int* nlist, const int* nn, int k_max, int N, hipStream_t s);
 void free_ctx_buffers(rc_ctx* c);       // every device buffer the context owns
-// a list's mean entries per particle, for the choice of kernels; within 15 % of the last one it is taken as the same,
+// a list's mean entries per particle, for the choice of kernels; within 7 % of the last one it is taken as the same,
 // so that a list that breathes does not move a system from one kernel to another at every build
 void note_list_len(rc_ctx* c, double len);
 // the context's pinned host words and wait event: the status copy, then kHostWords that kernels write,

@@ -163,7 +163,7 @@ int ensure_ssum(rc_ctx* c, size_t n) {
 }
 
 void note_list_len(rc_ctx* c, double len) {
-    if (c->list_len > 0.0f && len > 0.85 * c->list_len && len < 1.15 * c->list_len) return;
+    if (c->list_len > 0.0f && len > 0.93 * c->list_len && len < 1.07 * c->list_len) return;
     c->list_len = (float)len;
 }
 
