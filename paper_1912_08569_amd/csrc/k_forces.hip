@@ -935,9 +935,10 @@ static const void* few_fn(int ow) {
 //          10 (network) 4000 29.0, 23.3, 17.6, 15.1; 60000 31.1, 25.7, 21.1, 23.6; 160000 36.3, 31.7, 34.5, 43.3
 //   sums   0.9 (dumbbells) 110000 12.1, 12.4, 15.2, 21.7; 4.8 16000 20.4, 15.4, 12.8, 11.1; 80000 22.1, 18.3, 17.1, 19.6
 //          1.3 (dumbbells, aggregated) 90000 13.0, 13.1; 131072 13.8, 14.4; 150000 14.1, 15.1; 1.7 (reactive, 0.13)
-//          110000 12.1, 12.7; 2.1 (0.15) 96000 13.8, 13.1 (shorter ones up to 81920 take one launch, fused_sums)
+//          110000 12.1, 12.7; 2.1 (0.15) 96000 13.8, 13.1 (such lists up to 81920 particles take one launch, fused_sums,
+//          but for log steps: the sums of 512 dumbbells 5.1, 4.9)
 static int step_particles(int N, int form, float list_len) {
-    if (list_len < (form == RC_FORM_SUMS ? 1.9f : 0.87f)) return kStepBlock;
+    if (list_len < (form == RC_FORM_SUMS && N > 5120 * kFusedOwn ? 1.9f : 0.87f)) return kStepBlock;
     int ow = 32;
     while (ow > 8 && (float)ow * list_len > 44.0f) ow /= 2;
     const long wavefronts = list_len < 1.1f ? 3584 : 5120;
